@@ -9,8 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(OUT_DIR, "libcis.so")
-SOURCES = [os.path.join(CSRC, n) for n in ("cis_api.hip", "cis_kernels.hip", "cis_adjoint.hip")]
-HEADERS = [os.path.join(CSRC, n) for n in ("cis_internal.h", "cis_device.h", "cis_adjoint_math.h", "cis_adjoint.h")] + [
+SOURCES = [os.path.join(CSRC, n) for n in ("cis_api.hip", "cis_kernels.hip", "cis_macro.hip", "cis_adjoint.hip")]
+HEADERS = [os.path.join(CSRC, n) for n in ("cis_internal.h", "cis_device.h", "cis_adjoint_math.h", "cis_adjoint.h", "cis_macro.h")] + [
     os.path.join(os.path.dirname(HERE), "include", "cis.h")]
 
 FLAGS = [

@@ -798,8 +798,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_ysub(int64_t nc, int64_t off, co
 }  // namespace
 
 void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, double* out, double* tmp, double* cell,
-                              const int64_t* color_off, int64_t n_colors, int micro_pairs, int macro_pairs,
-                              hipStream_t st) {
+                              const int64_t* color_off, int64_t n_colors, int micro_pairs, int macro_pairs, Flow& flow,
+                              int32_t* flag, hipStream_t st) {
   const int64_t nc = d.nc, P = d.nc * d.nv;
   double* gW = cell;
   double* gq = gW + 6 * nc;
@@ -818,19 +818,22 @@ void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, dou
   if (macro_pairs > 0) {
     // t = B^T z (W part), then Mac^T u = t and x_phi = z + M_c^T u
     hipLaunchKernelGGL((k_cell_vjp<true, true>), dim3((unsigned)nc), dim3(kBlock), 0, st, d, b, a);
-    if (d.mf == 4)
-      hipLaunchKernelGGL(k_adj_macro_prep<4>, dim3(ncb), dim3(kBlock), 0, st, d, b, rc, mD);
-    else
-      hipLaunchKernelGGL(k_adj_macro_prep<kMaxFaces>, dim3(ncb), dim3(kBlock), 0, st, d, b, rc, mD);
-    launch_axpby(6 * nc, 0.0, gW, 0.0, u, st);
-    for (const int64_t c : sweep_sequence(color_off, n_colors, macro_pairs)) {
-      const int64_t n = color_off[c + 1] - color_off[c];
+    if (flow.plan.m == 0 || launch_adj_macro_flow(d, b, flow, gW, u, macro_pairs, flag, st) != hipSuccess) {
+      (void)hipGetLastError();
       if (d.mf == 4)
-        hipLaunchKernelGGL(k_adj_macro_sweep<4>, dim3((unsigned)((4 * n + 63) / 64)), dim3(64), 0, st, d, b,
-                           (const double*)rc, (const double*)mD, (const double*)gW, u, color_off[c], color_off[c + 1]);
+        hipLaunchKernelGGL(k_adj_macro_prep<4>, dim3(ncb), dim3(kBlock), 0, st, d, b, rc, mD);
       else
-        hipLaunchKernelGGL(k_adj_macro_sweep<kMaxFaces>, dim3((unsigned)((8 * n + 63) / 64)), dim3(64), 0, st, d, b,
-                           (const double*)rc, (const double*)mD, (const double*)gW, u, color_off[c], color_off[c + 1]);
+        hipLaunchKernelGGL(k_adj_macro_prep<kMaxFaces>, dim3(ncb), dim3(kBlock), 0, st, d, b, rc, mD);
+      launch_axpby(6 * nc, 0.0, gW, 0.0, u, st);
+      for (const int64_t c : sweep_sequence(color_off, n_colors, macro_pairs)) {
+        const int64_t n = color_off[c + 1] - color_off[c];
+        if (d.mf == 4)
+          hipLaunchKernelGGL(k_adj_macro_sweep<4>, dim3((unsigned)((4 * n + 63) / 64)), dim3(64), 0, st, d, b,
+                             (const double*)rc, (const double*)mD, (const double*)gW, u, color_off[c], color_off[c + 1]);
+        else
+          hipLaunchKernelGGL(k_adj_macro_sweep<kMaxFaces>, dim3((unsigned)((8 * n + 63) / 64)), dim3(64), 0, st, d, b,
+                             (const double*)rc, (const double*)mD, (const double*)gW, u, color_off[c], color_off[c + 1]);
+      }
     }
     hipLaunchKernelGGL(k_adj_lift, dim3((unsigned)nc, nch), dim3(kBlock), 0, st, d, (const double*)u, out);
   }

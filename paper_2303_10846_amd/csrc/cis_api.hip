@@ -16,6 +16,7 @@
 #include "../../include/cis.h"
 #include "cis_adjoint.h"
 #include "cis_internal.h"
+#include "cis_macro.h"
 
 using namespace cis;
 
@@ -149,8 +150,8 @@ template <class T> cis_status upload(T** p, const std::vector<T>& v, hipStream_t
   return CIS_OK;
 }
 
-__global__ void k_zero_i32(int32_t* p, int n) {
-  int i = threadIdx.x;
+__global__ void k_zero_i32(int32_t* p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
 }
 
@@ -183,6 +184,7 @@ struct cis_state {
   Dev dev{};
   Bufs buf{};
   Work work{};
+  Flow flow{};
   // library-owned device arrays
   int32_t *d_cell_nb = nullptr, *d_cell_face = nullptr, *d_face_cell = nullptr, *d_face_bc = nullptr,
           *d_spatial = nullptr;
@@ -354,7 +356,7 @@ cis_status wall_faces(cis_state* s, int32_t tag, std::vector<cis_wall_face>& out
 // Steps 2-6, n_iter times, on the state's stream, with the work arrays `w`; mark(it, k) runs between the stages.
 template <class Mark> cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t n_iter, Mark&& mark) {
   const cis_mesh* m = s->mesh;
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s->stream, w.flag, 4);
+  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s->stream, w.flag, (int64_t)4);
   return dispatch(s, [&](auto* tp) {
     using T = std::remove_pointer_t<decltype(tp)>;
     for (int32_t it = 0; it < n_iter; ++it) {
@@ -363,7 +365,11 @@ template <class Mark> cis_status enqueue_iterations(cis_state* s, const Work& w,
       mark(it, 1);
       launch_face<T>(s->dev, s->buf, w, s->stream);
       mark(it, 2);
-      launch_macro(s->dev, s->buf, w, m->color_off.data(), m->n_colors, s->num.n_macro, s->stream);
+      // one dataflow launch where the mesh's wavefronts are resident at once, else a launch per colour
+      if (s->flow.plan.m == 0 || launch_macro_flow(s->dev, s->buf, w, s->flow, s->num.n_macro, s->stream) != hipSuccess) {
+        (void)hipGetLastError();
+        launch_macro(s->dev, s->buf, w, m->color_off.data(), m->n_colors, s->num.n_macro, s->stream);
+      }
       mark(it, 3);
       launch_residual<T>(s->dev, s->buf, w, s->buf.resG, s->buf.resR, 0, s->stream);
       mark(it, 4);
@@ -383,6 +389,7 @@ cis_status finish_iterations(cis_state* s, const Work& w, int32_t n_iter, double
   if (res_hist)
     HIP_TRY(hipMemcpyAsync(res_hist, w.res, 6 * (size_t)n_iter * sizeof(double), hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(hipStreamSynchronize(s->stream));
+  if (flag[0] & kFlowStuck) return fail(CIS_E_DEVICE, "a macro sweep waited for a workgroup that never ran");
   if (flag[0]) return fail(CIS_E_NONFINITE, "non-finite or non-positive state (flag " + std::to_string(flag[0]) + ")");
   return CIS_OK;
 }
@@ -950,6 +957,17 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
   d.lim_frozen = nullptr;
   fill_dev_numerics(s);
   s->buf = Bufs{buf->G, buf->R, buf->dG, buf->dR, buf->resG, buf->resR, buf->faceG, buf->faceR, buf->W, buf->q};
+  s->flow.plan = flow_plan(d, m->color_off.data(), m->n_colors);
+  if (s->flow.plan.m && !s->flow.plan.local) {
+    // tag 0 in every word: no version of the first launch
+    if (own_alloc(s, &s->flow.words, (size_t)kFlowWords * nc) != CIS_OK) {
+      delete s;
+      return CIS_E_DEVICE;
+    }
+    const int64_t n = 2 * kFlowWords * nc;
+    hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s->stream,
+                       reinterpret_cast<int32_t*>(s->flow.words), n);
+  }
   launch_upwind_codes(d, s->stream);
   if (hipStreamSynchronize(s->stream) != hipSuccess || hipGetLastError() != hipSuccess) {
     delete s;
@@ -1086,7 +1104,7 @@ cis_status cis_iterate(cis_state* s, int32_t n_iter, double* res_hist) {
     (void)hipStreamSynchronize(s->stream);
     const int64_t nmac = (int64_t)sweep_sequence(m->color_off.data(), m->n_colors, s->num.n_macro).size();
     const int64_t nmic = (int64_t)sweep_sequence(m->color_off.data(), m->n_colors, s->num.n_micro).size();
-    const int64_t per_it[6] = {1, 1, 3 + nmac, 1, nmic, 3};
+    const int64_t per_it[6] = {1, 1, s->flow.plan.m ? 1 : 3 + nmac, 1, nmic, 3};
     for (int32_t it = 0; it < n_iter; ++it)
       for (int k = 0; k < 6; ++k) {
         float ms = 0.0f;
@@ -1389,12 +1407,13 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
   auto precond = [&](const double* in, double* out) {
     if (macro_pairs > 0)
       launch_adj_block_precond(s->dev, s->buf, in, out, ptmp, pcell, s->mesh->color_off.data(), s->mesh->n_colors,
-                               precond_pairs, macro_pairs, q);
+                               precond_pairs, macro_pairs, s->flow, s->work.flag, q);
     else if (precond_pairs == 0)
       launch_precond(s->dev, s->buf, in, out, q);
     else
       launch_adj_sweeps(s->dev, s->buf, in, out, s->mesh->color_off.data(), s->mesh->n_colors, precond_pairs, q);
   };
+  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, q, s->work.flag, (int64_t)4);
   // right-hand side and the explicit parameter dependence of J
   double gpJ[3], gpL[3] = {0.0, 0.0, 0.0};
   run_vjp(s, nullptr, 1.0, sl, b);
@@ -1468,6 +1487,10 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
     beta = std::sqrt(r2);
     done = beta <= rtol * bnorm || beta == 0.0;
   }
+  int32_t flag = 0;
+  HIP_TRY(hipMemcpyAsync(&flag, s->work.flag, sizeof(flag), hipMemcpyDeviceToHost, q));
+  HIP_TRY(hipStreamSynchronize(q));
+  if (flag & kFlowStuck) return fail(CIS_E_DEVICE, "a macro sweep waited for a workgroup that never ran");
   for (int k = 0; k < 3; ++k) dJdp[k] = gpJ[k] - gpL[k];
   if (info) {
     info->iterations = iters;
