@@ -27,8 +27,20 @@ namespace cis {
 namespace {
 
 // Velocity loop of a per-face / per-cell workgroup.
-template <class F> __device__ inline void v_loop(int64_t nv, F&& body) {
-  for (int64_t k = threadIdx.x; k < nv; k += kBlock) body(k);
+template <int NT = kBlock, class F> __device__ inline void v_loop(int64_t nv, F&& body) {
+  for (int64_t k = threadIdx.x; k < nv; k += NT) body(k);
+}
+
+// A value that is the same in every lane, moved to scalar registers (its vector registers are then free).
+template <class T> __device__ inline T uniform(const T& x) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  uint32_t w[sizeof(T) / 4];
+  __builtin_memcpy(w, &x, sizeof(T));
+#pragma unroll
+  for (size_t k = 0; k < sizeof(T) / 4; ++k) w[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[k]);
+  T y;
+  __builtin_memcpy(&y, w, sizeof(T));
+  return y;
 }
 
 // theta = (rho, U, T, T_tr, T_rot, q_tr, q_rot) and tau of a cell state (Eqs. 1-5, 13)
@@ -115,54 +127,70 @@ void launch_cell_steady(const Dev& d, const Bufs& b, double* rG, double* rR, dou
 // ---------------------------------------------------------------------------
 
 template <bool HasV, bool PhiOnly = false>
-__global__ __launch_bounds__(kBlock) void k_cell_vjp(Dev d, Bufs b, AdjArgs a) {
-  __shared__ double red[(kBlock / 64) * 2 * 17];
+__global__ __launch_bounds__(kBlock, 4) void k_cell_vjp(Dev d, Bufs b, AdjArgs a) {
+  __shared__ double red[(kBlock / 64) * 19];
   const int64_t i = blockIdx.x, nv = d.nv;
   const GasC& g = d.gas;
   const double* W = b.W + 6 * i;
-  double th[NTH];
-  Prim p;
-  const double tau = cell_theta(W, b.q + 6 * i, g, th, p);
-  const double it = 1.0 / tau;
-  EqAd e;
-  e.setup(th, g);
+  // the cell's state and equilibrium constants, by one thread; kept in LDS for it to finish with
+  __shared__ EqVjp sh_e;
+  __shared__ Prim sh_p;
+  __shared__ double sh_tau;
+  if (threadIdx.x == 0) {
+    double th[NTH];
+    sh_tau = cell_theta(W, b.q + 6 * i, g, th, sh_p);
+    sh_e.setup(th, g);
+  }
   double vW[6], vq[6];
   for (int m = 0; m < 6; ++m) {
-    vW[m] = HasV && !PhiOnly ? a.vW[6 * i + m] : 0.0;
-    vq[m] = HasV && !PhiOnly ? a.vq[6 * i + m] : 0.0;
+    vW[m] = HasV && !PhiOnly ? uniform(a.vW[6 * i + m]) : 0.0;
+    vq[m] = HasV && !PhiOnly ? uniform(a.vq[6 * i + m]) : 0.0;
   }
+  __syncthreads();
+  const EqVjp e = uniform(sh_e);
+  const double it = uniform(1.0 / sh_tau);
   const double* G = (const double*)b.G + i * nv;
   const double* R = (const double*)b.R + i * nv;
-  Acc<17, false, kBlock> acc;
+  // 15 derivative sums, the tau sum and (not PhiOnly) three sums of c = u - U inside the heat-flux sums of R_q
+  constexpr int NA = PhiOnly ? 16 : 19;
+  Acc<NA, false, kBlock> acc;
   acc.zero();
   v_loop(nv, [&](int64_t k) {
     const Vel v = vel(d, k);
-    double Gs, Rs, dG[NTH], dR[NTH];
-    e.eval(v.ux, v.uy, v.uz, Gs, Rs, dG, dR);
     const double gk = G[k], rk = R[k];
     const double vg = HasV ? a.vG[i * nv + k] : 0.0, vr = HasV ? a.vR[i * nv + k] : 0.0;
-    const double cx = v.ux - p.U[0], cy = v.uy - p.U[1], cz = v.uz - p.U[2];
-    const double c2 = cx * cx + cy * cy + cz * cz;
-    const double vqc = vq[0] * cx + vq[1] * cy + vq[2] * cz;
+    const EqVjp::At x = e.at(v.ux, v.uy, v.uz);
+    double Gs, Rs;
+    e.values(x, Gs, Rs);
     // -(dR/dphi_k)^T v: the collision term, the moments of R_W and the heat-flux sums of R_q
-    const double aG = vg * it + v.w * (vW[0] + vW[1] * v.ux + vW[2] * v.uy + vW[3] * v.uz + vW[4] * v.h2 + 0.5 * c2 * vqc);
-    const double aR = vr * it + v.w * (vW[4] + vW[5] + vq[3] * cx + vq[4] * cy + vq[5] * cz);
+    double aG = vg * it, aR = vr * it;
+    double vqc = 0.0;
     if (!PhiOnly) {
+      vqc = vq[0] * x.cx + vq[1] * x.cy + vq[2] * x.cz;
+      aG += v.w * (vW[0] + vW[1] * v.ux + vW[2] * v.uy + vW[3] * v.uz + vW[4] * v.h2 + 0.5 * x.c2 * vqc);
+      aR += v.w * (vW[4] + vW[5] + vq[3] * x.cx + vq[4] * x.cy + vq[5] * x.cz);
       a.gG[i * nv + k] = -aG;
       a.gR[i * nv + k] = -aR;
     }
-#pragma unroll
-    for (int m = 0; m < NTH; ++m) acc.add(m, aG * dG[m] + aR * dR[m]);
-    acc.add(13, -(vg * (Gs - gk) + vr * (Rs - rk)) * it * it);
-    // c = u - U inside the heat-flux sums of R_q
-    const double gd = v.w * (gk - Gs), rd = v.w * (rk - Rs);
-    acc.add(14, gd * (0.5 * vq[0] * c2 + vqc * cx) + vq[3] * rd);
-    acc.add(15, gd * (0.5 * vq[1] * c2 + vqc * cy) + vq[4] * rd);
-    acc.add(16, gd * (0.5 * vq[2] * c2 + vqc * cz) + vq[5] * rd);
+    (void)e.sums(x, aG, aR, [&](int m, double t) { acc.add(m, t); });
+    acc.add(15, -(vg * (Gs - gk) + vr * (Rs - rk)) * it * it);
+    if (!PhiOnly) {
+      const double gd = v.w * (gk - Gs), rd = v.w * (rk - Rs);
+      const double q2 = 0.5 * x.c2;
+      acc.add(NA - 3, gd * (vq[0] * q2 + vqc * x.cx) + vq[3] * rd);
+      acc.add(NA - 2, gd * (vq[1] * q2 + vqc * x.cy) + vq[4] * rd);
+      acc.add(NA - 1, gd * (vq[2] * q2 + vqc * x.cz) + vq[5] * rd);
+    }
   });
-  double s[17];
-  acc.reduce(s, red);
+  __shared__ double sh_s[NA];
+  acc.reduce_to_lds(sh_s, red);
   if (threadIdx.x == 0) {
+    const Prim p = sh_p;
+    const double tau = sh_tau;
+    double s[17];
+    sh_e.finish(sh_s, s);
+    s[13] = sh_s[15];
+    for (int m = 0; m < 3; ++m) s[14 + m] = PhiOnly ? 0.0 : sh_s[NA - 3 + m];
     const double a0 = (1.0 / 3.0) * (1.0 - (1.0 - g.omega0) / g.Z);
     const double a1 = (1.0 - g.delta) * (1.0 - (1.0 - g.omega1) / g.Z);
     for (int m = 0; m < 3; ++m) {
@@ -191,10 +219,51 @@ __global__ __launch_bounds__(kBlock) void k_cell_vjp(Dev d, Bufs b, AdjArgs a) {
 // The seed of the face flux A (u.n) phi_f is -A (u.n)(v_o/V_o - v_n/V_n), plus the objective's.
 // ---------------------------------------------------------------------------
 
-template <bool HasV, int NF> __global__ __launch_bounds__(kBlock) void k_face_vjp(Dev d, Bufs b, AdjArgs a) {
-  __shared__ double red[(kBlock / 64) * 2 * 14];
-  __shared__ double sh_th[NTH + 1], sh_jac[14 * 12], sh_bar[12];
+// Interior faces.  One sweep over the row takes the 17 moments of phi_bar about a reference velocity U0 (the mean of
+// the two cells'), from which the sums S1 (Eqs. 47-49), S2 (Eqs. 51-52) and the second moments follow exactly; the
+// Jacobian of the face state is taken with one dual number per lane, lane j carrying the derivative along sum j
+// (twelve directions on one thread were a serial chain of about 100 us a face); a second sweep forms the seeds and
+// the 15 sums of the equilibrium's transposed derivative, a third the adjoint of phi_bar.  Stage: the row is kept
+// in LDS from the first sweep, and its place holds the seeds from the second to the third (each thread reads back
+// its own velocities); rows that do not fit re-read phi_bar and form the seeds twice.
+// Measured on 1 296 hexahedra x 4 140 velocities (see launch_face_vjp for the variants).
+struct FaceSums {
+  double S1[6], S2[12];
+};
+__device__ inline FaceSums face_sums(const double* m, const double* U0) {
+  FaceSums f;
+  const double rho = m[0];
+  const double dl[3] = {m[1] / rho, m[2] / rho, m[3] / rho};
+  const double trM = m[4] + m[5] + m[6];
+  f.S1[0] = rho;
+  for (int e = 0; e < 3; ++e) f.S1[1 + e] = m[1 + e] + rho * U0[e];
+  f.S1[4] = 0.5 * (trM + 2.0 * (U0[0] * m[1] + U0[1] * m[2] + U0[2] * m[3]) +
+                   rho * (U0[0] * U0[0] + U0[1] * U0[1] + U0[2] * U0[2])) + m[13];
+  f.S1[5] = m[13];
+  const double Mx[3] = {m[4] * dl[0] + m[7] * dl[1] + m[8] * dl[2], m[7] * dl[0] + m[5] * dl[1] + m[9] * dl[2],
+                        m[8] * dl[0] + m[9] * dl[1] + m[6] * dl[2]};
+  const double d2 = dl[0] * dl[0] + dl[1] * dl[1] + dl[2] * dl[2];
+  for (int e = 0; e < 3; ++e) {
+    f.S2[e] = m[10 + e] - 2.0 * Mx[e] - dl[e] * trM + 2.0 * rho * d2 * dl[e];
+    f.S2[3 + e] = m[14 + e] - dl[e] * m[13];
+    f.S2[6 + e] = m[4 + e] - rho * dl[e] * dl[e];
+  }
+  f.S2[9] = m[7] - rho * dl[0] * dl[1];
+  f.S2[10] = m[8] - rho * dl[0] * dl[2];
+  f.S2[11] = m[9] - rho * dl[1] * dl[2];
+  return f;
+}
+
+template <bool HasV, int NF, bool Stage, int NT>
+__global__ __launch_bounds__(NT, 4) void k_face_vjp(Dev d, Bufs b, AdjArgs a) {
+  extern __shared__ __align__(16) double rows[];  // Stage: G then R, nv each
+  __shared__ double red[(NT / 64) * 17];
+  __shared__ double sh_m[17], sh_jac[14 * 12], sh_bar[12], sh_tau;
+  __shared__ EqVjp sh_e;
+  __shared__ FaceSums sh_fs;
   const int64_t f = blockIdx.x, nv = d.nv;
+  double* const sG = rows;
+  double* const sR = rows + nv;
   const double* fg = d.face_geo + FGW * f;
   const double A = fg[0], nx = fg[1], ny = fg[2], nz = fg[3], s = fg[4];
   const int64_t o = d.face_cell[2 * f], nb = d.face_cell[2 * f + 1];
@@ -220,120 +289,127 @@ template <bool HasV, int NF> __global__ __launch_bounds__(kBlock) void k_face_vj
   };
 
   if (bcs < 0) {
-    // forward: moment sums S1 (Eqs. 47-49), heat-flux sums S2 (Eqs. 51-52) and the second moments of G_bar
-    Acc<6, false, kBlock> a6;
-    a6.zero();
-    v_loop(nv, [&](int64_t k) {
-      const Vel v = vel(d, k);
-      const double wg = v.w * rowG[k], wr = v.w * rowR[k];
-      a6.add(0, wg);
-      a6.add(1, v.ux * wg);
-      a6.add(2, v.uy * wg);
-      a6.add(3, v.uz * wg);
-      a6.add(4, v.h2 * wg + wr);
-      a6.add(5, wr);
-    });
-    double S1[6];
-    a6.reduce(S1, red);
-    const double rho = S1[0];
-    const double U[3] = {S1[1] / rho, S1[2] / rho, S1[3] / rho};
-    Acc<12, false, kBlock> a12;
-    a12.zero();
-    v_loop(nv, [&](int64_t k) {
-      const Vel v = vel(d, k);
-      const double cx = v.ux - U[0], cy = v.uy - U[1], cz = v.uz - U[2];
-      const double c2 = cx * cx + cy * cy + cz * cz;
-      const double wg = v.w * rowG[k], wr = v.w * rowR[k];
-      a12.add(0, cx * c2 * wg);
-      a12.add(1, cy * c2 * wg);
-      a12.add(2, cz * c2 * wg);
-      a12.add(3, cx * wr);
-      a12.add(4, cy * wr);
-      a12.add(5, cz * wr);
-      a12.add(6, cx * cx * wg);
-      a12.add(7, cy * cy * wg);
-      a12.add(8, cz * cz * wg);
-      a12.add(9, cx * cy * wg);
-      a12.add(10, cx * cz * wg);
-      a12.add(11, cy * cz * wg);
-    });
-    double S2M[12];
-    a12.reduce(S2M, red);
-    if (threadIdx.x == 0) {
-      Dual<12> x1[6], x2[6], th[NTH], tau;
+    const double* Wo = b.W + 6 * o;
+    const double* Wn = b.W + 6 * nb;
+    const double U0[3] = {0.5 * (Wo[1] / Wo[0] + Wn[1] / Wn[0]), 0.5 * (Wo[2] / Wo[0] + Wn[2] / Wn[0]),
+                          0.5 * (Wo[3] / Wo[0] + Wn[3] / Wn[0])};
+    {
+      Acc<17, false, NT> a17;
+      a17.zero();
+      v_loop<NT>(nv, [&](int64_t k) {
+        const Vel v = vel(d, k);
+        const double gb = rowG[k], rb = rowR[k];
+        if (Stage) {
+          sG[k] = gb;
+          sR[k] = rb;
+        }
+        const double vx = v.ux - U0[0], vy = v.uy - U0[1], vz = v.uz - U0[2];
+        const double wg = v.w * gb, wr = v.w * rb;
+        const double gx = wg * vx, gy = wg * vy, gz = wg * vz, v2 = vx * vx + vy * vy + vz * vz;
+        a17.add(0, wg);
+        a17.add(1, gx);
+        a17.add(2, gy);
+        a17.add(3, gz);
+        a17.add(4, gx * vx);
+        a17.add(5, gy * vy);
+        a17.add(6, gz * vz);
+        a17.add(7, gx * vy);
+        a17.add(8, gx * vz);
+        a17.add(9, gy * vz);
+        a17.add(10, gx * v2);
+        a17.add(11, gy * v2);
+        a17.add(12, gz * v2);
+        a17.add(13, wr);
+        a17.add(14, wr * vx);
+        a17.add(15, wr * vy);
+        a17.add(16, wr * vz);
+      });
+      a17.reduce_to_lds(sh_m, red);
+    }
+    if (threadIdx.x < 64) {
+      // lane j: the face state and its derivative along sum j of (S1, S2)
+      const FaceSums fs = face_sums(sh_m, U0);
+      const int j = (int)threadIdx.x;
+      Dual<1> x1[6], x2[6], th[NTH], tau;
       for (int m = 0; m < 6; ++m) {
-        x1[m] = Dual<12>(S1[m]);
-        x1[m].d[m] = 1.0;
-        x2[m] = Dual<12>(S2M[m]);
-        x2[m].d[6 + m] = 1.0;
+        x1[m] = Dual<1>(fs.S1[m]);
+        x1[m].d[0] = j == m ? 1.0 : 0.0;
+        x2[m] = Dual<1>(fs.S2[m]);
+        x2[m].d[0] = j == 6 + m ? 1.0 : 0.0;
       }
       face_state(x1, x2, s, g, th, tau);
-      for (int m = 0; m < NTH; ++m) {
-        sh_th[m] = th[m].v;
-        for (int j = 0; j < 12; ++j) sh_jac[12 * m + j] = th[m].d[j];
+      if (j < 12) {
+        for (int m = 0; m < NTH; ++m) sh_jac[12 * m + j] = th[m].d[0];
+        sh_jac[12 * NTH + j] = tau.d[0];
       }
-      sh_th[NTH] = tau.v;
-      for (int j = 0; j < 12; ++j) sh_jac[12 * NTH + j] = tau.d[j];
+      double tv[NTH];
+      for (int m = 0; m < NTH; ++m) tv[m] = th[m].v;
+      if (j == 0) {
+        sh_tau = tau.v;
+        sh_fs = fs;
+        sh_e.setup(tv, g);
+      }
     }
     __syncthreads();
-    double th[NTH];
-    for (int m = 0; m < NTH; ++m) th[m] = sh_th[m];
-    const double tau = sh_th[NTH];
-    EqAd e;
-    e.setup(th, g);
+    const double tau = sh_tau;
     const double ct = tau / (tau + s), cs = s / (tau + s), ctau = s / ((tau + s) * (tau + s));
-    // reverse of Eq. 45: adjoints of theta and tau
-    Acc<14, false, kBlock> a14;
-    a14.zero();
-    v_loop(nv, [&](int64_t k) {
-      const Vel v = vel(d, k);
-      const double un = udotn(v, nx, ny, nz, d.snap);
-      double sg, sr;
-      seed(k, v, un, sg, sr);
-      double Gs, Rs, dG[NTH], dR[NTH];
-      e.eval(v.ux, v.uy, v.uz, Gs, Rs, dG, dR);
-#pragma unroll
-      for (int m = 0; m < NTH; ++m) a14.add(m, cs * (sg * dG[m] + sr * dR[m]));
-      a14.add(13, ctau * (sg * (rowG[k] - Gs) + sr * (rowR[k] - Rs)));
-    });
-    double tb[14];
-    a14.reduce(tb, red);
-    if (threadIdx.x == 0) {
-      double Sb[12];
-      for (int j = 0; j < 12; ++j) {
-        double x = 0.0;
-        for (int m = 0; m < 14; ++m) x += sh_jac[12 * m + j] * tb[m];
-        Sb[j] = x;
-      }
-      // U = S1[1..3]/S1[0] inside S2: dS2q_d/dU_e = -(delta_de trM + 2 M_de), dS2r_d/dU_e = -delta_de S1[5]
-      const double M[3][3] = {{S2M[6], S2M[9], S2M[10]}, {S2M[9], S2M[7], S2M[11]}, {S2M[10], S2M[11], S2M[8]}};
-      const double trM = S2M[6] + S2M[7] + S2M[8];
-      // Sb[0..5]: adjoint of S1, Sb[6..8]: of the q_tr sums, Sb[9..11]: of the q_rot sums
-      double Ub[3];
-      for (int ee = 0; ee < 3; ++ee) {
-        double x = -Sb[6 + ee] * trM - Sb[9 + ee] * S1[5];
-        for (int dd = 0; dd < 3; ++dd) x -= 2.0 * Sb[6 + dd] * M[dd][ee];
-        Ub[ee] = x;
-      }
-      double s1b[6];
-      for (int m = 0; m < 6; ++m) s1b[m] = Sb[m];
-      for (int ee = 0; ee < 3; ++ee) {
-        s1b[1 + ee] += Ub[ee] / rho;
-        s1b[0] -= Ub[ee] * U[ee] / rho;
-      }
-      for (int m = 0; m < 6; ++m) {
-        sh_bar[m] = s1b[m];
-        sh_bar[6 + m] = Sb[6 + m];
-      }
+    // reverse of Eq. 45: adjoints of theta (15 sums) and tau
+    {
+      const EqVjp e = uniform(sh_e);
+      Acc<16, false, NT> a16;
+      a16.zero();
+      v_loop<NT>(nv, [&](int64_t k) {
+        const Vel v = vel(d, k);
+        const double un = udotn(v, nx, ny, nz, d.snap);
+        double sg, sr;
+        seed(k, v, un, sg, sr);
+        const double gb = Stage ? sG[k] : rowG[k], rb = Stage ? sR[k] : rowR[k];
+        const double eqs = e.sums(e.at(v.ux, v.uy, v.uz), sg, sr, [&](int m, double t) { a16.add(m, t); });
+        a16.add(15, sg * gb + sr * rb - eqs);
+        if (Stage) {
+          sG[k] = sg;
+          sR[k] = sr;
+        }
+      });
+      a16.reduce_to_lds(sh_m, red);
+    }
+    if (threadIdx.x < 12) {
+      double tb[14];
+      sh_e.finish(sh_m, tb);
+      double x = ctau * sh_m[15] * sh_jac[12 * NTH + threadIdx.x];
+      for (int m = 0; m < NTH; ++m) x += sh_jac[12 * m + threadIdx.x] * (cs * tb[m]);
+      sh_bar[threadIdx.x] = x;
     }
     __syncthreads();
-    double sb[12];
-    for (int m = 0; m < 12; ++m) sb[m] = sh_bar[m];
-    v_loop(nv, [&](int64_t k) {
+    // U = S1[1..3]/S1[0] inside S2: dS2q_d/dU_e = -(delta_de trM + 2 M_de), dS2r_d/dU_e = -delta_de S1[5];
+    // sb[0..5] then holds the adjoint of S1, sb[6..8] that of the q_tr sums, sb[9..11] of the q_rot sums
+    double sb[12], U[3];
+    {
+      const FaceSums& fs = sh_fs;
+      const double irho = 1.0 / fs.S1[0];
+      for (int m = 0; m < 12; ++m) sb[m] = sh_bar[m];
+      const double M[3][3] = {
+          {fs.S2[6], fs.S2[9], fs.S2[10]}, {fs.S2[9], fs.S2[7], fs.S2[11]}, {fs.S2[10], fs.S2[11], fs.S2[8]}};
+      const double trM = fs.S2[6] + fs.S2[7] + fs.S2[8];
+      for (int ee = 0; ee < 3; ++ee) {
+        U[ee] = fs.S1[1 + ee] * irho;
+        double x = -sb[6 + ee] * trM - sb[9 + ee] * fs.S1[5];
+        for (int dd = 0; dd < 3; ++dd) x -= 2.0 * sb[6 + dd] * M[dd][ee];
+        sb[1 + ee] += x * irho;
+        sb[0] -= x * U[ee] * irho;
+      }
+      for (int m = 0; m < 12; ++m) sb[m] = uniform(sb[m]);
+      for (int ee = 0; ee < 3; ++ee) U[ee] = uniform(U[ee]);
+    }
+    v_loop<NT>(nv, [&](int64_t k) {
       const Vel v = vel(d, k);
-      const double un = udotn(v, nx, ny, nz, d.snap);
       double sg, sr;
-      seed(k, v, un, sg, sr);
+      if (Stage) {
+        sg = sG[k];
+        sr = sR[k];
+      } else {
+        seed(k, v, udotn(v, nx, ny, nz, d.snap), sg, sr);
+      }
       const double cx = v.ux - U[0], cy = v.uy - U[1], cz = v.uz - U[2];
       const double c2 = cx * cx + cy * cy + cz * cz;
       rowG[k] = ct * sg + v.w * (sb[0] + sb[1] * v.ux + sb[2] * v.uy + sb[3] * v.uz + sb[4] * v.h2 +
@@ -363,9 +439,9 @@ template <bool HasV, int NF> __global__ __launch_bounds__(kBlock) void k_face_vj
   double gp0 = 0.0, gp1 = 0.0, gp2 = 0.0;
   if (wall) {
     // rho_w = out/in (zero net mass flux); din = d(in)/dT_w
-    Acc<3, false, kBlock> a3;
+    Acc<3, false, NT> a3;
     a3.zero();
-    v_loop(nv, [&](int64_t k) {
+    v_loop<NT>(nv, [&](int64_t k) {
       const Vel v = vel(d, k);
       const double un = udotn(v, nx, ny, nz, d.snap);
       if (un > 0.0) {
@@ -381,9 +457,9 @@ template <bool HasV, int NF> __global__ __launch_bounds__(kBlock) void k_face_vj
     a3.reduce(t3, red);
     const double in = t3[1], rho_w = t3[0] / in;
     // adjoint of rho_w and the T_w terms of the incoming half
-    Acc<3, false, kBlock> b3;
+    Acc<3, false, NT> b3;
     b3.zero();
-    v_loop(nv, [&](int64_t k) {
+    v_loop<NT>(nv, [&](int64_t k) {
       const Vel v = vel(d, k);
       const double un = udotn(v, nx, ny, nz, d.snap);
       if (un > 0.0) return;
@@ -399,7 +475,7 @@ template <bool HasV, int NF> __global__ __launch_bounds__(kBlock) void k_face_vj
     b3.reduce(u3, red);
     const double rho_wb = u3[0];
     if (bcs == a.wslot) gp0 = u3[1] + u3[2] + rho_wb * (-rho_w / in) * t3[2];
-    v_loop(nv, [&](int64_t k) {
+    v_loop<NT>(nv, [&](int64_t k) {
       const Vel v = vel(d, k);
       const double un = udotn(v, nx, ny, nz, d.snap);
       if (un > 0.0) {
@@ -416,9 +492,9 @@ template <bool HasV, int NF> __global__ __launch_bounds__(kBlock) void k_face_vj
     const double rho_inf = bc[1];
     const double Um = sqrt(Ub[0] * Ub[0] + Ub[1] * Ub[1] + Ub[2] * Ub[2]);
     if (bcs == a.fslot) {
-      Acc<2, false, kBlock> b2;
+      Acc<2, false, NT> b2;
       b2.zero();
-      v_loop(nv, [&](int64_t k) {
+      v_loop<NT>(nv, [&](int64_t k) {
         const Vel v = vel(d, k);
         const double un = udotn(v, nx, ny, nz, d.snap);
         if (un > 0.0) return;
@@ -434,7 +510,7 @@ template <bool HasV, int NF> __global__ __launch_bounds__(kBlock) void k_face_vj
       gp1 = u2[0];
       gp2 = u2[1];
     }
-    v_loop(nv, [&](int64_t k) {
+    v_loop<NT>(nv, [&](int64_t k) {
       const Vel v = vel(d, k);
       const double un = udotn(v, nx, ny, nz, d.snap);
       if (un > 0.0) {
@@ -606,14 +682,27 @@ template <int NF> __global__ __launch_bounds__(kBlock) void k_recon_vjp(Dev d, B
   recon_vjp_one<NF>(d, (const double*)b.R, (const double*)b.faceR, a.gR, i, k, nb, fc, geo, kh3, v, un, LR);
 }
 
+// Row staging of the face terms: 256 threads where the two rows take at most 38 KB of LDS (four workgroups a
+// compute unit), 512 up to 77 KB (two), none beyond.
+template <bool HasV, int NF> void launch_face_vjp(const Dev& d, const Bufs& b, const AdjArgs& a, hipStream_t st) {
+  const dim3 grid((unsigned)d.nf);
+  const size_t row = 2 * sizeof(double) * (size_t)d.nv;
+  if (row <= 38 * 1024)
+    hipLaunchKernelGGL((k_face_vjp<HasV, NF, true, kBlock>), grid, dim3(kBlock), row, st, d, b, a);
+  else if (row <= 77 * 1024)
+    hipLaunchKernelGGL((k_face_vjp<HasV, NF, true, 2 * kBlock>), grid, dim3(2 * kBlock), row, st, d, b, a);
+  else
+    hipLaunchKernelGGL((k_face_vjp<HasV, NF, false, kBlock>), grid, dim3(kBlock), 0, st, d, b, a);
+}
+
 template <int NF> void launch_vjp_nf(const Dev& d, const Bufs& b, const AdjArgs& a, hipStream_t st) {
   const bool hv = a.vG != nullptr;
   launch_recon<double>(d, b, st);
   if (hv) {
-    hipLaunchKernelGGL((k_face_vjp<true, NF>), dim3((unsigned)d.nf), dim3(kBlock), 0, st, d, b, a);
+    launch_face_vjp<true, NF>(d, b, a, st);
     hipLaunchKernelGGL(k_cell_vjp<true>, dim3((unsigned)d.nc), dim3(kBlock), 0, st, d, b, a);
   } else {
-    hipLaunchKernelGGL((k_face_vjp<false, NF>), dim3((unsigned)d.nf), dim3(kBlock), 0, st, d, b, a);
+    launch_face_vjp<false, NF>(d, b, a, st);
     hipLaunchKernelGGL(k_cell_vjp<false>, dim3((unsigned)d.nc), dim3(kBlock), 0, st, d, b, a);
   }
   const unsigned nch = (unsigned)((d.nv + kBlock - 1) / kBlock);
