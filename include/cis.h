@@ -241,6 +241,8 @@ typedef struct {
   double q;
 } cis_wall_face;
 
+/* Wall loads, wall heat flux and wall coefficients evaluate the faces of `tag` and their cells only: of the face
+   buffers, the rows of those cells' faces are overwritten (all of them with limiter 4). */
 /* faces (host, [*n_faces], or NULL) receives the faces of `tag` in face order; *n_faces (or NULL) their count.
    force (host [3], or NULL) and heat (host, or NULL) receive the integrated loads. */
 cis_status cis_wall_loads(cis_state* s, int32_t tag, int64_t* n_faces, cis_wall_face* faces, double* force,

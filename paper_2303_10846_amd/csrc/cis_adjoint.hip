@@ -416,11 +416,6 @@ __global__ __launch_bounds__(NT, 4) void k_face_vjp(Dev d, Bufs b, AdjArgs a) {
                                  c2 * (sb[6] * cx + sb[7] * cy + sb[8] * cz));
       rowR[k] = ct * sr + v.w * (sb[4] + sb[5] + sb[9] * cx + sb[10] * cy + sb[11] * cz);
     });
-    if (threadIdx.x == 0) {
-      a.gpf[3 * f] = 0.0;
-      a.gpf[3 * f + 1] = 0.0;
-      a.gpf[3 * f + 2] = 0.0;
-    }
     return;
   }
 

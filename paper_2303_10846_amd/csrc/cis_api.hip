@@ -143,13 +143,6 @@ template <class T> cis_status dmalloc(T** p, size_t n) {
   return CIS_OK;
 }
 
-template <class T> cis_status upload(T** p, const std::vector<T>& v, hipStream_t st) {
-  cis_status s = dmalloc(p, v.size());
-  if (s != CIS_OK) return s;
-  HIP_TRY(hipMemcpyAsync(*p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, st));
-  return CIS_OK;
-}
-
 __global__ void k_zero_i32(int32_t* p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
@@ -186,6 +179,14 @@ struct cis_state {
   Work work{};
   Flow flow{};
   // library-owned device arrays
+  // boundary faces grouped by bc slot, in face order, then their cells (each once): host offsets into d_bnd
+  struct BndGroup {
+    std::vector<int32_t> faces;
+    int64_t face0 = 0, cell0 = 0, n_cells = 0;
+  };
+  std::vector<BndGroup> bnd;
+  std::vector<int32_t> bnd_faces;  // all boundary faces, in face order (at d_bnd)
+  int32_t* d_bnd = nullptr;
   int32_t *d_cell_nb = nullptr, *d_cell_face = nullptr, *d_face_cell = nullptr, *d_face_bc = nullptr,
           *d_spatial = nullptr;
   float* d_cell_geo_f = nullptr;
@@ -209,11 +210,35 @@ template <class T> cis_status own_alloc(cis_state* s, T** p, size_t n) {
   if (st == CIS_OK) s->owned.push_back((void*)*p);
   return st;
 }
-template <class T> cis_status own_upload(cis_state* s, T** p, const std::vector<T>& v) {
-  cis_status st = upload(p, v, s->stream);
-  if (st == CIS_OK) s->owned.push_back((void*)*p);
-  return st;
-}
+// The fixed arrays of a state in one allocation (an allocation each cost creation more than filling them): want()
+// every array, then commit(), which sets the pointers (256-byte aligned) and copies the host contents given.
+class Arena {
+ public:
+  template <class T> void want(T** p, size_t n, const T* host = nullptr) {
+    parts_.push_back({reinterpret_cast<void**>(p), total_, n * sizeof(T), host});
+    total_ += (std::max<size_t>(n, 1) * sizeof(T) + 255) / 256 * 256;
+  }
+  template <class T> void want(T** p, const std::vector<T>& v) { want(p, v.size(), v.data()); }
+  cis_status commit(cis_state* s) {
+    char* base = nullptr;
+    const cis_status st = own_alloc(s, &base, total_);
+    if (st != CIS_OK) return st;
+    for (const Part& q : parts_) {
+      *q.p = base + q.at;
+      if (q.host && q.bytes) HIP_TRY(hipMemcpyAsync(*q.p, q.host, q.bytes, hipMemcpyHostToDevice, s->stream));
+    }
+    return CIS_OK;
+  }
+
+ private:
+  struct Part {
+    void** p;
+    size_t at, bytes;
+    const void* host;
+  };
+  std::vector<Part> parts_;
+  size_t total_ = 0;
+};
 
 bool finite_all(const double* p, size_t n) {
   for (size_t i = 0; i < n; ++i)
@@ -280,10 +305,23 @@ void run_vjp(cis_state* s, const double* v, double cJ, const AdjSlots& sl, doubl
   launch_vjp(s->dev, s->buf, a, s->stream);
 }
 
-cis_status sum_gp(cis_state* s, double* gp) {
-  std::vector<double> h(3 * (size_t)s->mesh->nf);
-  HIP_TRY(hipMemcpyAsync(h.data(), s->work.gpf, h.size() * sizeof(double), hipMemcpyDeviceToHost, s->stream));
+// Rows of boundary faces (width values each, at most 6) from a per-face array, gathered on the device
+cis_status gather_boundary(cis_state* s, const double* src, int width, int64_t first, int64_t n, std::vector<double>& h) {
+  h.resize((size_t)width * n);
+  if (n == 0) return CIS_OK;
+  launch_gather_rows(src, width, s->d_bnd + first, n, s->work.bnd, s->stream);
+  cis_status st = device_check("gather");
+  if (st != CIS_OK) return st;
+  HIP_TRY(hipMemcpyAsync(h.data(), s->work.bnd, h.size() * sizeof(double), hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(hipStreamSynchronize(s->stream));
+  return CIS_OK;
+}
+
+// The per-face parameter adjoints (zero on interior faces) summed in face order
+cis_status sum_gp(cis_state* s, double* gp) {
+  std::vector<double> h;
+  const cis_status st = gather_boundary(s, s->work.gpf, 3, 0, (int64_t)s->bnd_faces.size(), h);
+  if (st != CIS_OK) return st;
   double a[3] = {0.0, 0.0, 0.0};
   for (size_t f = 0; f < h.size() / 3; ++f)
     for (int m = 0; m < 3; ++m) a[m] += h[3 * f + m];
@@ -293,15 +331,52 @@ cis_status sum_gp(cis_state* s, double* gp) {
 
 // J = sum over the boundary faces of bc slot `slot` of A sum_k w (u.n)(|u|^2/2 G_f + R_f), from the face pass
 cis_status objective_from_faces(cis_state* s, int slot, double* J) {
-  const cis_mesh* m = s->mesh;
-  std::vector<double> fm(6 * m->nf);
-  HIP_TRY(hipMemcpyAsync(fm.data(), s->work.face_mac, fm.size() * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-  HIP_TRY(hipStreamSynchronize(s->stream));
-  const int32_t tag = slot >= 0 ? s->bcs[slot].tag : INT32_MIN;
+  *J = 0.0;
+  if (slot < 0) {
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    return CIS_OK;
+  }
+  const auto& g = s->bnd[(size_t)slot];
+  std::vector<double> fm;
+  const cis_status st = gather_boundary(s, s->work.face_mac, 6, g.face0, (int64_t)g.faces.size(), fm);
+  if (st != CIS_OK) return st;
   double acc = 0.0;
-  for (int64_t f = 0; f < m->nf; ++f)
-    if (m->face_cell[2 * f + 1] < 0 && m->face_tag[f] == tag) acc += fm[6 * f + 4];
+  for (size_t f = 0; f < g.faces.size(); ++f) acc += fm[6 * f + 4];
   *J = acc;
+  return CIS_OK;
+}
+
+// Macro fluxes [n][6] of the faces of bc slot `slot` (-1: none) at the current state, in face order.  Only those
+// faces and their cells are evaluated, except with limiter 4, whose reconstruction lowers every stored value.
+cis_status boundary_fluxes(cis_state* s, int slot, std::vector<double>& fm, const char* what) {
+  fm.clear();
+  if (slot < 0 && s->num.limiter != 4) {
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    return CIS_OK;
+  }
+  const cis_status st = dispatch(s, [&](auto* tp) {
+    using T = std::remove_pointer_t<decltype(tp)>;
+    if (s->num.limiter == 4) {
+      launch_recon<T>(s->dev, s->buf, s->stream);
+      launch_face<T>(s->dev, s->buf, s->work, s->stream);
+    } else {
+      const auto& g = s->bnd[(size_t)slot];
+      launch_boundary_faces<T>(s->dev, s->buf, s->work, s->d_bnd + g.face0, (int64_t)g.faces.size(),
+                               s->d_bnd + g.cell0, g.n_cells, s->stream);
+    }
+    return device_check(what);
+  });
+  if (st != CIS_OK) return st;
+  if (slot < 0) {
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    return CIS_OK;
+  }
+  const auto& g = s->bnd[(size_t)slot];
+  if (s->num.limiter == 4) return gather_boundary(s, s->work.face_mac, 6, g.face0, (int64_t)g.faces.size(), fm);
+  fm.resize(6 * g.faces.size());
+  if (!fm.empty())
+    HIP_TRY(hipMemcpyAsync(fm.data(), s->work.face_mac, fm.size() * sizeof(double), hipMemcpyDeviceToHost, s->stream));
+  HIP_TRY(hipStreamSynchronize(s->stream));
   return CIS_OK;
 }
 
@@ -313,28 +388,27 @@ cis_status dev_dots(cis_state* s, const double* V, int64_t n, int nvec, const do
   return CIS_OK;
 }
 
-// Face pass on the current state, then the per-face wall loads of `tag` (Eqs. 70-72 numerators) from the face
-// macro fluxes, with n from the gas into the wall; F and Q receive the integrated force and heat load.
+int64_t wall_count(const cis_state* s, int32_t tag) {
+  const int slot = slot_of(s, tag);
+  return slot < 0 ? 0 : (int64_t)s->bnd[(size_t)slot].faces.size();
+}
+
+// The per-face wall loads of `tag` at the current state (Eqs. 70-72 numerators) from the macro fluxes of its faces,
+// with n from the gas into the wall; F and Q receive the integrated force and heat load.
 cis_status wall_faces(cis_state* s, int32_t tag, std::vector<cis_wall_face>& out, double* F, double* Q) {
   const cis_mesh* m = s->mesh;
-  cis_status st = dispatch(s, [&](auto* tp) {
-    using T = std::remove_pointer_t<decltype(tp)>;
-    launch_recon<T>(s->dev, s->buf, s->stream);
-    launch_face<T>(s->dev, s->buf, s->work, s->stream);
-    return device_check("wall loads");
-  });
+  const int slot = slot_of(s, tag);
+  std::vector<double> fm;
+  const cis_status st = boundary_fluxes(s, slot, fm, "wall loads");
   if (st != CIS_OK) return st;
-  std::vector<double> fm(6 * m->nf);
-  HIP_TRY(hipMemcpyAsync(fm.data(), s->work.face_mac, fm.size() * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-  HIP_TRY(hipStreamSynchronize(s->stream));
   out.clear();
   F[0] = F[1] = F[2] = 0.0;
   *Q = 0.0;
-  for (int64_t f = 0; f < m->nf; ++f) {
-    if (m->face_cell[2 * f + 1] >= 0 || m->face_tag[f] != tag) continue;
+  for (size_t r = 0; 6 * r < fm.size(); ++r) {
+    const int64_t f = s->bnd[(size_t)slot].faces[r];
     const double A = m->fA[f];
     const double* n = &m->fn[3 * f];
-    const double* mac = &fm[6 * f];  // A sum_k w (u.n) (G, u G, |u|^2/2 G + R, R)
+    const double* mac = &fm[6 * r];  // A sum_k w (u.n) (G, u G, |u|^2/2 G + R, R)
     const double mom[3] = {mac[1] / A, mac[2] / A, mac[3] / A};
     const double p = mom[0] * n[0] + mom[1] * n[1] + mom[2] * n[2];
     cis_wall_face o;
@@ -783,6 +857,28 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
   }
 
   auto* s = new cis_state();
+  // boundary faces: all in face order, then per condition, then the cells of each condition's faces
+  s->bnd.resize((size_t)n_bc);
+  std::vector<int32_t> bnd;
+  for (int64_t f = 0; f < m->nf; ++f)
+    if (face_bc[f] >= 0) {
+      s->bnd_faces.push_back((int32_t)f);
+      s->bnd[(size_t)face_bc[f]].faces.push_back((int32_t)f);
+    }
+  bnd = s->bnd_faces;
+  for (auto& g : s->bnd) {
+    g.face0 = (int64_t)bnd.size();
+    bnd.insert(bnd.end(), g.faces.begin(), g.faces.end());
+  }
+  for (auto& g : s->bnd) {
+    std::vector<int32_t> cells;
+    for (const int32_t f : g.faces) cells.push_back(m->face_cell[2 * f]);
+    std::sort(cells.begin(), cells.end());
+    cells.erase(std::unique(cells.begin(), cells.end()), cells.end());
+    g.cell0 = (int64_t)bnd.size();
+    g.n_cells = (int64_t)cells.size();
+    bnd.insert(bnd.end(), cells.begin(), cells.end());
+  }
   s->mesh = m;
   s->dvs = dv;
   s->gas = *gas;
@@ -893,39 +989,42 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
     for (int d = 0; d < 3; ++d) p[2 + d] = bc[b].U[d];
     p[5] = bc[b].T;
   }
-  cis_status e = CIS_OK;
-  auto chk = [&](cis_status x) {
-    if (e == CIS_OK) e = x;
-  };
-  chk(own_upload(s, &s->d_cell_nb, m->cell_nb));
-  chk(own_upload(s, &s->d_spatial, m->spatial));
-  chk(own_upload(s, &s->d_cell_face, m->cell_face));
-  chk(own_upload(s, &s->d_face_cell, m->face_cell));
-  chk(own_upload(s, &s->d_face_bc, face_bc));
-  chk(own_upload(s, &s->d_cell_geo, cgeo));
-  chk(own_upload(s, &s->d_cell_geo_f, cgeof));
-  chk(own_upload(s, &s->d_face_geo, fgeo));
-  chk(own_upload(s, &s->d_dvs, dvsv));
-  chk(own_upload(s, &s->d_dvs_f, dvsf));
-  chk(own_upload(s, &s->d_bc, bct));
+  Arena arena;
+  arena.want(&s->d_cell_nb, m->cell_nb);
+  arena.want(&s->d_spatial, m->spatial);
+  arena.want(&s->d_cell_face, m->cell_face);
+  arena.want(&s->d_face_cell, m->face_cell);
+  arena.want(&s->d_face_bc, face_bc);
+  arena.want(&s->d_bnd, bnd);
+  arena.want(&s->d_cell_geo, cgeo);
+  arena.want(&s->d_cell_geo_f, cgeof);
+  arena.want(&s->d_face_geo, fgeo);
+  arena.want(&s->d_dvs, dvsv);
+  arena.want(&s->d_dvs_f, dvsf);
+  arena.want(&s->d_bc, bct);
   Work& w = s->work;
-  chk(own_alloc(s, &w.face_mac, 6 * nf));
-  chk(own_alloc(s, &w.cell_prim, 8 * nc));
-  chk(own_alloc(s, &w.rcf, (size_t)mf * nc));
-  chk(own_alloc(s, &w.G0, (size_t)6 * mf * nc));
-  chk(own_alloc(s, &w.mres, 6 * nc));
-  chk(own_alloc(s, &w.mD, 2 * nc));
-  chk(own_alloc(s, &w.Fmac, 6 * nc));
-  chk(own_alloc(s, &w.dW, 6 * nc));
-  chk(own_alloc(s, &w.mbase, nc));
-  chk(own_alloc(s, &w.Wt, 6 * nc));
-  chk(own_alloc(s, &w.eq, ER * nc));
-  chk(own_alloc(s, &w.cellres, 6 * nc));
-  chk(own_alloc(s, &w.flag, 4));
-  chk(own_alloc(s, &w.respart, 6 * 256));
-  chk(own_alloc(s, &w.gpf, 3 * nf));
+  arena.want(&w.face_mac, 6 * nf);
+  arena.want(&w.cell_prim, 8 * nc);
+  arena.want(&w.rcf, (size_t)mf * nc);
+  arena.want(&w.G0, (size_t)6 * mf * nc);
+  arena.want(&w.mres, 6 * nc);
+  arena.want(&w.mD, 2 * nc);
+  arena.want(&w.Fmac, 6 * nc);
+  arena.want(&w.dW, 6 * nc);
+  arena.want(&w.mbase, nc);
+  arena.want(&w.Wt, 6 * nc);
+  arena.want(&w.eq, ER * nc);
+  arena.want(&w.cellres, 6 * nc);
+  arena.want(&w.flag, 4);
+  arena.want(&w.respart, 6 * 256);
+  arena.want(&w.gpf, 3 * nf);
+  arena.want(&w.bnd, 6 * s->bnd_faces.size());
+  s->dev.mf = mf;
+  s->flow.plan = flow_plan(s->dev, m->color_off.data(), m->n_colors);
+  if (s->flow.plan.m && !s->flow.plan.local) arena.want(&s->flow.words, (size_t)kFlowWords * nc);
   s->res_cap = 64;
-  chk(own_alloc(s, &w.res, 6 * s->res_cap));
+  cis_status e = arena.commit(s);
+  if (e == CIS_OK) e = own_alloc(s, &w.res, 6 * s->res_cap);
   if (e != CIS_OK) {
     delete s;
     return e;
@@ -957,13 +1056,8 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
   d.lim_frozen = nullptr;
   fill_dev_numerics(s);
   s->buf = Bufs{buf->G, buf->R, buf->dG, buf->dR, buf->resG, buf->resR, buf->faceG, buf->faceR, buf->W, buf->q};
-  s->flow.plan = flow_plan(d, m->color_off.data(), m->n_colors);
-  if (s->flow.plan.m && !s->flow.plan.local) {
+  if (s->flow.words) {
     // tag 0 in every word: no version of the first launch
-    if (own_alloc(s, &s->flow.words, (size_t)kFlowWords * nc) != CIS_OK) {
-      delete s;
-      return CIS_E_DEVICE;
-    }
     const int64_t n = 2 * kFlowWords * nc;
     hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s->stream,
                        reinterpret_cast<int32_t*>(s->flow.words), n);
@@ -1157,20 +1251,11 @@ cis_status cis_moments(cis_state* s, double* W, double* q) { return cis_state_ge
 
 cis_status cis_wall_heat_flux(cis_state* s, int32_t tag, double* Q) {
   if (!s || !Q) return fail(CIS_E_INVALID_ARG, "NULL argument");
-  const cis_mesh* m = s->mesh;
-  cis_status st = dispatch(s, [&](auto* tp) {
-    using T = std::remove_pointer_t<decltype(tp)>;
-    launch_recon<T>(s->dev, s->buf, s->stream);
-    launch_face<T>(s->dev, s->buf, s->work, s->stream);
-    return device_check("wall_heat_flux");
-  });
+  std::vector<double> fm;
+  const cis_status st = boundary_fluxes(s, slot_of(s, tag), fm, "wall_heat_flux");
   if (st != CIS_OK) return st;
-  std::vector<double> fm(6 * m->nf);
-  HIP_TRY(hipMemcpyAsync(fm.data(), s->work.face_mac, fm.size() * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-  HIP_TRY(hipStreamSynchronize(s->stream));
   double acc = 0.0;
-  for (int64_t f = 0; f < m->nf; ++f)
-    if (m->face_cell[2 * f + 1] < 0 && m->face_tag[f] == tag) acc += fm[6 * f + 4];
+  for (size_t r = 0; 6 * r < fm.size(); ++r) acc += fm[6 * r + 4];
   *Q = acc;
   return CIS_OK;
 }
@@ -1178,6 +1263,10 @@ cis_status cis_wall_heat_flux(cis_state* s, int32_t tag, double* Q) {
 cis_status cis_wall_loads(cis_state* s, int32_t tag, int64_t* n_faces, cis_wall_face* faces, double* force,
                           double* heat) {
   if (!s) return fail(CIS_E_INVALID_ARG, "state is NULL");
+  if (!faces && !force && !heat) {  // the count alone
+    if (n_faces) *n_faces = wall_count(s, tag);
+    return CIS_OK;
+  }
   std::vector<cis_wall_face> wf;
   double F[3], Q;
   cis_status st = wall_faces(s, tag, wf, F, &Q);
@@ -1264,6 +1353,10 @@ cis_status cis_wall_coefficients_of_loads(const cis_wall_face* faces, int64_t n_
 cis_status cis_wall_coefficients(cis_state* s, int32_t tag, const cis_wall_ref* ref, int64_t* n_faces,
                                  cis_wall_coef* coef, cis_wall_totals* totals) {
   if (!s || !ref) return fail(CIS_E_INVALID_ARG, "NULL argument");
+  if (!coef && !totals) {  // the count alone, after the same checks of the references
+    if (n_faces) *n_faces = wall_count(s, tag);
+    return cis_wall_coefficients_of_loads(nullptr, 0, s->gas.R, ref, nullptr, nullptr);
+  }
   std::vector<cis_wall_face> wf;
   double F[3], Q;
   cis_status st = wall_faces(s, tag, wf, F, &Q);

@@ -98,7 +98,14 @@ struct Work {
   double* res;       // [hist][6]
   double* respart;   // [kResidualParts][6] partial sums of the residual
   int32_t* flag;     // [4]
-  double* gpf;       // [nf][3] per-face parameter adjoints of the VJP
+  double* gpf;       // [nf][3] per-face parameter adjoints of the VJP (boundary faces)
+  double* bnd;       // [n_b][6] gathered rows of boundary faces
+};
+
+// Some cells of the mesh, in processing order
+struct CellList {
+  const int32_t* at;
+  int64_t n;
 };
 
 struct Bufs {
@@ -112,6 +119,13 @@ template <class T> void launch_init_eq(const Dev& d, const Bufs& b, const double
 // cap != nullptr: also store the limiter values (limiter 1's, whatever d.limiter is) into cap, [2][nc][nv]
 template <class T> void launch_recon(const Dev& d, const Bufs& b, hipStream_t st, void* cap = nullptr);
 template <class T> void launch_face(const Dev& d, const Bufs& b, const Work& w, hipStream_t st);
+// The same for n boundary faces (device list) and their n_cells cells only; macro fluxes in list order into
+// w.face_mac.  Not with limiter 4, whose reconstruction updates every cell's stored values.
+template <class T>
+void launch_boundary_faces(const Dev& d, const Bufs& b, const Work& w, const int32_t* faces, int64_t n,
+                           const int32_t* cells, int64_t n_cells, hipStream_t st);
+// out[r][width] = src[at[r]][width], n rows
+void launch_gather_rows(const double* src, int width, const int32_t* at, int64_t n, double* out, hipStream_t st);
 void launch_macro(const Dev& d, const Bufs& b, const Work& w, const int64_t* color_off, int64_t n_colors,
                   int n_macro, hipStream_t st);
 template <class T> void launch_residual(const Dev& d, const Bufs& b, const Work& w, void* outG, void* outR,

@@ -219,12 +219,14 @@ __device__ inline void recon_write(T phi, const T* pn, const int32_t* nb, const 
 // Every load of a thread's velocities is issued before its first store (the stores could alias later loads
 // as far as the compiler knows); per-cell geometry is converted once into registers.  Rows are addressed
 // from uniform base pointers with 32-bit element offsets.
-template <class T, int NF> __global__ __launch_bounds__(kBlock) void k_recon(Dev d, Bufs b, T* cap) {
+// List: the cells of a list; else every cell.
+template <class T, int NF, bool List = false>
+__global__ __launch_bounds__(kBlock) void k_recon(Dev d, Bufs b, T* cap, CellList cells) {
   using L = Lay<NF>;
   constexpr int U = VptRecon<T>::v;
-  const CellChunk cc = cell_chunk(d.nc);
-  if (cc.cell >= d.nc) return;
-  const int64_t i = d.spatial[cc.cell];
+  const CellChunk cc = cell_chunk(List ? cells.n : d.nc);
+  if (cc.cell >= (List ? cells.n : d.nc)) return;
+  const int64_t i = (List ? cells.at : d.spatial)[cc.cell];
   const int64_t nv = d.nv;
   const double* geo = d.cell_geo + L::CG * i;
   const T* G = (const T*)b.G;
@@ -327,11 +329,11 @@ template <class T, int NF> __global__ __launch_bounds__(kBlock) void k_recon(Dev
 }
 
 template <class T> void launch_recon(const Dev& d, const Bufs& b, hipStream_t st, void* cap) {
+  const dim3 grid = cell_chunk_grid_u<VptRecon<T>::v>(d.nc, d.nv);
   if (d.mf == 4)
-    hipLaunchKernelGGL((k_recon<T, 4>), cell_chunk_grid_u<VptRecon<T>::v>(d.nc, d.nv), dim3(kBlock), 0, st, d, b, (T*)cap);
+    hipLaunchKernelGGL((k_recon<T, 4>), grid, dim3(kBlock), 0, st, d, b, (T*)cap, CellList{});
   else
-    hipLaunchKernelGGL((k_recon<T, kMaxFaces>), cell_chunk_grid_u<VptRecon<T>::v>(d.nc, d.nv), dim3(kBlock), 0, st, d, b,
-                       (T*)cap);
+    hipLaunchKernelGGL((k_recon<T, kMaxFaces>), grid, dim3(kBlock), 0, st, d, b, (T*)cap, CellList{});
 }
 
 // ---------------------------------------------------------------------------
@@ -479,8 +481,9 @@ template <int Dw, int NT> __device__ inline void lds_dma_copy(const void* src, v
   }
 }
 
-template <class T, int Stage, int NF, int NT>
-__global__ __launch_bounds__(NT) void k_face(Dev d, Bufs b, Work w) {
+// List: the boundary faces faces[0 .. gridDim.x), their macro fluxes in list order; else every face in turn.
+template <class T, int Stage, int NF, int NT, bool List = false>
+__global__ __launch_bounds__(NT) void k_face(Dev d, Bufs b, Work w, const int32_t* faces) {
   static_assert(Stage == 0 || Stage == 2 || Stage == 3, "staging paths 0, 2, 3");
   static_assert(Stage != 0 || NT == kBlock, "prefix staging runs 256-thread workgroups");
   using Code = typename Lay<NF>::Code;
@@ -493,7 +496,7 @@ __global__ __launch_bounds__(NT) void k_face(Dev d, Bufs b, Work w) {
   T* sR0 = sG + M;
   __shared__ double red[(NT / 64) * 6];
   __shared__ double red17[(NT / 64) * 17];
-  const int64_t f = blockIdx.x;
+  const int64_t f = List ? (int64_t)faces[blockIdx.x] : (int64_t)blockIdx.x;
   const int64_t nv = d.nv;
   const double* fg = d.face_geo + FGW * f;
   const double A = fg[0], nx = fg[1], ny = fg[2], nz = fg[3], s = fg[4];
@@ -505,7 +508,7 @@ __global__ __launch_bounds__(NT) void k_face(Dev d, Bufs b, Work w) {
   Acc<6, false, NT> acc;
   __shared__ double tot[6];
 
-  if (bcs < 0) {
+  if (!List && bcs < 0) {
     // pass 1: the moments of Eqs. 47-49 and 51-52 in one sweep, taken about a reference velocity U0 (the mean
     // of the two cells' velocities), v = u - U0: m0 = sum w G, m = sum w v G, M = sum w v v G,
     // T3 = sum w v|v|^2 G, r0 = sum w R, r = sum w v R.  With delta = U_f - U0 = m/m0 the sums about the face
@@ -686,7 +689,7 @@ __global__ __launch_bounds__(NT) void k_face(Dev d, Bufs b, Work w) {
       acc.add(5, wr);
     });
     acc.reduce_to_lds(tot, red);
-    if (threadIdx.x < 6) w.face_mac[6 * f + threadIdx.x] = A * tot[threadIdx.x];
+    if (threadIdx.x < 6) w.face_mac[6 * (List ? (int64_t)blockIdx.x : f) + threadIdx.x] = A * tot[threadIdx.x];
   }
 }
 
@@ -718,19 +721,20 @@ template <class T, int NF> static FacePlan face_plan(const Dev& d, const Bufs& b
   return FacePlan{0, kBlock, (size_t)std::min<int64_t>(nv, kStagePrefix<T>) * 2 * sizeof(T)};
 }
 
-template <class T, int NF> void launch_face_nf(const Dev& d, const Bufs& b, const Work& w, hipStream_t st) {
+template <class T, int NF> static void launch_face_nf(const Dev& d, const Bufs& b, const Work& w, hipStream_t st) {
   const FacePlan p = face_plan<T, NF>(d, b);
   const dim3 grid((unsigned)d.nf);
+  const int32_t* const all = nullptr;
   if (p.stage == 3 && p.nt == kBlock)
-    hipLaunchKernelGGL((k_face<T, 3, NF, kBlock>), grid, dim3(kBlock), p.lds, st, d, b, w);
+    hipLaunchKernelGGL((k_face<T, 3, NF, kBlock>), grid, dim3(kBlock), p.lds, st, d, b, w, all);
   else if (p.stage == 3)
-    hipLaunchKernelGGL((k_face<T, 3, NF, kFaceWide>), grid, dim3(kFaceWide), p.lds, st, d, b, w);
+    hipLaunchKernelGGL((k_face<T, 3, NF, kFaceWide>), grid, dim3(kFaceWide), p.lds, st, d, b, w, all);
   else if (p.stage == 2 && p.nt == kBlock)
-    hipLaunchKernelGGL((k_face<T, 2, NF, kBlock>), grid, dim3(kBlock), p.lds, st, d, b, w);
+    hipLaunchKernelGGL((k_face<T, 2, NF, kBlock>), grid, dim3(kBlock), p.lds, st, d, b, w, all);
   else if (p.stage == 2)
-    hipLaunchKernelGGL((k_face<T, 2, NF, kFaceWide>), grid, dim3(kFaceWide), p.lds, st, d, b, w);
+    hipLaunchKernelGGL((k_face<T, 2, NF, kFaceWide>), grid, dim3(kFaceWide), p.lds, st, d, b, w, all);
   else
-    hipLaunchKernelGGL((k_face<T, 0, NF, kBlock>), grid, dim3(kBlock), p.lds, st, d, b, w);
+    hipLaunchKernelGGL((k_face<T, 0, NF, kBlock>), grid, dim3(kBlock), p.lds, st, d, b, w, all);
 }
 
 template <class T> void launch_face(const Dev& d, const Bufs& b, const Work& w, hipStream_t st) {
@@ -738,6 +742,38 @@ template <class T> void launch_face(const Dev& d, const Bufs& b, const Work& w, 
     launch_face_nf<T, 4>(d, b, w, st);
   else
     launch_face_nf<T, kMaxFaces>(d, b, w, st);
+}
+
+// phi_bar and the face pass for some boundary faces only: the reconstruction of their cells, then those faces'
+// macro fluxes, in list order, into w.face_mac.  (Wall coefficients of a sphere of 15 552 tetrahedra x 4 140
+// velocities, 432 of its 31 968 faces on the wall: 3 290 us with both passes over the whole mesh, and twice, for
+// the count and for the values; 92 us now.)
+template <class T>
+void launch_boundary_faces(const Dev& d, const Bufs& b, const Work& w, const int32_t* faces, int64_t n,
+                           const int32_t* cells, int64_t n_cells, hipStream_t st) {
+  if (n == 0) return;
+  const CellList list{cells, n_cells};
+  const dim3 grid = cell_chunk_grid_u<VptRecon<T>::v>(n_cells, d.nv);
+  T* const cap = nullptr;
+  if (d.mf == 4) {
+    hipLaunchKernelGGL((k_recon<T, 4, true>), grid, dim3(kBlock), 0, st, d, b, cap, list);
+    hipLaunchKernelGGL((k_face<T, 0, 4, kBlock, true>), dim3((unsigned)n), dim3(kBlock), 0, st, d, b, w, faces);
+  } else {
+    hipLaunchKernelGGL((k_recon<T, kMaxFaces, true>), grid, dim3(kBlock), 0, st, d, b, cap, list);
+    hipLaunchKernelGGL((k_face<T, 0, kMaxFaces, kBlock, true>), dim3((unsigned)n), dim3(kBlock), 0, st, d, b, w, faces);
+  }
+}
+
+// out[r] = rows [6 or 3 doubles] of the listed faces
+__global__ __launch_bounds__(kBlock) void k_gather_rows(const double* src, int width, const int32_t* at, int64_t n,
+                                                        double* out) {
+  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (t < n * width) out[t] = src[(int64_t)at[t / width] * width + t % width];
+}
+void launch_gather_rows(const double* src, int width, const int32_t* at, int64_t n, double* out, hipStream_t st) {
+  if (n == 0) return;
+  hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)((n * width + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, src,
+                     width, at, n, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -1648,6 +1684,10 @@ template void launch_recon<double>(const Dev&, const Bufs&, hipStream_t, void*);
 template void launch_recon<float>(const Dev&, const Bufs&, hipStream_t, void*);
 template void launch_face<double>(const Dev&, const Bufs&, const Work&, hipStream_t);
 template void launch_face<float>(const Dev&, const Bufs&, const Work&, hipStream_t);
+template void launch_boundary_faces<double>(const Dev&, const Bufs&, const Work&, const int32_t*, int64_t,
+                                            const int32_t*, int64_t, hipStream_t);
+template void launch_boundary_faces<float>(const Dev&, const Bufs&, const Work&, const int32_t*, int64_t,
+                                           const int32_t*, int64_t, hipStream_t);
 template void launch_residual<double>(const Dev&, const Bufs&, const Work&, void*, void*, int, hipStream_t);
 template void launch_residual<float>(const Dev&, const Bufs&, const Work&, void*, void*, int, hipStream_t);
 template void launch_micro<double>(const Dev&, const Bufs&, const Work&, const int64_t*, int64_t, int, hipStream_t);
