@@ -1197,7 +1197,7 @@ cis_status cis_iterate(cis_state* s, int32_t n_iter, double* res_hist) {
     const cis_mesh* m = s->mesh;
     (void)hipStreamSynchronize(s->stream);
     const int64_t nmac = (int64_t)sweep_sequence(m->color_off.data(), m->n_colors, s->num.n_macro).size();
-    const int64_t nmic = (int64_t)sweep_sequence(m->color_off.data(), m->n_colors, s->num.n_micro).size();
+    const int64_t nmic = micro_launches(s->dev, m->color_off.data(), m->n_colors, s->num.n_micro);
     const int64_t per_it[6] = {1, 1, s->flow.plan.m ? 1 : 3 + nmac, 1, nmic, 3};
     for (int32_t it = 0; it < n_iter; ++it)
       for (int k = 0; k < 6; ++k) {

@@ -130,6 +130,8 @@ void launch_macro(const Dev& d, const Bufs& b, const Work& w, const int64_t* col
                   int n_macro, hipStream_t st);
 template <class T> void launch_residual(const Dev& d, const Bufs& b, const Work& w, void* outG, void* outR,
                                         int flux_only, hipStream_t st);
+// Launches of launch_micro's sweeps
+int64_t micro_launches(const Dev& d, const int64_t* color_off, int64_t n_colors, int n_micro);
 template <class T> void launch_micro(const Dev& d, const Bufs& b, const Work& w, const int64_t* color_off,
                                      int64_t n_colors, int n_micro, hipStream_t st);
 template <class T> void launch_update(const Dev& d, const Bufs& b, const Work& w, int64_t it, hipStream_t st);

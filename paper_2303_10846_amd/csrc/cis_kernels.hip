@@ -26,6 +26,7 @@
 
 #include "cis_device.h"
 #include "cis_internal.h"
+#include "cis_macro.h"
 
 namespace cis {
 
@@ -1387,6 +1388,117 @@ __global__ __launch_bounds__(kBlock) void k_micro_sweep_vec(Dev d, Bufs b, Work 
   st_nt<T, V>(c.oR + k, oR);
 }
 
+// The sweeps of a small mesh in one launch.  Velocities do not couple, so a workgroup takes kChunkVel of them through
+// every colour of every pass, the increments of all its cells in LDS and one barrier between colours; the arithmetic
+// is that of the launch per colour, whose launches of 4 to 6.5 us bind it there.  Increments go to memory at a cell's
+// last relaxation.  Lanes: 4 velocities of 256 cells a round (4 rather than 8 or 16: more workgroups; 16 velocities
+// took 1.1 to 1.4 times as long).
+constexpr int kChunkThreads = 1024;
+constexpr int kChunkVel = 4;
+
+// Colours of a launch in one workgroup
+struct ColorPlan {
+  int m;
+  int32_t off[kFlowColors], n[kFlowColors];
+};
+
+// position -> colour of the sequence 0, 1, .., m-1, m-2, .., 0, 1, ..
+struct ZigZag {
+  int c = 0, up = 1;
+  __device__ void next(int m) {
+    if (m < 2) return;
+    if (c == m - 1) up = -1;
+    if (c == 0) up = 1;
+    c += up;
+  }
+};
+
+template <class T, int NF>
+__global__ __launch_bounds__(kChunkThreads) void k_micro_chunk(Dev d, Bufs b, Work w, ColorPlan pl, int steps) {
+  constexpr int VC = kChunkVel;
+  using L = Lay<NF>;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* const xG = reinterpret_cast<T*>(smem_raw);
+  T* const xR = xG + d.nc * VC;
+  const int v = (int)threadIdx.x % VC, row = (int)threadIdx.x / VC;
+  const int64_t nv = d.nv, k = (int64_t)blockIdx.x * VC + v;
+  const bool live = k < nv;
+  for (int64_t x = threadIdx.x; x < 2 * d.nc * VC; x += kChunkThreads) xG[x] = T(0);
+  T ux = 0, uy = 0, uz = 0;
+  if (live) vel_t<T>(d, k, ux, uy, uz);
+  __syncthreads();
+  ZigZag z;
+  for (int p = 0; p < steps; ++p) {
+    const bool last = p == steps - 1 - z.c;
+    for (int j = row; j < pl.n[z.c]; j += kChunkThreads / VC) {
+      if (!live) continue;
+      const int64_t i = pl.off[z.c] + j;
+      const double* geo = d.cell_geo + L::CG * i;
+      const unsigned code = reinterpret_cast<const typename L::Code*>(d.upw)[i * nv + k];
+      T aG = ((const T*)b.resG)[i * nv + k], aR = ((const T*)b.resR)[i * nv + k];
+      double D = w.mbase[i];
+#pragma unroll
+      for (int a = 0; a < NF; ++a) {
+        const int32_t nb = d.cell_nb[NF * i + a];
+        const double* s = geo + CG_FACE + CG_SLOT * a;
+        const T nx = (T)s[2], ny = (T)s[3], nz = (T)s[4], av = (T)s[1];
+        const unsigned cd = (code >> (2 * a)) & 3u;
+        const T t = ux * nx + uy * ny + uz * nz;
+        const T pos = cd == 1u ? vmax(t, T(0)) : T(0);
+        const T neg = cd == 2u ? vmin(t, T(0)) : T(0);
+        D += (double)(av * pos);
+        if (nb >= 0 && cd == 2u) {
+          aG -= av * neg * xG[nb * VC + v];
+          aR -= av * neg * xR[nb * VC + v];
+        }
+      }
+      const double iD = 1.0 / D;
+      const T oG = (T)((double)aG * iD), oR = (T)((double)aR * iD);
+      xG[i * VC + v] = oG;
+      xR[i * VC + v] = oR;
+      if (last) {
+        ((T*)b.dG)[i * nv + k] = oG;
+        ((T*)b.dR)[i * nv + k] = oR;
+      }
+    }
+    __syncthreads();
+    z.next(pl.m);
+  }
+}
+
+// Which meshes take the sweeps in one launch.  Measured, one launch against one per colour: 11.5 against 36 us (48
+// tets x 216, FP64, 9 relaxations), the preconditioner's 56 against 85 us (384 six-slot cells x 1288, 13), but 52
+// against 50 us (1296 tets x 512, FP32) and 58 against 56 us (925 x 729, FP64), where a colour's cells
+// outgrow a round and its loads bind.  1024 cells are a few rounds of 256 cells a colour; 2^19 values lie
+// between the last two pairs.
+static bool chunk_sweeps(const Dev& d, const ColorPlan& pl) {
+  return pl.m > 0 && d.nc <= 1024 && d.nc * d.nv <= (int64_t)1 << 19;
+}
+static ColorPlan color_plan(const int64_t* color_off, int64_t n_colors) {
+  ColorPlan pl{};
+  for (int64_t c = 0; c < n_colors; ++c) {
+    const int64_t n = color_off[c + 1] - color_off[c];
+    if (n <= 0) continue;
+    if (pl.m == kFlowColors) return ColorPlan{};
+    pl.off[pl.m] = (int32_t)color_off[c];
+    pl.n[pl.m++] = (int32_t)n;
+  }
+  return pl;
+}
+int64_t micro_launches(const Dev& d, const int64_t* color_off, int64_t n_colors, int n_micro) {
+  const int64_t n = (int64_t)sweep_sequence(color_off, n_colors, n_micro).size();
+  return n > 0 && chunk_sweeps(d, color_plan(color_off, n_colors)) ? 1 : n;
+}
+
+template <class T, int NF>
+static bool launch_micro_chunk(const Dev& d, const Bufs& b, const Work& w, const ColorPlan& pl, int steps, hipStream_t st) {
+  if (!chunk_sweeps(d, pl)) return false;
+  const dim3 grid((unsigned)((d.nv + kChunkVel - 1) / kChunkVel));
+  const size_t lds = (size_t)d.nc * kChunkVel * 2 * sizeof(T);
+  hipLaunchKernelGGL((k_micro_chunk<T, NF>), grid, dim3(kChunkThreads), lds, st, d, b, w, pl, steps);
+  return true;
+}
+
 // Preconditioner of the discrete adjoint (FP64): point relaxation over one colour of
 // (D + N^T) x = -in for both distributions, where -(D + N) is dR_phi/dphi with first-order upwind faces and
 // the collision term frozen: D_i = 1/tau_i + sum_f (A_f/V_i) max(u.n_i, 0) and N_ij = (A_f/V_i) min(u.n_i, 0).
@@ -1446,12 +1558,75 @@ __global__ __launch_bounds__(kBlock) void k_copy_tail(const double* in, double* 
     out[off + t] = in[off + t];
 }
 
+// The preconditioner's sweeps of a small mesh in one launch, as k_micro_chunk.
+template <int NF>
+__global__ __launch_bounds__(kChunkThreads) void k_adj_chunk(Dev d, Bufs b, const double* in, double* x, ColorPlan pl,
+                                                             int steps) {
+  constexpr int VC = kChunkVel;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* const xG = reinterpret_cast<double*>(smem_raw);
+  double* const xR = xG + d.nc * VC;
+  const int v = (int)threadIdx.x % VC, row = (int)threadIdx.x / VC;
+  const int64_t nv = d.nv, P = d.nc * nv, k = (int64_t)blockIdx.x * VC + v;
+  const bool live = k < nv;
+  double* const itau = xR + d.nc * VC;
+  for (int64_t q = threadIdx.x; q < 2 * d.nc * VC; q += kChunkThreads) xG[q] = 0.0;
+  for (int64_t i = threadIdx.x; i < d.nc; i += kChunkThreads) {
+    const Prim p = prim_of(b.W + 6 * i, d.gas.R);
+    itau[i] = (p.rho * d.gas.R * p.Ttr) / visc(p.Ttr, d.gas);
+  }
+  const double ux = live ? d.dvs[k] : 0.0, uy = live ? d.dvs[nv + k] : 0.0, uz = live ? d.dvs[2 * nv + k] : 0.0;
+  __syncthreads();
+  ZigZag z;
+  for (int p = 0; p < steps; ++p) {
+    const bool last = p == steps - 1 - z.c;
+    for (int j = row; j < pl.n[z.c]; j += kChunkThreads / VC) {
+      if (!live) continue;
+      const int64_t i = pl.off[z.c] + j;
+      const double* geo = d.cell_geo + Lay<NF>::CG * i;
+      const unsigned code = reinterpret_cast<const typename Lay<NF>::Code*>(d.upw)[i * nv + k];
+      double aG = -in[i * nv + k], aR = -in[P + i * nv + k];
+      double D = itau[i];
+#pragma unroll
+      for (int a = 0; a < NF; ++a) {
+        const int32_t nb = d.cell_nb[NF * i + a];
+        const double* s = geo + CG_FACE + CG_SLOT * a;
+        if (((code >> (2 * a)) & 3u) != 1u) continue;
+        const double un = ux * s[2] + uy * s[3] + uz * s[4];
+        D += s[1] * un;
+        if (nb >= 0) {
+          const double cT = s[1] * geo[0] * d.cell_geo[Lay<NF>::CG * (int64_t)nb + 1] * un;
+          aG += cT * xG[nb * VC + v];
+          aR += cT * xR[nb * VC + v];
+        }
+      }
+      const double iD = 1.0 / D, oG = aG * iD, oR = aR * iD;
+      xG[i * VC + v] = oG;
+      xR[i * VC + v] = oR;
+      if (last) {
+        x[i * nv + k] = oG;
+        x[P + i * nv + k] = oR;
+      }
+    }
+    __syncthreads();
+    z.next(pl.m);
+  }
+}
+
 void launch_adj_sweeps(const Dev& d, const Bufs& b, const double* in, double* out, const int64_t* color_off,
                        int64_t n_colors, int n_pairs, hipStream_t st) {
   const std::vector<int64_t> seq = sweep_sequence(color_off, n_colors, n_pairs);
+  const ColorPlan pl = color_plan(color_off, n_colors);
+  const bool chunk = chunk_sweeps(d, pl);
+  if (chunk) {
+    const dim3 grid((unsigned)((d.nv + kChunkVel - 1) / kChunkVel));
+    const size_t lds = (size_t)d.nc * (2 * kChunkVel + 1) * sizeof(double);
+    const auto kernel = d.mf == 4 ? k_adj_chunk<4> : k_adj_chunk<kMaxFaces>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kChunkThreads), lds, st, d, b, in, out, pl, (int)seq.size());
+  }
   int64_t nonempty = 0;
   for (int64_t c = 0; c < n_colors; ++c) nonempty += color_off[c + 1] > color_off[c];
-  for (size_t q = 0; q < seq.size(); ++q) {
+  for (size_t q = 0; !chunk && q < seq.size(); ++q) {
     const int64_t c = seq[q];
     const int64_t n = color_off[c + 1] - color_off[c];
     if (d.mf == 4)
@@ -1513,6 +1688,7 @@ void launch_micro_nf(const Dev& d, const Bufs& b, const Work& w, const int64_t* 
     hipLaunchKernelGGL(k_zero<T>, dim3(nb), dim3(kBlock), 0, st, (T*)b.dG, (T*)b.dR, n);
     return;
   }
+  if (launch_micro_chunk<T, NF>(d, b, w, color_plan(color_off, n_colors), (int)seq.size(), st)) return;
   int64_t nonempty = 0;
   for (int64_t c = 0; c < n_colors; ++c) nonempty += color_off[c + 1] > color_off[c];
   constexpr int V = 16 / sizeof(T);  // 16-byte vectors: four FP32 or two FP64 velocities
