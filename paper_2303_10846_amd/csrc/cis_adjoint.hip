@@ -882,7 +882,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_ysub(int64_t nc, int64_t off, co
 }  // namespace
 
 void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, double* out, double* tmp, double* cell,
-                              const int64_t* color_off, int64_t n_colors, int micro_pairs, int macro_pairs, Flow& flow,
+                              const int64_t* color_off, int64_t n_colors, int micro_pairs, int macro_pairs, MacroSweeps& sweeps,
                               int32_t* flag, hipStream_t st) {
   const int64_t nc = d.nc, P = d.nc * d.nv;
   double* gW = cell;
@@ -902,7 +902,7 @@ void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, dou
   if (macro_pairs > 0) {
     // t = B^T z (W part), then Mac^T u = t and x_phi = z + M_c^T u
     hipLaunchKernelGGL((k_cell_vjp<true, true>), dim3((unsigned)nc), dim3(kBlock), 0, st, d, b, a);
-    if (flow.plan.m == 0 || launch_adj_macro_flow(d, b, flow, gW, u, macro_pairs, flag, st) != hipSuccess) {
+    if (sweeps.plan.m == 0 || launch_adj_macro_sweeps(d, b, sweeps, gW, u, macro_pairs, flag, st) != hipSuccess) {
       (void)hipGetLastError();
       if (d.mf == 4)
         hipLaunchKernelGGL(k_adj_macro_prep<4>, dim3(ncb), dim3(kBlock), 0, st, d, b, rc, mD);

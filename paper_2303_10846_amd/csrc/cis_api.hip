@@ -177,7 +177,7 @@ struct cis_state {
   Dev dev{};
   Bufs buf{};
   Work work{};
-  Flow flow{};
+  MacroSweeps sweeps{};
   // library-owned device arrays
   // boundary faces grouped by bc slot, in face order, then their cells (each once): host offsets into d_bnd
   struct BndGroup {
@@ -439,8 +439,8 @@ template <class Mark> cis_status enqueue_iterations(cis_state* s, const Work& w,
       mark(it, 1);
       launch_face<T>(s->dev, s->buf, w, s->stream);
       mark(it, 2);
-      // one dataflow launch where the mesh's wavefronts are resident at once, else a launch per colour
-      if (s->flow.plan.m == 0 || launch_macro_flow(s->dev, s->buf, w, s->flow, s->num.n_macro, s->stream) != hipSuccess) {
+      // one launch where the mesh fits one (cis_macro.h), else a launch per colour
+      if (s->sweeps.plan.m == 0 || launch_macro_sweeps(s->dev, s->buf, w, s->sweeps, s->num.n_macro, s->stream) != hipSuccess) {
         (void)hipGetLastError();
         launch_macro(s->dev, s->buf, w, m->color_off.data(), m->n_colors, s->num.n_macro, s->stream);
       }
@@ -463,7 +463,7 @@ cis_status finish_iterations(cis_state* s, const Work& w, int32_t n_iter, double
   if (res_hist)
     HIP_TRY(hipMemcpyAsync(res_hist, w.res, 6 * (size_t)n_iter * sizeof(double), hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(hipStreamSynchronize(s->stream));
-  if (flag[0] & kFlowStuck) return fail(CIS_E_DEVICE, "a macro sweep waited for a workgroup that never ran");
+  if (flag[0] & kSweepStuck) return fail(CIS_E_DEVICE, "a macro sweep waited for a workgroup that never ran");
   if (flag[0]) return fail(CIS_E_NONFINITE, "non-finite or non-positive state (flag " + std::to_string(flag[0]) + ")");
   return CIS_OK;
 }
@@ -1020,8 +1020,14 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
   arena.want(&w.gpf, 3 * nf);
   arena.want(&w.bnd, 6 * s->bnd_faces.size());
   s->dev.mf = mf;
-  s->flow.plan = flow_plan(s->dev, m->color_off.data(), m->n_colors);
-  if (s->flow.plan.m && !s->flow.plan.local) arena.want(&s->flow.words, (size_t)kFlowWords * nc);
+  s->sweeps.plan = sweep_plan(s->dev, m->color_off.data(), m->n_colors);
+  const int blocks = block_count(s->sweeps.plan, s->dev, nc);
+  int32_t* block_waves = nullptr;
+  if (blocks) {
+    arena.want(&s->sweeps.words, (size_t)2 * kSweepWords * nc);
+    arena.want(&s->sweeps.block.rec, (size_t)blocks);
+    arena.want(&block_waves, kBlockCands);
+  }
   s->res_cap = 64;
   cis_status e = arena.commit(s);
   if (e == CIS_OK) e = own_alloc(s, &w.res, 6 * s->res_cap);
@@ -1056,17 +1062,22 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
   d.lim_frozen = nullptr;
   fill_dev_numerics(s);
   s->buf = Bufs{buf->G, buf->R, buf->dG, buf->dR, buf->resG, buf->resR, buf->faceG, buf->faceR, buf->W, buf->q};
-  if (s->flow.words) {
-    // tag 0 in every word: no version of the first launch
-    const int64_t n = 2 * kFlowWords * nc;
+  int32_t waves[kBlockCands] = {};
+  if (blocks) {
+    // tag 0 in every word: no window of the first launch
+    const int64_t n = 4 * kSweepWords * nc;
     hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s->stream,
-                       reinterpret_cast<int32_t*>(s->flow.words), n);
+                       reinterpret_cast<int32_t*>(s->sweeps.words), n);
+    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s->stream, block_waves, (int64_t)kBlockCands);
+    block_probe(d, blocks, s->sweeps, block_waves, s->stream);
   }
   launch_upwind_codes(d, s->stream);
+  if (blocks) (void)hipMemcpyAsync(waves, block_waves, sizeof waves, hipMemcpyDeviceToHost, s->stream);
   if (hipStreamSynchronize(s->stream) != hipSuccess || hipGetLastError() != hipSuccess) {
     delete s;
     return fail(CIS_E_DEVICE, "upwind codes failed");
   }
+  if (!s->sweeps.plan.local && !(blocks && block_plan(d, blocks, s->sweeps, waves, s->stream))) s->sweeps.plan.m = 0;
   *out = s;
   return CIS_OK;
 }
@@ -1198,7 +1209,7 @@ cis_status cis_iterate(cis_state* s, int32_t n_iter, double* res_hist) {
     (void)hipStreamSynchronize(s->stream);
     const int64_t nmac = (int64_t)sweep_sequence(m->color_off.data(), m->n_colors, s->num.n_macro).size();
     const int64_t nmic = micro_launches(s->dev, m->color_off.data(), m->n_colors, s->num.n_micro);
-    const int64_t per_it[6] = {1, 1, s->flow.plan.m ? 1 : 3 + nmac, 1, nmic, 3};
+    const int64_t per_it[6] = {1, 1, s->sweeps.plan.m ? 1 : 3 + nmac, 1, nmic, 3};
     for (int32_t it = 0; it < n_iter; ++it)
       for (int k = 0; k < 6; ++k) {
         float ms = 0.0f;
@@ -1500,7 +1511,7 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
   auto precond = [&](const double* in, double* out) {
     if (macro_pairs > 0)
       launch_adj_block_precond(s->dev, s->buf, in, out, ptmp, pcell, s->mesh->color_off.data(), s->mesh->n_colors,
-                               precond_pairs, macro_pairs, s->flow, s->work.flag, q);
+                               precond_pairs, macro_pairs, s->sweeps, s->work.flag, q);
     else if (precond_pairs == 0)
       launch_precond(s->dev, s->buf, in, out, q);
     else
@@ -1583,7 +1594,7 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
   int32_t flag = 0;
   HIP_TRY(hipMemcpyAsync(&flag, s->work.flag, sizeof(flag), hipMemcpyDeviceToHost, q));
   HIP_TRY(hipStreamSynchronize(q));
-  if (flag & kFlowStuck) return fail(CIS_E_DEVICE, "a macro sweep waited for a workgroup that never ran");
+  if (flag & kSweepStuck) return fail(CIS_E_DEVICE, "a macro sweep waited for a workgroup that never ran");
   for (int k = 0; k < 3; ++k) dJdp[k] = gpJ[k] - gpL[k];
   if (info) {
     info->iterations = iters;

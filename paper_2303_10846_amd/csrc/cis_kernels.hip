@@ -1399,7 +1399,7 @@ constexpr int kChunkVel = 4;
 // Colours of a launch in one workgroup
 struct ColorPlan {
   int m;
-  int32_t off[kFlowColors], n[kFlowColors];
+  int32_t off[kSweepColors], n[kSweepColors];
 };
 
 // position -> colour of the sequence 0, 1, .., m-1, m-2, .., 0, 1, ..
@@ -1479,7 +1479,7 @@ static ColorPlan color_plan(const int64_t* color_off, int64_t n_colors) {
   for (int64_t c = 0; c < n_colors; ++c) {
     const int64_t n = color_off[c + 1] - color_off[c];
     if (n <= 0) continue;
-    if (pl.m == kFlowColors) return ColorPlan{};
+    if (pl.m == kSweepColors) return ColorPlan{};
     pl.off[pl.m] = (int32_t)color_off[c];
     pl.n[pl.m++] = (int32_t)n;
   }

@@ -1,4 +1,4 @@
-// The coloured PR-SGS sweeps of the macroscopic systems as one dataflow launch (kernels in cis_macro.hip).
+// The coloured PR-SGS sweeps of the macroscopic systems in one launch (kernels in cis_macro.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -8,43 +8,72 @@
 
 namespace cis {
 
-// 64-bit words per cell in the exchange buffer: one 128-byte line, whose 16-byte chunk c ^ (cell & 7) holds double c
-// of the increment as two tagged words (the swizzle spreads the chunks of neighbouring cells over the LDS banks).
-constexpr int kFlowWords = 16;
-constexpr int kFlowColors = 16;  // most non-empty colours of a dataflow launch
+constexpr int kSweepWords = 16;   // 64-bit words per cell in the exchange buffer (12 used): a 128-byte line
+constexpr int kSweepColors = 16;  // most non-empty colours
 
-// The non-empty colours of a mesh and the wavefronts that own them: colour k's cells off[k] .. off[k] + n[k] - 1
-// belong to wavefronts wave0[k] .. wave0[k + 1] - 1 (64 / lanes-per-cell cells each).
-struct FlowPlan {
-  int m = 0;           // non-empty colours; 0: no dataflow launch for this mesh
-  bool local = false;  // the whole mesh in one workgroup of kFlowLocal threads, increments in LDS; else one
-                       // workgroup of 64 threads per wavefront
-  int32_t off[kFlowColors], n[kFlowColors], wave0[kFlowColors + 1];
+// The non-empty colours of a mesh: colour k's cells are off[k] .. off[k] + n[k] - 1, in one workgroup those of
+// wavefronts wave0[k] .. wave0[k + 1] - 1 (64 / lanes-per-cell cells each).
+struct SweepPlan {
+  int m = 0;           // non-empty colours; 0: the mesh keeps a launch per colour
+  bool local = false;  // the whole mesh in one workgroup of kLocalThreads threads; else in blocks
+  int32_t off[kSweepColors], n[kSweepColors], wave0[kSweepColors + 1];
 };
-constexpr int kFlowLocal = 1024;
+constexpr int kLocalThreads = 1024;
 
-// Dataflow state of one cis_state: the plan, the exchange buffer [nc][kFlowWords] (device) and the tag of the
-// last version published in it.
-struct Flow {
-  FlowPlan plan;
+// The sweeps in blocks: `blocks` workgroups own equal parts of the cells in spatial order, and each relaxes in LDS
+// what its cells' values of the next h steps depend on, cells of others included, so that increments are exchanged
+// once in h steps.  The colours of the steps repeat after a period of 2(m - 1), of which h is a divisor or a multiple.
+constexpr int kBlockWaves = 8;            // wavefronts of a workgroup, each with cells of one colour
+constexpr int kBlockVals = 512;           // increments in LDS: of its wavefronts' slots, then of other cells read
+constexpr int kBlockReads = 256;          // increments read from other workgroups per window
+constexpr int kBlockCells = 16384;        // largest mesh
+constexpr int kBlockSlots = 16 * kBlockWaves;  // cells that a workgroup relaxes (half of them with 6 face slots)
+constexpr int kBlockMax = 256;            // workgroups
+struct BlockRecord {
+  int32_t reads;                     // entries of read[]
+  int32_t color[kBlockWaves];        // a wavefront's colour, -1: none
+  int32_t cell[kBlockVals];          // the cell of an increment, -1: none
+  int16_t nb[kBlockSlots][kMaxFaces];  // increments of a slot's neighbours, -1: none
+  uint8_t own[kBlockSlots];
+  int16_t read[kBlockReads];         // increments that other workgroups own
+};
+struct BlockPlan {
+  int blocks = 0;  // 0: the mesh does not fit
+  int h = 0;
+  BlockRecord* rec = nullptr;  // [blocks], device
+};
+
+// State of the sweeps of one cis_state: the plans, the exchange buffer [2][nc][kSweepWords] (device) and the tag of
+// the last window published in it.
+struct MacroSweeps {
+  SweepPlan plan;
+  BlockPlan block;
   uint64_t* words = nullptr;
   uint32_t tag = 0;
 };
 
-// The plan for a mesh on the current device: m = 0 where the mesh has more than kFlowColors colours or more
-// wavefronts than the dataflow launch takes.
-FlowPlan flow_plan(const Dev& d, const int64_t* color_off, int64_t n_colors);
+// The colours of a mesh: m = 0 where there are more than kSweepColors.
+SweepPlan sweep_plan(const Dev& d, const int64_t* color_off, int64_t n_colors);
 
-// Bit of Work::flag[0] set when a wait of a dataflow launch ran out (its results are then not valid).
-constexpr int32_t kFlowStuck = 8;
+// Blocks for a mesh of nc cells on the current device (0: none, the mesh is too large or runs in one workgroup).
+// block_probe finds the wavefronts that windows of several lengths ask of the largest block (most[kBlockCands],
+// device, zeroed); block_plan takes the longest that fits, from a host copy of them, and lays out f.block.rec
+// ([blocks]) on the stream.  false: none fits.
+constexpr int kBlockCands = 6;
+int block_count(const SweepPlan& pl, const Dev& d, int64_t nc);
+void block_probe(const Dev& d, int blocks, const MacroSweeps& f, int32_t* most, hipStream_t st);
+bool block_plan(const Dev& d, int blocks, MacroSweeps& f, const int32_t* most, hipStream_t st);
+
+// Bit of Work::flag[0] set when a wait of the sweeps in blocks ran out (its results are then not valid).
+constexpr int32_t kSweepStuck = 8;
 
 // Step 4 in one launch (spectral radii, right-hand side, n_macro forward + backward sweep pairs and the
 // predicted equilibrium); f.plan.m > 0.
-hipError_t launch_macro_flow(const Dev& d, const Bufs& b, const Work& w, Flow& f, int n_macro, hipStream_t st);
+hipError_t launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, MacroSweeps& f, int n_macro, hipStream_t st);
 
 // Mac^T u = t of the adjoint's block preconditioner, n_pairs sweep pairs from u = 0; f.plan.m > 0.  flag: as
 // Work::flag.
-hipError_t launch_adj_macro_flow(const Dev& d, const Bufs& b, Flow& f, const double* t, double* u, int n_pairs,
+hipError_t launch_adj_macro_sweeps(const Dev& d, const Bufs& b, MacroSweeps& f, const double* t, double* u, int n_pairs,
                                  int32_t* flag, hipStream_t st);
 
 }  // namespace cis

@@ -3,31 +3,30 @@
 // A sweep pair over m colours is 2(m - 1) dependent relaxations of a few thousand six-component cells: bound by
 // the latency of one step, not by arithmetic or bytes.  With one launch per relaxation a step costs a launch and
 // its drain (4 to 5.3 us), 161 times for 40 pairs of 3 colours, whatever the mesh.  Here every cell keeps its
-// operands in the registers of the lanes that own it (one lane per face slot) for all sweeps.  A mesh of up to 16
-// wavefronts runs in one workgroup: increments in LDS, one barrier a step.  A larger one, one wavefront a
-// workgroup, runs as a dataflow: a cell's relaxation waits for the versions of its neighbours' increments that
-// the coloured order asks for, and for nothing else.
+// operands in the registers of the lanes that own it (one lane per face slot) for all sweeps, and a step is an
+// exchange through LDS and a barrier.  A mesh of up to 16 wavefronts runs in one workgroup.  A larger one is cut
+// into one block a compute unit, of spatially close cells; a block relaxes, besides its own cells, those of its
+// neighbours that its own depend on within the next h steps, so that increments go through memory once in h steps
+// instead of after each (a word's way from a store to a load on another XCD takes 0.5 us, a whole exchange 1.5).
 //
-// Measured: a step costs 0.48 us in one workgroup (48 tetrahedra), 1.55 us as a dataflow on 1 296 tetrahedra (81
-// wavefronts; 0.5 us of it one word's way from a store to a load on another XCD, the rest the poll, the flux
-// and its divisions) and 1.7 us on 4 608; against the launch per colour and its separate preparation the stage
-// went from 400-450 to 77 us, from 530-640 to 250 us and from 560-680 to 274 us.
+// Measured: a step costs 0.48 us in one workgroup (48 tetrahedra), most of it the relaxation's 200 FP64 instructions, and
+// 0.9 us in blocks of windows of 4 steps (1 296 and 4 608 tetrahedra; 3 072 cells of 6 slots, windows of 3: 1.2).  Against
+// the launch per colour and its separate preparation the stage went from 400-450 to 77 us (48 tetrahedra), from
+// 530-640 to 144 us (1 296) and from 560-680 to 156 us (4 608).  With the increments exchanged after every step
+// (one wavefront a workgroup, each cell waiting for its neighbours' versions) it took 250 us on 1 296 and 274 us
+// on 4 608 tetrahedra; half as many blocks cost up to a third more where the cells are many (4 608: 208 us), since the
+// wavefronts of a colour then share a SIMD, and nothing where they are few.
 //
 // Exchange: the six doubles of an increment travel as twelve 64-bit words, each holding 32 bits of payload and
-// the 32-bit tag of its version, written with relaxed 64-bit atomics of agent scope (one word is always
-// consistent, so a reader that finds the awaited tag in all twelve has the whole version: one memory round trip
-// and no fence).  A wavefront reads the lines of its 64 neighbours with 16-byte LDS-DMA loads of device scope
-// (eight lanes a line, 64 line requests a poll instead of the 768 of one load per lane and word).  A single buffer
-// is enough: a neighbour publishes its next version only after it has read this cell's, which this cell publishes
-// after reading the neighbour's current one.
+// the 32-bit tag of its window, written and read with relaxed 64-bit atomics of agent scope (one word is always
+// consistent, so a reader that finds the awaited tag has the value: one memory round trip and no fence).
 //
-// Progress: a wavefront relaxes cells of one colour, takes its relaxations in sweep order and waits only for
-// versions of earlier positions of the sequence, so the wavefront at the lowest position can go on, provided that
-// it is resident and gets to issue.  Resident: the launch is cooperative (the runtime refuses a grid that does
-// not fit and runs no two of them at once).  Issue: a SIMD serves its oldest wavefront first, and two or three
-// polling ones kept a younger one of the same SIMD from ever publishing (seen with 3 wavefronts a SIMD, in LDS
-// and in memory alike), so the kernels are allocated one wavefront per SIMD.  Every wait is bounded besides
-// (kSpinMax).
+// Progress: a block waits only for what the others publish before they wait, so all can go on provided that all
+// are resident and get to issue.  Resident: the launch is cooperative (the runtime refuses a grid that does not fit
+// and runs no two of them at once).  Issue: a SIMD serves its oldest wavefront first, and polling ones of other
+// workgroups kept a younger one of the same SIMD from ever publishing (seen with three workgroups a SIMD), so
+// a block has its compute unit to itself (kBlockLds), and its wavefronts poll only once all of them have
+// published.  Every wait is bounded besides (kSpinMax).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -44,7 +43,7 @@ namespace cis {
 namespace {
 
 // Lanes per cell: the face slots rounded up to 4 or 8 (lanes past NF carry zero terms).
-template <int NF> struct FlowLanes { static constexpr int n = NF <= 4 ? 4 : 8; };
+template <int NF> struct SlotLanes { static constexpr int n = NF <= 4 ? 4 : 8; };
 
 // The value of slot q's lane, in the lanes of a cell's first quad (4 lanes: a quad permutation; 8 lanes: slots
 // 4 and 5 come from the second quad by a mirror of the eight).
@@ -134,26 +133,7 @@ __device__ inline void macro_flux_increment(const double* W, double nx, double n
   dG[5] = fma_(W[5], f.Un, -G0[5]);
 }
 
-// The sequence of positions is 0, 1, .., m-1, m-2, .., 0, 1, ..: colour c is relaxed on the way up and on the way
-// down, the two end colours once per turn.  Relaxations of colour c in a sequence of n positions:
-__device__ inline int relaxations(int c, int n, int m) {
-  if (m == 1) return n > 0 ? 1 : 0;
-  const int period = 2 * (m - 1), full = n / period, t = n % period;
-  const bool end = c == 0 || c == m - 1;
-  return full * (end ? 1 : 2) + (t > c ? 1 : 0) + (!end && t > period - c ? 1 : 0);
-}
-// Versions of a neighbour of colour k that the successive relaxations of a cell of colour c read: the first one
-// reads `first`; from one way up to the next way down the neighbour is relaxed `up` times, and from a way down
-// to the next way up `down` times (an end colour turns round at once: `up` and `down` in every gap).
-struct Versions {
-  uint32_t v, up, down;
-};
-__device__ inline Versions versions_of(int c, int k, int m) {
-  const uint32_t gap = k == 0 || k == m - 1 ? 1u : 2u;
-  Versions x{k < c ? 1u : 0u, k > c ? gap : 0u, k < c ? gap : 0u};
-  if (c == 0 || c == m - 1) x.up = x.down = gap;
-  return x;
-}
+// Positions of the sequence 0, 1, .., m-1, m-2, .., 0, 1, .. for so many pairs
 __host__ __device__ inline int sequence_length(int m, int pairs) {
   return pairs == 0 ? 0 : m == 1 ? 1 : pairs * 2 * (m - 1) + 1;
 }
@@ -161,21 +141,16 @@ __host__ __device__ inline int sequence_length(int m, int pairs) {
 // Polls of one wait before the kernel gives up (each at least a memory round trip); a wait that long means a
 // wavefront is missing, and the flag turns the call into an error.
 constexpr uint32_t kSpinMax = 1u << 18;
-// Wavefronts of a dataflow launch per compute unit: one per SIMD (16 384 tetrahedra or 8 192 cells of 6 face slots on
-// 256 compute units).  Larger meshes keep a launch per colour; their macro stage is 4-7% of an iteration.
-constexpr int kFlowWavesPerCu = 4;
-// Cache policy of the polls: device scope (the sc1 bit).
-constexpr int kSc1 = 16;
-
 // A lane's cell and neighbour
-template <int NF> struct FlowLane {
-  static constexpr int NL = FlowLanes<NF>::n, CW = 64 / NL;
+template <int NF> struct SlotLane {
+  static constexpr int NL = SlotLanes<NF>::n, CW = 64 / NL;
   int64_t i = 0, nb = kNoFace;  // cell, neighbour through this lane's slot (< 0: none)
-  int a = 0, color = -1, nb_color = 0;
-  bool valid = false;
+  int a = 0, color = -1;
+  bool valid = false, own = false;  // own: this launch's result of the cell comes from this lane
+  int vi = 0, vn = -1;              // places of the cell's and the neighbour's increments in LDS
 
   // color = -1 where the wavefront owns no cells
-  __device__ void find(const Dev& d, const FlowPlan& pl, int wave) {
+  __device__ void find(const Dev& d, const SweepPlan& pl, int wave) {
     const int lane = threadIdx.x & 63, m = pl.m;
     a = lane % NL;
     if (wave >= pl.wave0[m]) return;
@@ -186,8 +161,24 @@ template <int NF> struct FlowLane {
     i = pl.off[color] + (valid ? local : 0);
     if (a < NF) nb = d.cell_nb[NF * i + a];
     if (!valid) nb = kNoFace;
-    if (nb >= 0)
-      while (nb_color + 1 < m && nb >= pl.off[nb_color + 1]) ++nb_color;
+    own = valid;
+    vi = (int)i;
+    vn = (int)nb;
+  }
+  __device__ void find(const Dev& d, const BlockRecord& r) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    a = lane % NL;
+    color = __builtin_amdgcn_readfirstlane(r.color[wave]);
+    if (color < 0) return;
+    vi = wave * CW + lane / NL;
+    valid = r.cell[vi] >= 0;
+    i = valid ? r.cell[vi] : r.cell[wave * CW];
+    if (!valid) return;
+    own = r.own[vi] != 0;
+    if (a < NF) {
+      nb = d.cell_nb[NF * i + a];
+      vn = r.nb[vi][a];
+    }
   }
 };
 
@@ -207,7 +198,7 @@ template <class Put> __device__ inline void spread(int a, const double* x, Put&&
 // The sweeps in one workgroup.  inc: the cells' increments in LDS, [nc][6].  relax(xj, x): one relaxation from the
 // neighbour's increment xj to the cell's x.
 template <int NF, class Relax>
-__device__ inline void sweeps_in_lds(const FlowLane<NF>& L, int64_t nc, int m, int steps, double* inc, double* x,
+__device__ inline void sweeps_in_lds(const SlotLane<NF>& L, int64_t nc, int m, int steps, double* inc, double* x,
                                      Relax&& relax) {
   for (int64_t k = threadIdx.x; k < 6 * nc; k += blockDim.x) inc[k] = 0.0;
   __syncthreads();
@@ -216,9 +207,9 @@ __device__ inline void sweeps_in_lds(const FlowLane<NF>& L, int64_t nc, int m, i
     if (c == L.color) {
       double xj[6];
 #pragma unroll
-      for (int q = 0; q < 6; ++q) xj[q] = L.nb >= 0 ? inc[6 * L.nb + q] : 0.0;
+      for (int q = 0; q < 6; ++q) xj[q] = L.vn >= 0 ? inc[6 * L.vn + q] : 0.0;
       relax(xj, x);
-      if (L.valid) spread(L.a, x, [&](int q, double v) { inc[6 * L.i + q] = v; });
+      if (L.valid) spread(L.a, x, [&](int q, double v) { inc[6 * L.vi + q] = v; });
     }
     __syncthreads();
     if (m > 1) {
@@ -229,77 +220,131 @@ __device__ inline void sweeps_in_lds(const FlowLane<NF>& L, int64_t nc, int m, i
   }
 }
 
-// The sweeps as a dataflow over workgroups of one wavefront.  words: the exchange buffer; stage: LDS for the
-// lines of the 64 lanes' neighbours.  false: a wait ran out.
+// The position after colour c of the sequence 0, 1, .., m-1, m-2, .., 0, 1, ..
+__host__ __device__ inline void next_color(int& c, int& up, int m) {
+  if (m < 2) return;
+  if (c == m - 1) up = -1;
+  if (c == 0) up = 1;
+  c += up;
+}
+
+// LDS of a workgroup of the sweeps in blocks: more than half a compute unit's, so that no two share one (the waits of
+// one would keep the other's older wavefronts from issuing).
+constexpr int kBlockLds = 96 * 1024;
+static_assert(6 * sizeof(double) * kBlockVals <= kBlockLds, "increments of a block");
+
+// The sweeps in blocks (BlockPlan).  Within a window of h steps: LDS and a barrier a step, as in one workgroup.
+// After it every workgroup publishes the increments that it owns, tagged with the window, and waits for those that
+// it reads.  Two buffers in turn: a workgroup publishes window w after it has read window w - 1 of all its
+// neighbours, and these published that after they had read window w - 2, whose buffer w overwrites.
+// words: [2][nc][kSweepWords].  false: a wait ran out.
 template <int NF, class Relax>
-__device__ inline bool sweeps_as_flow(const FlowLane<NF>& L, int m, int steps, uint64_t* words, uint64_t* stage,
-                                      uint32_t tag0, double* x, Relax&& relax) {
-  const int lane = threadIdx.x & 63;
-  const int line = (int)(L.nb >= 0 ? L.nb : L.i);
-  uint32_t src[8];  // byte offsets of the chunks that this lane loads: of the neighbours of lanes 8k + lane / 8
+__device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord& r, int64_t nc, int m, int steps, int h,
+                                        uint64_t* words, uint32_t tag0, double* inc, double* x, Relax&& relax) {
+  constexpr int NT = 64 * kBlockWaves, K = 12 * kBlockReads / NT;
+  __shared__ int stuck;
+  const int tid = (int)threadIdx.x;
+  // this thread's words of the increments that it reads: 64-bit places in the buffer, 32-bit places in LDS
+  uint32_t src[K], dst[K];
+  const int reads = 12 * __builtin_amdgcn_readfirstlane(r.reads);
 #pragma unroll
-  for (int k = 0; k < 8; ++k)
-    src[k] = (uint32_t)__shfl(line, 8 * k + lane / 8, 64) * (uint32_t)(8 * kFlowWords) + 16u * (lane & 7);
-  Versions need = L.nb >= 0 ? versions_of(L.color, L.nb_color, m) : Versions{0, 0, 0};
-  const int count = relaxations(L.color, steps, m);
-  for (int n = 0; n < count; ++n) {
-    // the neighbour's increment of version need.v (0: before its first relaxation)
-    double xj[6] = {0, 0, 0, 0, 0, 0};
-    const uint32_t tag = tag0 + need.v;
-    bool ok = need.v == 0u;
-    uint32_t spins = 0;
-    for (uint64_t wanted = __ballot(!ok); wanted != 0; wanted = __ballot(!ok)) {
-      if (++spins > kSpinMax) return false;
+  for (int k = 0; k < K; ++k) {
+    const int t = tid + NT * k, v = t < reads ? r.read[t / 12] : 0, q = t % 12;
+    src[k] = (uint32_t)(kSweepWords * r.cell[v] + q);
+    dst[k] = (uint32_t)(12 * v + q);
+  }
+  for (int k = tid; k < 6 * kBlockVals; k += NT) inc[k] = 0.0;
+  if (tid == 0) stuck = 0;
+  __syncthreads();
+  int c = 0, up = 1;
+  uint32_t window = 0;
+  for (int p0 = 0; p0 < steps; p0 += h, ++window) {
+    const int n = steps - p0 < h ? steps - p0 : h;
+    const bool more = p0 + h < steps;
+    uint64_t* const buf = words + (window & 1u) * (uint64_t)(kSweepWords * nc);
+    const uint32_t tag = tag0 + 1u + window;
+    auto publish = [&]() {
+      if (L.own)
+        spread(L.a, x, [&](int q, double v) {
+          const uint64_t t = (uint64_t)tag << 32, u = __builtin_bit_cast(uint64_t, v);
+          uint64_t* to = buf + kSweepWords * L.i + 2 * q;
+          __hip_atomic_store(to, t | (uint32_t)u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(to + 1, t | (u >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        });
+    };
+    int last = -1;  // last step of the window that relaxes this wavefront's colour
+    for (int s = 0, cc = c, uu = up; s < n; ++s, next_color(cc, uu, m))
+      if (cc == L.color) last = s;
+    if (more && last < 0) publish();
+    for (int s = 0; s < n; ++s) {
+      if (c == L.color) {
+        double xj[6];
 #pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if ((wanted >> (8 * k)) & 0xffu)
-          __builtin_amdgcn_global_load_lds(
-              (__attribute__((address_space(1))) const void*)(reinterpret_cast<const char*>(words) + src[k]),
-              (__attribute__((address_space(3))) void*)(stage + 8 * kFlowWords * k), 16, 0, kSc1);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      const uint64_t* r = stage + kFlowWords * lane;
-      uint32_t miss = 0;
-      uint64_t lo[6], hi[6];
-#pragma unroll
-      for (int c = 0; c < 6; ++c) {
-        lo[c] = r[2 * (c ^ (line & 7))];
-        hi[c] = r[2 * (c ^ (line & 7)) + 1];
-        miss |= ((uint32_t)(lo[c] >> 32) ^ tag) | ((uint32_t)(hi[c] >> 32) ^ tag);
+        for (int q = 0; q < 6; ++q) xj[q] = L.vn >= 0 ? inc[6 * L.vn + q] : 0.0;
+        relax(xj, x);
+        if (L.valid) spread(L.a, x, [&](int q, double v) { inc[6 * L.vi + q] = v; });
+        if (more && s == last) publish();
       }
-      asm volatile("" ::: "memory");
-      if (!ok && miss == 0u) {
-        ok = true;
-#pragma unroll
-        for (int c = 0; c < 6; ++c) xj[c] = __builtin_bit_cast(double, (uint64_t)(uint32_t)lo[c] | (hi[c] << 32));
-      }
+      __syncthreads();
+      next_color(c, up, m);
     }
-    relax(xj, x);
-    if (L.valid)
-      spread(L.a, x, [&](int c, double v) {
-        const uint64_t t = (uint64_t)(tag0 + (uint32_t)n + 1u) << 32, u = __builtin_bit_cast(uint64_t, v);
-        uint64_t* dst = words + kFlowWords * L.i + 2 * (c ^ ((int)L.i & 7));
-        __hip_atomic_store(dst, t | (uint32_t)u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(dst + 1, t | (u >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      });
-    need.v += n & 1 ? need.down : need.up;
+    if (!more) break;
+    uint32_t wanted = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) wanted |= (tid + NT * k < reads ? 1u : 0u) << k;
+    for (uint32_t spins = 0; wanted != 0; ++spins) {
+      if (spins > kSpinMax) {
+        stuck = 1;
+        break;
+      }
+      uint64_t got[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if ((wanted >> k) & 1u) got[k] = __hip_atomic_load(buf + src[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (((wanted >> k) & 1u) && (uint32_t)(got[k] >> 32) == tag) {
+          reinterpret_cast<uint32_t*>(inc)[dst[k]] = (uint32_t)got[k];
+          wanted &= ~(1u << k);
+        }
+    }
+    __syncthreads();
+    if (stuck) return false;
   }
   return true;
 }
 
-// Both kernels: one workgroup of kFlowLocal threads (Local), else one wavefront a workgroup and a SIMD
-#define CIS_FLOW_KERNEL __global__ __launch_bounds__(Local ? kFlowLocal : 64) \
-    __attribute__((amdgpu_waves_per_eu(Local ? 4 : 1, Local ? 4 : 1)))
+// The forms of both kernels: the whole mesh in one workgroup of kLocalThreads threads, or blocks of 64 kBlockWaves
+// threads.
+enum Form { kLocal, kBlocks };
+#define CIS_SWEEP_KERNEL __global__ __launch_bounds__(F == kLocal ? kLocalThreads : 64 * kBlockWaves) \
+    __attribute__((amdgpu_waves_per_eu(F == kLocal ? 4 : 2, F == kLocal ? 4 : 2)))
+template <int NF, Form F> __device__ inline SlotLane<NF> lane_of(const Dev& d, const SweepPlan& pl, const BlockPlan& bp) {
+  SlotLane<NF> L;
+  if constexpr (F == kBlocks) L.find(d, bp.rec[blockIdx.x]);
+  else L.find(d, pl, __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)));
+  return L;
+}
+template <Form F, int NF, class Relax>
+__device__ inline bool sweeps(const SlotLane<NF>& L, const SweepPlan& pl, const BlockPlan& bp, int64_t nc, int steps,
+                              uint64_t* words, uint64_t* lds, uint32_t tag0, double* x, Relax&& relax) {
+  if constexpr (F == kLocal) {
+    sweeps_in_lds<NF>(L, nc, pl.m, steps, reinterpret_cast<double*>(lds), x, relax);
+    return true;
+  } else {
+    return sweeps_in_blocks<NF>(L, bp.rec[blockIdx.x], nc, pl.m, steps, bp.h, words, tag0,
+                                reinterpret_cast<double*>(lds), x, relax);
+  }
+}
 
 // Step 4 (Eqs. 38-43): macro flux per cell (Eq. 37), spectral radii r_ij (Eq. 41), diagonal and right-hand side
 // of Eq. 43, the sweeps (matrix-free increment G(W_j + dW_j) - G(W_j)) and the predicted state with its
 // equilibrium coefficients (q~ = q^n).
-template <int NF, bool Local>
-CIS_FLOW_KERNEL void k_macro_flow(Dev d, const double* W, const double* q,
-                                                                            Work w, FlowPlan pl, uint64_t* words,
-                                                                            uint32_t tag0, int steps) {
+template <int NF, Form F>
+CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Work w, SweepPlan pl, BlockPlan bp,
+                                  uint64_t* words, uint32_t tag0, int steps) {
   extern __shared__ __align__(16) uint64_t lds_words[];
-  FlowLane<NF> L;
-  L.find(d, pl, Local ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)blockIdx.x);
+  const SlotLane<NF> L = lane_of<NF, F>(d, pl, bp);
   const int64_t i = L.i;
   const GasC& g = d.gas;
   const double* geo = d.cell_geo + Lay<NF>::CG * i;
@@ -334,10 +379,10 @@ CIS_FLOW_KERNEL void k_macro_flow(Dev d, const double* W, const double* q,
   const double iD = 1.0 / D, D5 = D + 1.0 / (g.Z * tau);
 #pragma unroll
   for (int m = 0; m < 6; ++m) {
-    double F = 0.0;
-    slot_fma<NF>(F, fsum[m], iV);
-    if (L.valid && L.a == 0) w.Fmac[6 * i + m] = F;
-    res[m] = -F;
+    double Fm = 0.0;
+    slot_fma<NF>(Fm, fsum[m], iV);
+    if (L.own && L.a == 0) w.Fmac[6 * i + m] = Fm;
+    res[m] = -Fm;
   }
   res[5] += fma_(pa.rho * g.R, pa.T, -Wi[5]) / (g.Z * tau);
   double dW[6] = {0, 0, 0, 0, 0, 0};
@@ -358,13 +403,11 @@ CIS_FLOW_KERNEL void k_macro_flow(Dev d, const double* W, const double* q,
       x[m] = m == 5 ? acc / D5 : acc * iD;
     }
   };
-  if constexpr (Local) {
-    sweeps_in_lds<NF>(L, d.nc, pl.m, steps, reinterpret_cast<double*>(lds_words), dW, relax);
-  } else if (!sweeps_as_flow<NF>(L, pl.m, steps, words, lds_words, tag0, dW, relax)) {
-    atomicOr(&w.flag[0], kFlowStuck);
+  if (!sweeps<F>(L, pl, bp, d.nc, steps, words, lds_words, tag0, dW, relax)) {
+    atomicOr(&w.flag[0], kSweepStuck);
     return;
   }
-  if (!L.valid || L.a != 0) return;
+  if (!L.own || L.a != 0) return;
   // W~ = W^n + dW~; predicted equilibrium coefficients with q~ = q^n
   double Wt[6];
 #pragma unroll
@@ -385,15 +428,11 @@ CIS_FLOW_KERNEL void k_macro_flow(Dev d, const double* W, const double* q,
 // Mac^T u = t: row i couples the neighbours j through Mac_ji^T = -(A_f/V_j)(dG_n/dW (W_i)^T + r_f I)/2 with n out
 // of cell i (the flux Jacobian is odd in n and r_f is the same from both sides); Mac is the steady macro system,
 // D_i = sum_f (A_f/V_i) r_f / 2 (+ 1/(Z tau_i) for rho E_rot).
-template <int NF, bool Local>
-CIS_FLOW_KERNEL void k_adj_macro_flow(Dev d, const double* W,
-                                                                                const double* t, double* u,
-                                                                                int32_t* flag, FlowPlan pl,
-                                                                                uint64_t* words, uint32_t tag0,
-                                                                                int steps) {
+template <int NF, Form F>
+CIS_SWEEP_KERNEL void k_adj_macro_sweeps(Dev d, const double* W, const double* t, double* u, int32_t* flag, SweepPlan pl,
+                                      BlockPlan bp, uint64_t* words, uint32_t tag0, int steps) {
   extern __shared__ __align__(16) uint64_t lds_words[];
-  FlowLane<NF> L;
-  L.find(d, pl, Local ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)blockIdx.x);
+  const SlotLane<NF> L = lane_of<NF, F>(d, pl, bp);
   const int64_t i = L.i;
   const GasC& g = d.gas;
   const double* geo = d.cell_geo + Lay<NF>::CG * i;
@@ -438,39 +477,148 @@ CIS_FLOW_KERNEL void k_adj_macro_flow(Dev d, const double* W,
       ui[m] = acc * (m == 5 ? iD5 : iD);
     }
   };
-  if constexpr (Local) {
-    sweeps_in_lds<NF>(L, d.nc, pl.m, steps, reinterpret_cast<double*>(lds_words), x, relax);
-  } else if (!sweeps_as_flow<NF>(L, pl.m, steps, words, lds_words, tag0, x, relax)) {
-    atomicOr(flag, kFlowStuck);
+  if (!sweeps<F>(L, pl, bp, d.nc, steps, words, lds_words, tag0, x, relax)) {
+    atomicOr(flag, kSweepStuck);
     return;
   }
-  if (!L.valid || L.a != 0) return;
+  if (!L.own || L.a != 0) return;
 #pragma unroll
   for (int m = 0; m < 6; ++m) u[6 * i + m] = x[m];
 }
 
-constexpr size_t kStageBytes = 64 * sizeof(uint64_t) * kFlowWords;
-
-// Whether `waves` workgroups of the kernel are within the launch's bound and resident at once.
-bool all_resident(const void* kernel, int waves) {
-  int dev = 0, cus = 0, per = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, 64, kStageBytes) != hipSuccess) return false;
-  return waves <= cus * std::min(per, kFlowWavesPerCu);
+// The plan of block blockIdx.x for windows of cand.h[blockIdx.y] steps (write: into rec; else only the most
+// wavefronts of a block, into most[blockIdx.y], kTooMany where something else does not fit).
+// What a window's own values depend on, by walking its steps backwards: `need` holds the cells whose value is needed
+// after the step; those of the step's colour are relaxed in it and pass the need on to their neighbours.
+constexpr int kPlanThreads = 1024, kTooMany = 1 << 20;
+struct BlockCands {
+  int n = 0, h[kBlockCands];
+};
+__global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl, BlockCands cand, int cw, int write,
+                                                             BlockRecord* rec, int32_t* most) {
+  enum : uint8_t { kNeed = 1, kValue = 2, kSlot = 4, kOwn = 8, kRelax = 16, kRead = 32 };
+  __shared__ uint8_t st[kBlockCells];
+  __shared__ int16_t loc[kBlockCells];
+  __shared__ int wave_sum[kPlanThreads / 64];
+  const int nc = (int)d.nc, m = pl.m, tid = (int)threadIdx.x, h = cand.h[blockIdx.y];
+  const int period = m > 1 ? 2 * (m - 1) : 1, phases = h < period ? period / h : 1;
+  for (int i = tid; i < nc; i += kPlanThreads) st[i] = 0;
+  __syncthreads();
+  const int j0 = (int)((int64_t)nc * blockIdx.x / gridDim.x), j1 = (int)((int64_t)nc * (blockIdx.x + 1) / gridDim.x);
+  for (int j = j0 + tid; j < j1; j += kPlanThreads) st[d.spatial[j]] = kOwn | kValue | kSlot;
+  __syncthreads();
+  // full windows of every phase, then windows cut short after a whole number of periods and one step
+  for (int w = 0; w < phases + (h > period ? h / period : 1); ++w) {
+    const bool full = w < phases;
+    const int n = full ? h : (w - phases) * period + 1;
+    for (int i = tid; i < nc; i += kPlanThreads) st[i] = (uint8_t)((st[i] & ~kNeed) | (st[i] & kOwn ? kNeed : 0));
+    __syncthreads();
+    for (int s = n - 1; s >= 0; --s) {
+      const int at = ((full ? w * h : 0) + s) % period, c = at < m ? at : period - at;
+      for (int i = pl.off[c] + tid; i < pl.off[c] + pl.n[c]; i += kPlanThreads)
+        if (st[i] & kNeed) st[i] = (uint8_t)((st[i] & ~kNeed) | kSlot | kValue | kRelax);
+      __syncthreads();
+      for (int i = pl.off[c] + tid; i < pl.off[c] + pl.n[c]; i += kPlanThreads)
+        if (st[i] & kRelax) {
+          st[i] = (uint8_t)(st[i] & ~kRelax);
+          for (int a = 0; a < d.mf; ++a) {
+            const int32_t nb = d.cell_nb[(int64_t)d.mf * i + a];
+            if (nb >= 0) st[nb] = (uint8_t)(st[nb] | kNeed | kValue);
+          }
+        }
+      __syncthreads();
+    }
+    for (int i = tid; i < nc; i += kPlanThreads)
+      if ((st[i] & kNeed) && !(st[i] & kOwn)) st[i] |= kRead;
+    __syncthreads();
+  }
+  // places, in cell order: rank of a set flag among those of lower threads, and their sum
+  auto rank = [&](bool flag, int& total) {
+    const uint64_t mask = __ballot(flag);
+    const int lane = tid & 63, wv = tid >> 6;
+    if (lane == 0) wave_sum[wv] = __popcll(mask);
+    __syncthreads();
+    int before = 0;
+    total = 0;
+    for (int k = 0; k < kPlanThreads / 64; ++k) {
+      before += k < wv ? wave_sum[k] : 0;
+      total += wave_sum[k];
+    }
+    __syncthreads();
+    return before + __popcll(mask & ((1ull << lane) - 1ull));
+  };
+  int waves = 0, color_of_wave[kBlockWaves];
+  for (int k = 0; k < kBlockWaves; ++k) color_of_wave[k] = -1;
+  for (int c = 0; c < m; ++c) {
+    int found = 0;
+    for (int i0 = 0; i0 < pl.n[c]; i0 += kPlanThreads) {
+      const int i = pl.off[c] + i0 + tid;
+      const bool slot = i0 + tid < pl.n[c] && (st[i] & kSlot);
+      int total;
+      const int at = rank(slot, total);
+      if (slot) loc[i] = (int16_t)min(waves * cw + found + at, 32767);
+      found += total;
+    }
+    const int w = (found + cw - 1) / cw;
+    for (int k = 0; k < kBlockWaves; ++k)
+      if (k >= waves && k < waves + w) color_of_wave[k] = c;
+    waves += w;
+  }
+  const int slots = waves * cw;
+  int others = 0, reads = 0;
+  BlockRecord* const r = rec + blockIdx.x;
+  for (int i0 = 0; i0 < nc; i0 += kPlanThreads) {
+    const int i = i0 + tid;
+    const uint8_t f = i < nc ? st[i] : (uint8_t)0;
+    int total;
+    const int at = rank((f & kValue) && !(f & kSlot), total);
+    if ((f & kValue) && !(f & kSlot)) loc[i] = (int16_t)min(slots + others + at, 32767);
+    others += total;
+    const int ar = rank((f & kRead) != 0, total);
+    if (write && (f & kRead)) r->read[min(reads + ar, kBlockReads - 1)] = loc[i];
+    reads += total;
+  }
+  if (!write) {
+    const bool fits = slots + others <= kBlockVals && reads <= kBlockReads;
+    if (tid == 0) atomicMax(&most[blockIdx.y], fits ? waves : kTooMany);
+    return;
+  }
+  for (int v = tid; v < kBlockVals; v += kPlanThreads) r->cell[v] = -1;
+  __syncthreads();
+  if (tid == 0) {
+    r->reads = reads;
+    for (int k = 0; k < kBlockWaves; ++k) r->color[k] = color_of_wave[k];
+  }
+  for (int i = tid; i < nc; i += kPlanThreads) {
+    const uint8_t f = st[i];
+    if (!(f & kValue)) continue;
+    const int v = loc[i];
+    r->cell[v] = i;
+    if (!(f & kSlot)) continue;
+    r->own[v] = f & kOwn ? 1 : 0;
+    for (int a = 0; a < d.mf; ++a) {
+      const int32_t nb = d.cell_nb[(int64_t)d.mf * i + a];
+      r->nb[v][a] = nb >= 0 && (st[nb] & kValue) ? loc[nb] : (int16_t)-1;
+    }
+  }
 }
 
-template <int NF> hipError_t run(bool adjoint, const FlowPlan& pl, int64_t nc, void** args, hipStream_t st) {
-  const void* kl = adjoint ? (const void*)k_adj_macro_flow<NF, true> : (const void*)k_macro_flow<NF, true>;
-  const void* kg = adjoint ? (const void*)k_adj_macro_flow<NF, false> : (const void*)k_macro_flow<NF, false>;
-  if (pl.local)
-    return hipLaunchKernel(kl, dim3(1), dim3(kFlowLocal), args, 6 * sizeof(double) * (size_t)nc, st);
-  return hipLaunchCooperativeKernel(kg, dim3((unsigned)pl.wave0[pl.m]), dim3(64), args, (unsigned)kStageBytes, st);
+template <int NF> const void* kernel_of(bool adjoint, Form f) {
+  if (adjoint) return f == kLocal ? (const void*)k_adj_macro_sweeps<NF, kLocal> : (const void*)k_adj_macro_sweeps<NF, kBlocks>;
+  return f == kLocal ? (const void*)k_macro_sweeps<NF, kLocal> : (const void*)k_macro_sweeps<NF, kBlocks>;
+}
+
+hipError_t run(const Dev& d, bool adjoint, const MacroSweeps& fl, void** args, hipStream_t st) {
+  const Form f = fl.plan.local ? kLocal : kBlocks;
+  const void* k = d.mf == 4 ? kernel_of<4>(adjoint, f) : kernel_of<kMaxFaces>(adjoint, f);
+  if (f == kLocal) return hipLaunchKernel(k, dim3(1), dim3(kLocalThreads), args, 6 * sizeof(double) * (size_t)d.nc, st);
+  return hipLaunchCooperativeKernel(k, dim3((unsigned)fl.block.blocks), dim3(64 * kBlockWaves), args,
+                                    (unsigned)kBlockLds, st);
 }
 
 // The tags of one launch: versions 1 .. of this call follow the last call's, so no word left behind by an earlier
 // call carries an awaited tag.
-uint32_t take_tags(Flow& f, int steps) {
+uint32_t take_tags(MacroSweeps& f, int steps) {
   const uint32_t t0 = f.tag;
   f.tag += (uint32_t)steps + 1u;
   return t0;
@@ -478,50 +626,91 @@ uint32_t take_tags(Flow& f, int steps) {
 
 }  // namespace
 
-FlowPlan flow_plan(const Dev& d, const int64_t* color_off, int64_t n_colors) {
-  FlowPlan pl;
-  const int cw = 64 / (d.mf == 4 ? FlowLanes<4>::n : FlowLanes<kMaxFaces>::n);
+SweepPlan sweep_plan(const Dev& d, const int64_t* color_off, int64_t n_colors) {
+  SweepPlan pl;
+  const int cw = 64 / (d.mf == 4 ? SlotLanes<4>::n : SlotLanes<kMaxFaces>::n);
   int m = 0, waves = 0;
   for (int64_t c = 0; c < n_colors; ++c) {
     const int64_t n = color_off[c + 1] - color_off[c];
     if (n <= 0) continue;
-    if (m == kFlowColors || n > (int64_t)1 << 24) return FlowPlan();
+    if (m == kSweepColors || n > (int64_t)1 << 24) return SweepPlan();
     pl.off[m] = (int32_t)color_off[c];
     pl.n[m] = (int32_t)n;
     pl.wave0[m] = waves;
     waves += (int)((n + cw - 1) / cw);
     pl.wave0[++m] = waves;
   }
-  if (m == 0) return FlowPlan();
-  pl.local = waves <= kFlowLocal / 64;
-  if (!pl.local) {
-    const bool tet = d.mf == 4;
-    const void* k0 = tet ? (const void*)k_macro_flow<4, false> : (const void*)k_macro_flow<kMaxFaces, false>;
-    const void* k1 = tet ? (const void*)k_adj_macro_flow<4, false> : (const void*)k_adj_macro_flow<kMaxFaces, false>;
-    if (!all_resident(k0, waves) || !all_resident(k1, waves)) return FlowPlan();
-  }
+  if (m == 0) return SweepPlan();
+  pl.local = waves <= kLocalThreads / 64;
   pl.m = m;
   return pl;
 }
 
-hipError_t launch_macro_flow(const Dev& d, const Bufs& b, const Work& w, Flow& f, int n_macro, hipStream_t st) {
+int block_count(const SweepPlan& pl, const Dev& d, int64_t nc) {
+  if (pl.m == 0 || pl.local || nc > kBlockCells) return 0;
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 0;
+  for (const bool adjoint : {false, true}) {
+    const void* k = d.mf == 4 ? kernel_of<4>(adjoint, kBlocks) : kernel_of<kMaxFaces>(adjoint, kBlocks);
+    int per = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, 64 * kBlockWaves, kBlockLds) != hipSuccess || per < 1)
+      return 0;
+  }
+  return (int)std::min<int64_t>(std::min(cus, kBlockMax), nc);
+}
+
+// Windows tried, the longest first: a period and its divisors (and two periods of two colours, whose cells all
+// depend on each other only through the other colour).
+static BlockCands block_windows(int m) {
+  const int period = m > 1 ? 2 * (m - 1) : 1;
+  BlockCands c;
+  if (period == 2) c.h[c.n++] = 4;
+  for (int k = 1; k <= period && c.n < kBlockCands; ++k)
+    if (period % k == 0) c.h[c.n++] = period / k;
+  return c;
+}
+
+static int cells_per_wave(const Dev& d) { return 64 / (d.mf == 4 ? SlotLanes<4>::n : SlotLanes<kMaxFaces>::n); }
+
+void block_probe(const Dev& d, int blocks, const MacroSweeps& f, int32_t* most, hipStream_t st) {
+  const BlockCands c = block_windows(f.plan.m);
+  hipLaunchKernelGGL(k_block_plan, dim3(blocks, c.n), dim3(kPlanThreads), 0, st, d, f.plan, c, cells_per_wave(d), 0,
+                     f.block.rec, most);
+}
+
+bool block_plan(const Dev& d, int blocks, MacroSweeps& f, const int32_t* most, hipStream_t st) {
+  BlockCands c = block_windows(f.plan.m);
+  int k = 0;
+  while (k < c.n && most[k] > kBlockWaves) ++k;
+  if (k == c.n) return false;
+  c.h[0] = c.h[k];
+  hipLaunchKernelGGL(k_block_plan, dim3(blocks), dim3(kPlanThreads), 0, st, d, f.plan, c, cells_per_wave(d), 1,
+                     f.block.rec, (int32_t*)nullptr);
+  f.block.h = c.h[0];
+  f.block.blocks = blocks;
+  return true;
+}
+
+hipError_t launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, MacroSweeps& f, int n_macro, hipStream_t st) {
   int steps = sequence_length(f.plan.m, n_macro);
   uint32_t tag0 = take_tags(f, steps);
   Dev dd = d;
   const double *W = b.W, *q = b.q;
   Work ww = w;
-  void* args[] = {&dd, &W, &q, &ww, &f.plan, &f.words, &tag0, &steps};
-  return d.mf == 4 ? run<4>(false, f.plan, d.nc, args, st) : run<kMaxFaces>(false, f.plan, d.nc, args, st);
+  void* args[] = {&dd, &W, &q, &ww, &f.plan, &f.block, &f.words, &tag0, &steps};
+  return run(d, false, f, args, st);
 }
 
-hipError_t launch_adj_macro_flow(const Dev& d, const Bufs& b, Flow& f, const double* t, double* u, int n_pairs,
+hipError_t launch_adj_macro_sweeps(const Dev& d, const Bufs& b, MacroSweeps& f, const double* t, double* u, int n_pairs,
                                  int32_t* flag, hipStream_t st) {
   int steps = sequence_length(f.plan.m, n_pairs);
   uint32_t tag0 = take_tags(f, steps);
   Dev dd = d;
   const double* W = b.W;
-  void* args[] = {&dd, &W, &t, &u, &flag, &f.plan, &f.words, &tag0, &steps};
-  return d.mf == 4 ? run<4>(true, f.plan, d.nc, args, st) : run<kMaxFaces>(true, f.plan, d.nc, args, st);
+  void* args[] = {&dd, &W, &t, &u, &flag, &f.plan, &f.block, &f.words, &tag0, &steps};
+  return run(d, true, f, args, st);
 }
 
 }  // namespace cis

@@ -1,6 +1,6 @@
 """The macroscopic sweeps against the oracle at the edges of their launch forms: one workgroup (up to 16
-wavefronts), the dataflow over many workgroups, and a launch per colour beyond its largest mesh.  A wavefront
-holds 16 tetrahedra or 8 cells of 6 face slots of one colour."""
+wavefronts), blocks over up to 256 workgroups, and a launch per colour beyond the largest mesh of 16 384 cells.  A
+wavefront holds 16 tetrahedra or 8 cells of 6 face slots of one colour."""
 import sys
 
 import numpy as np
@@ -30,12 +30,17 @@ def colrel(a, b):
     ("hex", 2, 4, 1),      # two colours, one wavefront each
     ("tet", 3, 4, 0),      # no sweep: dW = 0
     ("hex", 5, 4, 40),     # 16 wavefronts: the largest one-workgroup mesh
-    ("hex", 6, 4, 40),     # 28 wavefronts, the last of each colour half full
+    ("hex", 6, 4, 40),     # 28 wavefronts, 216 blocks of one cell
     ("tet", 4, 4, 3),      # three colours, an odd number of pairs
     ("mixed", 5, 4, 40),   # 5- and 6-face cells with unused slots
     ("tet", 11, 3, 40),    # 501 wavefronts
-    ("tet", 13, 3, 40),    # 826 wavefronts: near the dataflow's largest mesh (4 a compute unit)
-    ("tet", 14, 3, 40),    # 1 031 wavefronts: a launch per colour
+    ("tet", 13, 3, 40),    # 826 wavefronts: near the largest mesh in blocks
+    ("tet", 14, 3, 40),    # 16 464 cells: a launch per colour
+    ("hex", 7, 4, 2),      # 343 cells: blocks of one and two cells; windows of two periods, the last cut to one step
+    ("hex", 8, 4, 3),      # .. and to three steps
+    ("hex", 20, 3, 40),    # 8 000 cells, 31 a block
+    ("mixed", 8, 3, 40),   # blocks with cells of 5 and 6 faces
+    ("tet", 8, 3, 1),      # one pair
 ])
 def test_macro_sweeps_match_oracle(kind, n, nv_side, n_macro):
     from paper_2303_10846_amd.binding import Solver
@@ -58,3 +63,19 @@ def test_macro_sweeps_match_oracle(kind, n, nv_side, n_macro):
     else:
         assert not np.any(s.debug_stage("dW"))
     assert colrel(s.debug_stage("Wt"), o.stage("Wt")) < TOL
+
+
+@pytest.mark.parametrize("kind,n", [("hex", 6), ("tet", 5), ("mixed", 5)])
+def test_adjoint_macro_sweeps_in_blocks(kind, n):
+    """The transposed sweeps, as a part of the adjoint's preconditioner: the same gradient in fewer iterations."""
+    from paper_2303_10846_amd.binding import Solver
+    c = configs.open_box_case(n=n, nv_side=5, kind=kind)
+    print("case", c["name"], flush=True)
+    s = Solver(c, precision="fp64")
+    s.init_equilibrium(c["W0"])
+    s.iterate(140)
+    a = s.adjoint(1, 2, restart=60, max_iter=600, rtol=1e-10)
+    ab = s.adjoint(1, 2, restart=60, max_iter=600, rtol=1e-10, macro_pairs=10)
+    print("iterations", a["iterations"], ab["iterations"], flush=True)
+    assert a["converged"] and ab["converged"] and ab["iterations"] < a["iterations"]
+    assert np.allclose(ab["dJdp"], a["dJdp"], rtol=1e-6, atol=0.0)
