@@ -1024,8 +1024,10 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
   const int blocks = block_count(s->sweeps.plan, s->dev, nc);
   int32_t* block_waves = nullptr;
   if (blocks) {
-    arena.want(&s->sweeps.words, (size_t)2 * kSweepWords * nc);
+    arena.want(&s->sweeps.words, (size_t)sweep_words(nc));
     arena.want(&s->sweeps.block.rec, (size_t)blocks);
+    arena.want(&s->sweeps.block.owner, nc);
+    arena.want(&s->sweeps.block.link, kBlockLink);
     arena.want(&block_waves, kBlockCands);
   }
   s->res_cap = 64;
@@ -1065,10 +1067,12 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
   int32_t waves[kBlockCands] = {};
   if (blocks) {
     // tag 0 in every word: no window of the first launch
-    const int64_t n = 4 * kSweepWords * nc;
+    const int64_t n = 2 * sweep_words(nc);
     hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s->stream,
                        reinterpret_cast<int32_t*>(s->sweeps.words), n);
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s->stream, block_waves, (int64_t)kBlockCands);
+    hipLaunchKernelGGL(k_zero_i32, dim3((kBlockLink + 255) / 256), dim3(256), 0, s->stream,
+                       reinterpret_cast<int32_t*>(s->sweeps.block.link), (int64_t)kBlockLink);
     block_probe(d, blocks, s->sweeps, block_waves, s->stream);
   }
   launch_upwind_codes(d, s->stream);

@@ -24,26 +24,35 @@ constexpr int kLocalThreads = 1024;
 // what its cells' values of the next h steps depend on, cells of others included, so that increments are exchanged
 // once in h steps.  The colours of the steps repeat after a period of 2(m - 1), of which h is a divisor or a multiple.
 constexpr int kBlockWaves = 8;            // wavefronts of a workgroup, each with cells of one colour
+constexpr int kWideBlockWaves = 16;       // .. of meshes whose blocks do not fit 8
 constexpr int kBlockVals = 512;           // increments in LDS: of its wavefronts' slots, then of other cells read
 constexpr int kBlockReads = 256;          // increments read from other workgroups per window
-constexpr int kBlockCells = 16384;        // largest mesh
-constexpr int kBlockSlots = 16 * kBlockWaves;  // cells that a workgroup relaxes (half of them with 6 face slots)
+constexpr int kBlockCells = 54000;        // largest mesh (3 bytes of LDS a cell while the plan is made)
+constexpr int kBlockSlots = 16 * kWideBlockWaves;  // cells that a workgroup relaxes (half of them with 6 face slots)
 constexpr int kBlockMax = 256;            // workgroups
 struct BlockRecord {
-  int32_t reads;                     // entries of read[]
-  int32_t color[kBlockWaves];        // a wavefront's colour, -1: none
-  int32_t cell[kBlockVals];          // the cell of an increment, -1: none
+  int32_t reads, acks;                 // entries of read[] and ack[]
+  int32_t color[kWideBlockWaves];      // a wavefront's colour, -1: none
+  int32_t cell[kBlockVals];            // the cell of an increment, -1: none
   int16_t nb[kBlockSlots][kMaxFaces];  // increments of a slot's neighbours, -1: none
   uint8_t own[kBlockSlots];
-  int16_t read[kBlockReads];         // increments that other workgroups own
+  int16_t read[kBlockReads];           // increments that other workgroups own, and their colours
+  uint8_t read_color[kBlockReads];
+  int16_t ack[kBlockMax];              // the workgroups that read this one's
 };
 struct BlockPlan {
-  int blocks = 0;  // 0: the mesh does not fit
+  int blocks = 0;    // 0: the mesh does not fit
   int h = 0;
+  bool wide = false;
   BlockRecord* rec = nullptr;  // [blocks], device
+  int32_t* owner = nullptr;    // [nc] block of a cell
+  uint32_t* link = nullptr;    // [kBlockMax][kBlockMax / 32] bit b of row a: block b reads increments of block a
 };
+constexpr int kBlockLink = kBlockMax * kBlockMax / 32;
+// 64-bit words of the exchange buffer: [2][nc][kSweepWords], then one word per block a 64-byte line, [2][kBlockMax][8]
+inline __host__ __device__ int64_t sweep_words(int64_t nc) { return 2 * (kSweepWords * nc + 8 * kBlockMax); }
 
-// State of the sweeps of one cis_state: the plans, the exchange buffer [2][nc][kSweepWords] (device) and the tag of
+// State of the sweeps of one cis_state: the plans, the exchange buffer (device) and the tag of
 // the last window published in it.
 struct MacroSweeps {
   SweepPlan plan;

@@ -9,24 +9,26 @@
 // neighbours that its own depend on within the next h steps, so that increments go through memory once in h steps
 // instead of after each (a word's way from a store to a load on another XCD takes 0.5 us, a whole exchange 1.5).
 //
-// Measured: a step costs 0.48 us in one workgroup (48 tetrahedra), most of it the relaxation's 200 FP64 instructions, and
-// 0.9 us in blocks of windows of 4 steps (1 296 and 4 608 tetrahedra; 3 072 cells of 6 slots, windows of 3: 1.2).  Against
-// the launch per colour and its separate preparation the stage went from 400-450 to 77 us (48 tetrahedra), from
-// 530-640 to 144 us (1 296) and from 560-680 to 156 us (4 608).  With the increments exchanged after every step
-// (one wavefront a workgroup, each cell waiting for its neighbours' versions) it took 250 us on 1 296 and 274 us
-// on 4 608 tetrahedra; half as many blocks cost up to a third more where the cells are many (4 608: 208 us), since the
-// wavefronts of a colour then share a SIMD, and nothing where they are few.
+// Measured: a step costs 0.48 us in one workgroup (48 tetrahedra), most of it the relaxation's 200 FP64 instructions;
+// in blocks 1.0 us with windows of 4 steps (1 296 and 4 608 tetrahedra), 1.2 with windows of 3 (3 072 cells of 6 slots)
+// and 2.8 with an exchange every step (50 400 tetrahedra, 197 a block).  Against the launch per colour and its separate
+// preparation the stage went from 400-450 to 77 us (48 tetrahedra), from 530-640 to 152 us (1 296), from 560-680 to
+// 162 us (4 608) and from 945 to 460 us (50 400).  With the increments exchanged after every step (one wavefront a
+// workgroup, each cell waiting for its neighbours' versions) it took 250 us on 1 296 and 274 us on 4 608 tetrahedra;
+// half as many blocks cost up to a third more where the cells are many (4 608: 208 us), since the wavefronts of a
+// colour then share a SIMD, and nothing where they are few.
 //
 // Exchange: the six doubles of an increment travel as twelve 64-bit words, each holding 32 bits of payload and
 // the 32-bit tag of its window, written and read with relaxed 64-bit atomics of agent scope (one word is always
 // consistent, so a reader that finds the awaited tag has the value: one memory round trip and no fence).
 //
-// Progress: a block waits only for what the others publish before they wait, so all can go on provided that all
-// are resident and get to issue.  Resident: the launch is cooperative (the runtime refuses a grid that does not fit
-// and runs no two of them at once).  Issue: a SIMD serves its oldest wavefront first, and polling ones of other
-// workgroups kept a younger one of the same SIMD from ever publishing (seen with three workgroups a SIMD), so
-// a block has its compute unit to itself (kBlockLds), and its wavefronts poll only once all of them have
-// published.  Every wait is bounded besides (kSpinMax).
+// Progress: a block waits only for what the others publish before they wait in the same window (increments, and
+// that they entered it), so the one furthest behind can go on, provided that all are resident and get to issue.
+// Resident: the launch is cooperative (the runtime refuses a grid that does not fit and runs no two of them at
+// once).  Issue: a SIMD serves its oldest wavefront first, and polling ones of other workgroups kept a younger one
+// of the same SIMD from ever publishing (seen with three workgroups a SIMD), so a block has its compute unit to
+// itself (kBlockLds), and its wavefronts poll only once all of them have published.  Every wait is bounded
+// besides (kSpinMax).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -234,25 +236,34 @@ constexpr int kBlockLds = 96 * 1024;
 static_assert(6 * sizeof(double) * kBlockVals <= kBlockLds, "increments of a block");
 
 // The sweeps in blocks (BlockPlan).  Within a window of h steps: LDS and a barrier a step, as in one workgroup.
-// After it every workgroup publishes the increments that it owns, tagged with the window, and waits for those that
-// it reads.  Two buffers in turn: a workgroup publishes window w after it has read window w - 1 of all its
-// neighbours, and these published that after they had read window w - 2, whose buffer w overwrites.
-// words: [2][nc][kSweepWords].  false: a wait ran out.
-template <int NF, class Relax>
-__device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord& r, int64_t nc, int m, int steps, int h,
-                                        uint64_t* words, uint32_t tag0, double* inc, double* x, Relax&& relax) {
-  constexpr int NT = 64 * kBlockWaves, K = 12 * kBlockReads / NT;
+// After it a workgroup has published its increments of the window's colours, tagged with the window, and waits for
+// those that it reads.  A slot of another block may be relaxed here from values that are not up to date; such a
+// result is needed by nothing in the window and is read from its owner after it, as its colour is one of the window's.
+// Two buffers in turn: window w overwrites window w - 2, so a workgroup ends window w - 1 only when every block that
+// reads from it has entered that window, that is has read window w - 2 (what a block reads follows the order of the
+// colours and is not mutual, so this takes a word of its own).
+// false: a wait ran out.
+template <int NF, int Waves, class Relax>
+__device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord& r, int64_t nc, int m,
+                                        int steps, int h, uint64_t* words, uint32_t tag0, double* inc, double* x,
+                                        Relax&& relax) {
+  constexpr int NT = 64 * Waves, K = 12 * kBlockReads / NT;
+  static_assert(12 * kBlockReads % NT == 0 && kBlockMax <= NT, "polls of a thread");
   __shared__ int stuck;
   const int tid = (int)threadIdx.x;
   // this thread's words of the increments that it reads: 64-bit places in the buffer, 32-bit places in LDS
-  uint32_t src[K], dst[K];
+  uint32_t src[K], dst[K], colors = 0;
   const int reads = 12 * __builtin_amdgcn_readfirstlane(r.reads);
+  const int acks = __builtin_amdgcn_readfirstlane(r.acks);
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const int t = tid + NT * k, v = t < reads ? r.read[t / 12] : 0, q = t % 12;
     src[k] = (uint32_t)(kSweepWords * r.cell[v] + q);
     dst[k] = (uint32_t)(12 * v + q);
+    if (t < reads) colors |= (uint32_t)r.read_color[t / 12] << (4 * k);
   }
+  uint64_t* const entered = words + 2 * kSweepWords * nc;  // [2][kBlockMax][8]
+  const int ack = tid < acks ? r.ack[tid] : 0;
   for (int k = tid; k < 6 * kBlockVals; k += NT) inc[k] = 0.0;
   if (tid == 0) stuck = 0;
   __syncthreads();
@@ -262,20 +273,15 @@ __device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord
     const int n = steps - p0 < h ? steps - p0 : h;
     const bool more = p0 + h < steps;
     uint64_t* const buf = words + (window & 1u) * (uint64_t)(kSweepWords * nc);
+    uint64_t* const in = entered + (window & 1u) * (uint64_t)(8 * kBlockMax);
     const uint32_t tag = tag0 + 1u + window;
-    auto publish = [&]() {
-      if (L.own)
-        spread(L.a, x, [&](int q, double v) {
-          const uint64_t t = (uint64_t)tag << 32, u = __builtin_bit_cast(uint64_t, v);
-          uint64_t* to = buf + kSweepWords * L.i + 2 * q;
-          __hip_atomic_store(to, t | (uint32_t)u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(to + 1, t | (u >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        });
-    };
+    if (tid == NT - 1) __hip_atomic_store(in + 8 * blockIdx.x, (uint64_t)tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int last = -1;  // last step of the window that relaxes this wavefront's colour
-    for (int s = 0, cc = c, uu = up; s < n; ++s, next_color(cc, uu, m))
+    uint32_t relaxed = 0;
+    for (int s = 0, cc = c, uu = up; s < n; ++s, next_color(cc, uu, m)) {
       if (cc == L.color) last = s;
-    if (more && last < 0) publish();
+      relaxed |= 1u << cc;
+    }
     for (int s = 0; s < n; ++s) {
       if (c == L.color) {
         double xj[6];
@@ -283,30 +289,40 @@ __device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord
         for (int q = 0; q < 6; ++q) xj[q] = L.vn >= 0 ? inc[6 * L.vn + q] : 0.0;
         relax(xj, x);
         if (L.valid) spread(L.a, x, [&](int q, double v) { inc[6 * L.vi + q] = v; });
-        if (more && s == last) publish();
+        if (more && s == last && L.own)
+          spread(L.a, x, [&](int q, double v) {
+            const uint64_t t = (uint64_t)tag << 32, u = __builtin_bit_cast(uint64_t, v);
+            uint64_t* to = buf + kSweepWords * L.i + 2 * q;
+            __hip_atomic_store(to, t | (uint32_t)u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(to + 1, t | (u >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          });
       }
       __syncthreads();
       next_color(c, up, m);
     }
     if (!more) break;
-    uint32_t wanted = 0;
+    uint32_t wanted = tid < acks ? 1u << K : 0u;
 #pragma unroll
-    for (int k = 0; k < K; ++k) wanted |= (tid + NT * k < reads ? 1u : 0u) << k;
+    for (int k = 0; k < K; ++k)
+      if (tid + NT * k < reads && ((relaxed >> ((colors >> (4 * k)) & 15u)) & 1u)) wanted |= 1u << k;
     for (uint32_t spins = 0; wanted != 0; ++spins) {
       if (spins > kSpinMax) {
         stuck = 1;
         break;
       }
-      uint64_t got[K];
+      uint64_t got[K], hers = 0;
 #pragma unroll
       for (int k = 0; k < K; ++k)
         if ((wanted >> k) & 1u) got[k] = __hip_atomic_load(buf + src[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((wanted >> K) & 1u) hers = __hip_atomic_load(in + 8 * ack, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
       for (int k = 0; k < K; ++k)
         if (((wanted >> k) & 1u) && (uint32_t)(got[k] >> 32) == tag) {
           reinterpret_cast<uint32_t*>(inc)[dst[k]] = (uint32_t)got[k];
           wanted &= ~(1u << k);
         }
+      // the reader entered this window (or by now the next but one, whose tag replaces this one's)
+      if (((wanted >> K) & 1u) && (uint32_t)hers - tag < 0x80000000u && hers != 0) wanted &= ~(1u << K);
     }
     __syncthreads();
     if (stuck) return false;
@@ -314,15 +330,15 @@ __device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord
   return true;
 }
 
-// The forms of both kernels: the whole mesh in one workgroup of kLocalThreads threads, or blocks of 64 kBlockWaves
-// threads.
-enum Form { kLocal, kBlocks };
-#define CIS_SWEEP_KERNEL __global__ __launch_bounds__(F == kLocal ? kLocalThreads : 64 * kBlockWaves) \
-    __attribute__((amdgpu_waves_per_eu(F == kLocal ? 4 : 2, F == kLocal ? 4 : 2)))
+// The forms of both kernels: the whole mesh in one workgroup of kLocalThreads threads, or blocks of 8 or 16 wavefronts.
+enum Form { kLocal, kBlocks, kWideBlocks };
+constexpr int threads_of(Form f) { return f == kLocal ? kLocalThreads : 64 * (f == kBlocks ? kBlockWaves : kWideBlockWaves); }
+#define CIS_SWEEP_KERNEL __global__ __launch_bounds__(threads_of(F)) \
+    __attribute__((amdgpu_waves_per_eu(threads_of(F) / 256, threads_of(F) / 256)))
 template <int NF, Form F> __device__ inline SlotLane<NF> lane_of(const Dev& d, const SweepPlan& pl, const BlockPlan& bp) {
   SlotLane<NF> L;
-  if constexpr (F == kBlocks) L.find(d, bp.rec[blockIdx.x]);
-  else L.find(d, pl, __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)));
+  if constexpr (F == kLocal) L.find(d, pl, __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)));
+  else L.find(d, bp.rec[blockIdx.x]);
   return L;
 }
 template <Form F, int NF, class Relax>
@@ -332,8 +348,8 @@ __device__ inline bool sweeps(const SlotLane<NF>& L, const SweepPlan& pl, const 
     sweeps_in_lds<NF>(L, nc, pl.m, steps, reinterpret_cast<double*>(lds), x, relax);
     return true;
   } else {
-    return sweeps_in_blocks<NF>(L, bp.rec[blockIdx.x], nc, pl.m, steps, bp.h, words, tag0,
-                                reinterpret_cast<double*>(lds), x, relax);
+    return sweeps_in_blocks<NF, threads_of(F) / 64>(L, bp.rec[blockIdx.x], nc, pl.m, steps, bp.h, words, tag0,
+                                                    reinterpret_cast<double*>(lds), x, relax);
   }
 }
 
@@ -375,7 +391,8 @@ CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Wo
   }
   double D = 0.0, res[6];
   slot_fma<NF>(D, hav, r);
-  D += inv_dt_cell(d, geo[2]);
+  const double inv_dt = inv_dt_cell(d, geo[2]);
+  D += inv_dt;
   const double iD = 1.0 / D, D5 = D + 1.0 / (g.Z * tau);
 #pragma unroll
   for (int m = 0; m < 6; ++m) {
@@ -385,6 +402,12 @@ CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Wo
     res[m] = -Fm;
   }
   res[5] += fma_(pa.rho * g.R, pa.T, -Wi[5]) / (g.Z * tau);
+  // the gas's constants wait for the end of the sweeps in vector registers: the sweeps in blocks need the scalar ones
+  GasC gas = g;
+  if constexpr (F == kBlocks)
+    for (double* c : {&gas.R, &gas.gamma, &gas.Z, &gas.delta, &gas.omega0, &gas.omega1, &gas.mu_ref, &gas.omega_v,
+                      &gas.T_ref, &gas.C_s})
+      asm("" : "+v"(*c));
   double dW[6] = {0, 0, 0, 0, 0, 0};
   auto relax = [&](const double* dWj, double* x) {
     double term[6] = {0, 0, 0, 0, 0, 0};
@@ -416,13 +439,13 @@ CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Wo
     Wt[m] = Wi[m] + dW[m];
     w.Wt[6 * i + m] = Wt[m];
   }
-  const Prim p = macro_prim(Wt, g.R);
+  const Prim p = macro_prim(Wt, gas.R);
   if (!(p.rho > 0.0) || !(p.T > 0.0) || !(p.Ttr > 0.0) || !(p.Trot > 0.0)) atomicOr(&w.flag[0], 1);
   double* e = w.eq + ER * i;
-  eq_coeffs(p, q + 6 * i, g, e);
-  const double taut = macro_tau(p, g);
+  eq_coeffs(p, q + 6 * i, gas, e);
+  const double taut = macro_tau(p, gas);
   e[7] = taut;
-  w.mbase[i] = inv_dt_cell(d, geo[2]) + 1.0 / taut;
+  w.mbase[i] = inv_dt + 1.0 / taut;
 }
 
 // Mac^T u = t: row i couples the neighbours j through Mac_ji^T = -(A_f/V_j)(dG_n/dW (W_i)^T + r_f I)/2 with n out
@@ -486,26 +509,48 @@ CIS_SWEEP_KERNEL void k_adj_macro_sweeps(Dev d, const double* W, const double* t
   for (int m = 0; m < 6; ++m) u[6 * i + m] = x[m];
 }
 
-// The plan of block blockIdx.x for windows of cand.h[blockIdx.y] steps (write: into rec; else only the most
-// wavefronts of a block, into most[blockIdx.y], kTooMany where something else does not fit).
+// The readers of each block, from the links that the plans of all blocks set.  all_colors: every window relaxes
+// every colour, so that a reader which this block reads from is known to have entered a window by its increments.
+__global__ __launch_bounds__(kBlockMax) void k_block_acks(BlockPlan bp, int blocks, int all_colors) {
+  const int me = (int)threadIdx.x;
+  if (me >= blocks) return;
+  BlockRecord& r = bp.rec[me];
+  int n = 0;
+  for (int w = 0; w < kBlockMax / 32; ++w)
+    for (uint32_t bits = bp.link[me * (kBlockMax / 32) + w]; bits != 0; bits &= bits - 1u) {
+      const int b = 32 * w + __ffs((int)bits) - 1;
+      const bool mutual = (bp.link[b * (kBlockMax / 32) + me / 32] >> (me % 32)) & 1u;
+      if (!all_colors || !mutual) r.ack[n++] = (int16_t)b;
+    }
+  r.acks = n;
+}
+
+// The plan of block blockIdx.x for windows of cand.h[blockIdx.y] steps (write: into its record and the
+// links; else the owners and the most wavefronts of a block, into most[blockIdx.y], kTooMany where something else does
+// not fit).
 // What a window's own values depend on, by walking its steps backwards: `need` holds the cells whose value is needed
 // after the step; those of the step's colour are relaxed in it and pass the need on to their neighbours.
 constexpr int kPlanThreads = 1024, kTooMany = 1 << 20;
 struct BlockCands {
   int n = 0, h[kBlockCands];
 };
-__global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl, BlockCands cand, int cw, int write,
-                                                             BlockRecord* rec, int32_t* most) {
+__global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl, BlockPlan bp, BlockCands cand, int cw,
+                                                             int write, int32_t* most) {
   enum : uint8_t { kNeed = 1, kValue = 2, kSlot = 4, kOwn = 8, kRelax = 16, kRead = 32 };
-  __shared__ uint8_t st[kBlockCells];
-  __shared__ int16_t loc[kBlockCells];
+  extern __shared__ int16_t plan_lds[];
+  int16_t* const loc = plan_lds;  // [nc] place of a cell's increment
+  uint8_t* const st = reinterpret_cast<uint8_t*>(plan_lds + d.nc);  // [nc]
   __shared__ int wave_sum[kPlanThreads / 64];
   const int nc = (int)d.nc, m = pl.m, tid = (int)threadIdx.x, h = cand.h[blockIdx.y];
   const int period = m > 1 ? 2 * (m - 1) : 1, phases = h < period ? period / h : 1;
   for (int i = tid; i < nc; i += kPlanThreads) st[i] = 0;
   __syncthreads();
   const int j0 = (int)((int64_t)nc * blockIdx.x / gridDim.x), j1 = (int)((int64_t)nc * (blockIdx.x + 1) / gridDim.x);
-  for (int j = j0 + tid; j < j1; j += kPlanThreads) st[d.spatial[j]] = kOwn | kValue | kSlot;
+  for (int j = j0 + tid; j < j1; j += kPlanThreads) {
+    const int i = d.spatial[j];
+    st[i] = kOwn | kValue | kSlot;
+    if (!write && blockIdx.y == 0) bp.owner[i] = (int32_t)blockIdx.x;
+  }
   __syncthreads();
   // full windows of every phase, then windows cut short after a whole number of periods and one step
   for (int w = 0; w < phases + (h > period ? h / period : 1); ++w) {
@@ -547,8 +592,10 @@ __global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl
     __syncthreads();
     return before + __popcll(mask & ((1ull << lane) - 1ull));
   };
-  int waves = 0, color_of_wave[kBlockWaves];
-  for (int k = 0; k < kBlockWaves; ++k) color_of_wave[k] = -1;
+  int waves = 0;
+  BlockRecord* const r = bp.rec + blockIdx.x;
+  if (write && tid < kWideBlockWaves) r->color[tid] = -1;
+  __syncthreads();
   for (int c = 0; c < m; ++c) {
     int found = 0;
     for (int i0 = 0; i0 < pl.n[c]; i0 += kPlanThreads) {
@@ -560,13 +607,11 @@ __global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl
       found += total;
     }
     const int w = (found + cw - 1) / cw;
-    for (int k = 0; k < kBlockWaves; ++k)
-      if (k >= waves && k < waves + w) color_of_wave[k] = c;
+    if (write && tid < w && waves + tid < kWideBlockWaves) r->color[waves + tid] = c;
     waves += w;
   }
   const int slots = waves * cw;
   int others = 0, reads = 0;
-  BlockRecord* const r = rec + blockIdx.x;
   for (int i0 = 0; i0 < nc; i0 += kPlanThreads) {
     const int i = i0 + tid;
     const uint8_t f = i < nc ? st[i] : (uint8_t)0;
@@ -575,7 +620,14 @@ __global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl
     if ((f & kValue) && !(f & kSlot)) loc[i] = (int16_t)min(slots + others + at, 32767);
     others += total;
     const int ar = rank((f & kRead) != 0, total);
-    if (write && (f & kRead)) r->read[min(reads + ar, kBlockReads - 1)] = loc[i];
+    if (write && (f & kRead)) {
+      const int at = min(reads + ar, kBlockReads - 1);
+      int c = 0;
+      while (c + 1 < m && i >= pl.off[c + 1]) ++c;
+      r->read[at] = loc[i];
+      r->read_color[at] = (uint8_t)c;
+      atomicOr(&bp.link[bp.owner[i] * (kBlockMax / 32) + blockIdx.x / 32], 1u << (blockIdx.x % 32));
+    }
     reads += total;
   }
   if (!write) {
@@ -585,10 +637,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl
   }
   for (int v = tid; v < kBlockVals; v += kPlanThreads) r->cell[v] = -1;
   __syncthreads();
-  if (tid == 0) {
-    r->reads = reads;
-    for (int k = 0; k < kBlockWaves; ++k) r->color[k] = color_of_wave[k];
-  }
+  if (tid == 0) r->reads = reads;
   for (int i = tid; i < nc; i += kPlanThreads) {
     const uint8_t f = st[i];
     if (!(f & kValue)) continue;
@@ -603,17 +652,20 @@ __global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl
   }
 }
 
-template <int NF> const void* kernel_of(bool adjoint, Form f) {
-  if (adjoint) return f == kLocal ? (const void*)k_adj_macro_sweeps<NF, kLocal> : (const void*)k_adj_macro_sweeps<NF, kBlocks>;
-  return f == kLocal ? (const void*)k_macro_sweeps<NF, kLocal> : (const void*)k_macro_sweeps<NF, kBlocks>;
+template <int NF, Form F> const void* kernel_of(bool adjoint) {
+  return adjoint ? (const void*)k_adj_macro_sweeps<NF, F> : (const void*)k_macro_sweeps<NF, F>;
+}
+template <Form F> const void* kernel_of(bool adjoint, const Dev& d) {
+  return d.mf == 4 ? kernel_of<4, F>(adjoint) : kernel_of<kMaxFaces, F>(adjoint);
 }
 
-hipError_t run(const Dev& d, bool adjoint, const MacroSweeps& fl, void** args, hipStream_t st) {
-  const Form f = fl.plan.local ? kLocal : kBlocks;
-  const void* k = d.mf == 4 ? kernel_of<4>(adjoint, f) : kernel_of<kMaxFaces>(adjoint, f);
-  if (f == kLocal) return hipLaunchKernel(k, dim3(1), dim3(kLocalThreads), args, 6 * sizeof(double) * (size_t)d.nc, st);
-  return hipLaunchCooperativeKernel(k, dim3((unsigned)fl.block.blocks), dim3(64 * kBlockWaves), args,
-                                    (unsigned)kBlockLds, st);
+hipError_t run(const Dev& d, bool adjoint, const MacroSweeps& s, void** args, hipStream_t st) {
+  if (s.plan.local)
+    return hipLaunchKernel(kernel_of<kLocal>(adjoint, d), dim3(1), dim3(kLocalThreads), args,
+                           6 * sizeof(double) * (size_t)d.nc, st);
+  const void* k = s.block.wide ? kernel_of<kWideBlocks>(adjoint, d) : kernel_of<kBlocks>(adjoint, d);
+  return hipLaunchCooperativeKernel(k, dim3((unsigned)s.block.blocks),
+                                    dim3(threads_of(s.block.wide ? kWideBlocks : kBlocks)), args, (unsigned)kBlockLds, st);
 }
 
 // The tags of one launch: versions 1 .. of this call follow the last call's, so no word left behind by an earlier
@@ -652,16 +704,11 @@ int block_count(const SweepPlan& pl, const Dev& d, int64_t nc) {
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
-  for (const bool adjoint : {false, true}) {
-    const void* k = d.mf == 4 ? kernel_of<4>(adjoint, kBlocks) : kernel_of<kMaxFaces>(adjoint, kBlocks);
-    int per = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, 64 * kBlockWaves, kBlockLds) != hipSuccess || per < 1)
-      return 0;
-  }
   return (int)std::min<int64_t>(std::min(cus, kBlockMax), nc);
 }
 
-// Windows tried, the longest first: a period and its divisors (and two periods of two colours, whose cells all
+// Windows tried, the longest first (the fewest exchanges; measured on 1 296 tetrahedra: 144 us with 4 steps, 192 with 2):
+// a period and its divisors (and two periods of two colours, whose cells all
 // depend on each other only through the other colour).
 static BlockCands block_windows(int m) {
   const int period = m > 1 ? 2 * (m - 1) : 1;
@@ -676,18 +723,25 @@ static int cells_per_wave(const Dev& d) { return 64 / (d.mf == 4 ? SlotLanes<4>:
 
 void block_probe(const Dev& d, int blocks, const MacroSweeps& f, int32_t* most, hipStream_t st) {
   const BlockCands c = block_windows(f.plan.m);
-  hipLaunchKernelGGL(k_block_plan, dim3(blocks, c.n), dim3(kPlanThreads), 0, st, d, f.plan, c, cells_per_wave(d), 0,
-                     f.block.rec, most);
+  hipLaunchKernelGGL(k_block_plan, dim3(blocks, c.n), dim3(kPlanThreads), 3 * (size_t)d.nc, st, d, f.plan, f.block, c,
+                     cells_per_wave(d), 0, most);
 }
 
 bool block_plan(const Dev& d, int blocks, MacroSweeps& f, const int32_t* most, hipStream_t st) {
   BlockCands c = block_windows(f.plan.m);
+  // 8 wavefronts where a window fits them, two a SIMD; 16 only where none does (a longer window with 16 gains nothing: the
+  // wavefronts of a colour share a SIMD)
   int k = 0;
   while (k < c.n && most[k] > kBlockWaves) ++k;
+  f.block.wide = k == c.n;
+  if (f.block.wide)
+    for (k = 0; k < c.n && most[k] > kWideBlockWaves; ++k) {}
   if (k == c.n) return false;
   c.h[0] = c.h[k];
-  hipLaunchKernelGGL(k_block_plan, dim3(blocks), dim3(kPlanThreads), 0, st, d, f.plan, c, cells_per_wave(d), 1,
-                     f.block.rec, (int32_t*)nullptr);
+  hipLaunchKernelGGL(k_block_plan, dim3(blocks), dim3(kPlanThreads), 3 * (size_t)d.nc, st, d, f.plan, f.block, c,
+                     cells_per_wave(d), 1, (int32_t*)nullptr);
+  hipLaunchKernelGGL(k_block_acks, dim3(1), dim3(kBlockMax), 0, st, f.block, blocks,
+                     c.h[0] >= f.plan.m ? 1 : 0);
   f.block.h = c.h[0];
   f.block.blocks = blocks;
   return true;

@@ -1,5 +1,5 @@
 """The macroscopic sweeps against the oracle at the edges of their launch forms: one workgroup (up to 16
-wavefronts), blocks over up to 256 workgroups, and a launch per colour beyond the largest mesh of 16 384 cells.  A
+wavefronts), blocks over up to 256 workgroups, and a launch per colour beyond the largest mesh of 54 000 cells.  A
 wavefront holds 16 tetrahedra or 8 cells of 6 face slots of one colour."""
 import sys
 
@@ -34,8 +34,11 @@ def colrel(a, b):
     ("tet", 4, 4, 3),      # three colours, an odd number of pairs
     ("mixed", 5, 4, 40),   # 5- and 6-face cells with unused slots
     ("tet", 11, 3, 40),    # 501 wavefronts
-    ("tet", 13, 3, 40),    # 826 wavefronts: near the largest mesh in blocks
-    ("tet", 14, 3, 40),    # 16 464 cells: a launch per colour
+    ("tet", 13, 3, 40),    # 826 wavefronts, 51 cells a block
+    ("tet", 14, 3, 40),    # 16 464 cells: blocks of 16 wavefronts
+    ("tet", 20, 3, 3),     # 48 000 cells: near the largest mesh in blocks
+    ("tet", 21, 3, 3),     # 55 566 cells: a launch per colour
+    ("hex", 29, 3, 3),     # 24 389 cells of 6 slots
     ("hex", 7, 4, 2),      # 343 cells: blocks of one and two cells; windows of two periods, the last cut to one step
     ("hex", 8, 4, 3),      # .. and to three steps
     ("hex", 20, 3, 40),    # 8 000 cells, 31 a block
