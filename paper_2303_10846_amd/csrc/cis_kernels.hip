@@ -1067,8 +1067,9 @@ template <class T, int V> struct alignas(sizeof(T) * V) VecR { T v[V]; };
 // The micro residual with V adjacent velocities per thread moved as 16-byte vectors (four FP32 or two FP64
 // values; nv a multiple of V and 16-byte aligned rows, so every row offset keeps them aligned), Res stored
 // non-temporally; the arithmetic of k_residual<T>, velocity by velocity.  Measured on the sphere (4140
-// velocities): mixed 1.68 -> 1.50 ms with V = 4; FP64 4.10 -> 2.89 ms with V = 2.
-template <class T, int V, int NF>
+// velocities): mixed 1.68 -> 1.50 ms with V = 4; FP64 4.10 -> 2.89 ms with V = 2.  Flux: F instead of Res
+// (15 552 tetrahedra x 2 708, FP32: 258 -> 216 us against one velocity a lane).
+template <class T, int V, int NF, bool Flux>
 __global__ __launch_bounds__(kBlock) void k_residual_vec(Dev d, Bufs b, Work w, T* outG, T* outR) {
   const CellChunk cc = cell_chunk(d.nc);
   if (cc.cell >= d.nc) return;
@@ -1088,29 +1089,42 @@ __global__ __launch_bounds__(kBlock) void k_residual_vec(Dev d, Bufs b, Work w, 
     xR[a] = *reinterpret_cast<const VF*>((const T*)b.faceR + f * nv + k);
     sg[a] = (T)(geo[CG_FACE + CG_SLOT * a] * geo[1]);
   }
-  const VF pG = *reinterpret_cast<const VF*>((const T*)b.G + i * nv + k);
-  const VF pR = *reinterpret_cast<const VF*>((const T*)b.R + i * nv + k);
-  const T* dvs = std::is_same<T, float>::value ? (const T*)d.dvs_f : (const T*)d.dvs;
-  const VF ux = *reinterpret_cast<const VF*>(dvs + k);
-  const VF uy = *reinterpret_cast<const VF*>(dvs + nv + k);
-  const VF uz = *reinterpret_cast<const VF*>(dvs + 2 * nv + k);
-  const double* ec = w.eq + ER * i;
-  Eq<T> e;
-  e.load(ec);
-  const T itau = (T)(1.0 / ec[7]);
   VF oG, oR;
+  if constexpr (Flux) {
 #pragma unroll
-  for (int q = 0; q < V; ++q) {
-    T FG = sg[0] * xG[0].v[q], FR = sg[0] * xR[0].v[q];
+    for (int q = 0; q < V; ++q) {
+      oG.v[q] = sg[0] * xG[0].v[q];
+      oR.v[q] = sg[0] * xR[0].v[q];
 #pragma unroll
-    for (int a = 1; a < NF; ++a) {
-      FG += sg[a] * xG[a].v[q];
-      FR += sg[a] * xR[a].v[q];
+      for (int a = 1; a < NF; ++a) {
+        oG.v[q] += sg[a] * xG[a].v[q];
+        oR.v[q] += sg[a] * xR[a].v[q];
+      }
     }
-    T gs, rs;
-    e.eval(ux.v[q], uy.v[q], uz.v[q], gs, rs);
-    oG.v[q] = (gs - pG.v[q]) * itau - FG;
-    oR.v[q] = (rs - pR.v[q]) * itau - FR;
+  } else {
+    const VF pG = *reinterpret_cast<const VF*>((const T*)b.G + i * nv + k);
+    const VF pR = *reinterpret_cast<const VF*>((const T*)b.R + i * nv + k);
+    const T* dvs = std::is_same<T, float>::value ? (const T*)d.dvs_f : (const T*)d.dvs;
+    const VF ux = *reinterpret_cast<const VF*>(dvs + k);
+    const VF uy = *reinterpret_cast<const VF*>(dvs + nv + k);
+    const VF uz = *reinterpret_cast<const VF*>(dvs + 2 * nv + k);
+    const double* ec = w.eq + ER * i;
+    Eq<T> e;
+    e.load(ec);
+    const T itau = (T)(1.0 / ec[7]);
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+      T FG = sg[0] * xG[0].v[q], FR = sg[0] * xR[0].v[q];
+#pragma unroll
+      for (int a = 1; a < NF; ++a) {
+        FG += sg[a] * xG[a].v[q];
+        FR += sg[a] * xR[a].v[q];
+      }
+      T gs, rs;
+      e.eval(ux.v[q], uy.v[q], uz.v[q], gs, rs);
+      oG.v[q] = (gs - pG.v[q]) * itau - FG;
+      oR.v[q] = (rs - pR.v[q]) * itau - FR;
+    }
   }
   typedef T ev __attribute__((ext_vector_type(V)));
   ev sG, sR;
@@ -1138,17 +1152,16 @@ template <class T, int NF>
 void launch_residual_nf(const Dev& d, const Bufs& b, const Work& w, void* outG, void* outR, int flux_only,
                         hipStream_t st) {
   constexpr int V = 16 / sizeof(T);
-  if (!flux_only && rows_aligned<T>(d, b, V) && (uintptr_t)outG % 16 == 0 && (uintptr_t)outR % 16 == 0) {
-    hipLaunchKernelGGL((k_residual_vec<T, V, NF>), cell_chunk_grid_u<V>(d.nc, d.nv), dim3(kBlock), 0, st, d, b, w,
-                       (T*)outG, (T*)outR);
-    return;
-  }
-  if (std::is_same<T, float>::value && !flux_only && rows_aligned<T>(d, b, 2) && (uintptr_t)outG % 8 == 0 &&
-      (uintptr_t)outR % 8 == 0) {
-    hipLaunchKernelGGL((k_residual_vec<float, 2, NF>), cell_chunk_grid_u<2>(d.nc, d.nv), dim3(kBlock), 0, st, d, b,
-                       w, (float*)outG, (float*)outR);
-    return;
-  }
+  const auto vec = [&](auto width) {
+    constexpr int W = decltype(width)::value;
+    const uintptr_t bytes = W * sizeof(T);
+    if (!rows_aligned<T>(d, b, W) || (uintptr_t)outG % bytes || (uintptr_t)outR % bytes) return false;
+    const auto kernel = flux_only ? k_residual_vec<T, W, NF, true> : k_residual_vec<T, W, NF, false>;
+    hipLaunchKernelGGL(kernel, cell_chunk_grid_u<W>(d.nc, d.nv), dim3(kBlock), 0, st, d, b, w, (T*)outG, (T*)outR);
+    return true;
+  };
+  if (vec(std::integral_constant<int, V>{})) return;
+  if (std::is_same<T, float>::value && vec(std::integral_constant<int, 2>{})) return;
   hipLaunchKernelGGL((k_residual<T, NF>), cell_chunk_grid<T>(d.nc, d.nv), dim3(kBlock), 0, st, d, b, w, (T*)outG,
                      (T*)outR, flux_only);
 }
