@@ -969,6 +969,14 @@ __global__ __launch_bounds__(kBlock) void k_axpby(int64_t n, double a, const dou
     y[i] = (c == 0.0 ? 0.0 : c * y[i]) + (a == 0.0 ? 0.0 : a * x[i]);
 }
 
+// w /= sqrt(*n2), left as it is where that is not positive
+__global__ __launch_bounds__(kBlock) void k_normalize(int64_t n, const double* n2, double* w) {
+  const double norm = sqrt(*n2);
+  if (!(norm > 0.0)) return;
+  const double a = 1.0 / norm;
+  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) w[i] = a * w[i];
+}
+
 unsigned grid_for(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + kBlock - 1) / kBlock, 8192)); }
 }  // namespace
 
@@ -983,6 +991,10 @@ void launch_gemv_sub(const double* V, int64_t n, int nvec, const double* h, doub
 
 void launch_axpby(int64_t n, double a, const double* x, double c, double* y, hipStream_t st) {
   hipLaunchKernelGGL(k_axpby, dim3(grid_for(n)), dim3(kBlock), 0, st, n, a, x, c, y);
+}
+
+void launch_normalize(int64_t n, const double* n2, double* w, hipStream_t st) {
+  hipLaunchKernelGGL(k_normalize, dim3(grid_for(n)), dim3(kBlock), 0, st, n, n2, w);
 }
 
 int dot_partials() { return kDotBlocks; }

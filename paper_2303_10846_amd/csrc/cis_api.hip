@@ -26,6 +26,7 @@ using namespace cis;
 // address from hipGetSymbolAddress once per device (scratch_of_device) and passes that.
 static constexpr int32_t kNoAllocMaxIter = 4096;
 static constexpr size_t kScratchFlagDoubles = 32;
+static constexpr int kMaxRestart = 1000;  // of the adjoint's GMRES
 static constexpr size_t kScratchPartDoubles = 6 * (size_t)kResidualParts;
 static constexpr size_t kScratchDoubles = kScratchFlagDoubles + kScratchPartDoubles + 6 * (size_t)kNoAllocMaxIter;
 static constexpr int kMaxDevices = 64;
@@ -178,6 +179,7 @@ struct cis_state {
   Bufs buf{};
   Work work{};
   MacroSweeps sweeps{};
+  double* krylov = nullptr;  // Gram-Schmidt coefficients and norm of the adjoint's Krylov step
   // library-owned device arrays
   // boundary faces grouped by bc slot, in face order, then their cells (each once): host offsets into d_bnd
   struct BndGroup {
@@ -1019,6 +1021,7 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
   arena.want(&w.respart, 6 * 256);
   arena.want(&w.gpf, 3 * nf);
   arena.want(&w.bnd, 6 * s->bnd_faces.size());
+  arena.want(&s->krylov, 2 * kMaxRestart + 3);
   s->dev.mf = mf;
   s->sweeps.plan = sweep_plan(s->dev, m->color_off.data(), m->n_colors);
   const int blocks = block_count(s->sweeps.plan, s->dev, nc);
@@ -1480,7 +1483,7 @@ cis_status cis_residual_vjp(cis_state* s, const double* vG, const double* vR, co
 
 cis_status cis_adjoint_required_bytes(const cis_state* s, int32_t restart, int64_t* bytes) {
   if (!s || !bytes) return fail(CIS_E_INVALID_ARG, "NULL argument");
-  if (restart < 1 || restart > 1000) return fail(CIS_E_INVALID_ARG, "restart must be in 1..1000");
+  if (restart < 1 || restart > kMaxRestart) return fail(CIS_E_INVALID_ARG, "restart must be in 1..1000");
   *bytes = adjoint_doubles(s, restart) * (int64_t)sizeof(double);
   return CIS_OK;
 }
@@ -1491,7 +1494,7 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
   if (!s || !work || !lam || !dJdp) return fail(CIS_E_INVALID_ARG, "NULL argument");
   if (s->precision != CIS_FP64) return fail(CIS_E_UNSUPPORTED, "the adjoint is FP64 only");
   if (s->num.limiter == 4) return fail(CIS_E_UNSUPPORTED, "limiter 4 updates its values: use limiter 3 (stored values)");
-  if (restart < 1 || restart > 1000 || max_iter < 0 || !(rtol > 0.0) || precond_pairs < 0 || precond_pairs > 64 ||
+  if (restart < 1 || restart > kMaxRestart || max_iter < 0 || !(rtol > 0.0) || precond_pairs < 0 || precond_pairs > 64 ||
       macro_pairs < 0 || macro_pairs > 200)
     return fail(CIS_E_INVALID_ARG, "restart, max_iter, rtol, precond_pairs or macro_pairs out of range");
   if (work_bytes < adjoint_doubles(s, restart) * (int64_t)sizeof(double))
@@ -1534,7 +1537,7 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
   int32_t iters = 0;
   double beta = bnorm;
   launch_axpby(N, 1.0, b, 0.0, V, q);  // r = b - A*0
-  std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), gv(m + 1), y(m), h(m + 1), h2(m + 1);
+  std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), gv(m + 1), y(m), h(m + 1), h2(2 * m + 3);
   bool done = bnorm == 0.0;
   while (!done && iters < max_iter) {
     launch_axpby(N, 1.0 / beta, V, 0.0, V, q);
@@ -1546,16 +1549,19 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
       double* w = V + (int64_t)(j + 1) * N;
       precond(vj, z);
       run_vjp(s, z, 0.0, sl, w);
-      // classical Gram-Schmidt, twice
-      if ((st = dots(V, j + 1, w, h.data())) != CIS_OK) return st;
-      launch_gemv_sub(V, N, j + 1, hdev, w, q);
-      if ((st = dots(V, j + 1, w, h2.data())) != CIS_OK) return st;
-      launch_gemv_sub(V, N, j + 1, hdev, w, q);
-      for (int i = 0; i <= j; ++i) h[i] += h2[i];
-      double hn2;
-      if ((st = dots(w, 1, w, &hn2)) != CIS_OK) return st;
-      const double hn = std::sqrt(hn2);
-      if (hn > 0.0) launch_axpby(N, 1.0 / hn, w, 0.0, w, q);
+      // classical Gram-Schmidt, twice, and the norm; the coefficients stay on the device until the step's end (a copy
+      // and a wait for each of the three left the device idle for 40 us at a time)
+      double* const hd = s->krylov;
+      launch_dots(V, N, j + 1, w, part, hd, q);
+      launch_gemv_sub(V, N, j + 1, hd, w, q);
+      launch_dots(V, N, j + 1, w, part, hd + (j + 1), q);
+      launch_gemv_sub(V, N, j + 1, hd + (j + 1), w, q);
+      launch_dots(w, N, 1, w, part, hd + 2 * (j + 1), q);
+      launch_normalize(N, hd + 2 * (j + 1), w, q);
+      HIP_TRY(hipMemcpyAsync(h2.data(), hd, (2 * j + 3) * sizeof(double), hipMemcpyDeviceToHost, q));
+      HIP_TRY(hipStreamSynchronize(q));
+      for (int i = 0; i <= j; ++i) h[i] = h2[i] + h2[j + 1 + i];
+      const double hn = std::sqrt(h2[2 * (j + 1)]);
       // Givens rotations on column j
       for (int i = 0; i < j; ++i) {
         const double t = cs[i] * h[i] + sn[i] * h[i + 1];

@@ -156,6 +156,7 @@ void launch_adj_sweeps(const Dev& d, const Bufs& b, const double* in, double* ou
 void launch_dots(const double* V, int64_t n, int nvec, const double* w, double* part, double* out, hipStream_t st);
 void launch_gemv_sub(const double* V, int64_t n, int nvec, const double* h, double* w, hipStream_t st);
 void launch_axpby(int64_t n, double a, const double* x, double c, double* y, hipStream_t st);
+void launch_normalize(int64_t n, const double* n2, double* w, hipStream_t st);  // w /= sqrt(*n2) where positive
 int dot_partials();
 
 }  // namespace cis
