@@ -9,13 +9,13 @@
 // neighbours that its own depend on within the next h steps, so that increments go through memory once in h steps
 // instead of after each (a word's way from a store to a load on another XCD takes 0.5 us, a whole exchange 1.5).
 //
-// Measured: a step costs 0.48 us in one workgroup (48 tetrahedra), most of it the relaxation's 200 FP64 instructions;
-// in blocks 1.0 us with windows of 4 steps (1 296 and 4 608 tetrahedra), 1.2 with windows of 3 (3 072 cells of 6 slots)
-// and 2.8 with an exchange every step (50 400 tetrahedra, 197 a block).  Against the launch per colour and its separate
-// preparation the stage went from 400-450 to 77 us (48 tetrahedra), from 530-640 to 152 us (1 296), from 560-680 to
-// 162 us (4 608) and from 945 to 460 us (50 400).  With the increments exchanged after every step (one wavefront a
+// Measured: a step costs 0.47 us in one workgroup (48 tetrahedra), most of it the relaxation's chain of FP64
+// instructions; in blocks 0.85 us with windows of 4 steps (1 296 and 4 608 tetrahedra), 1.0 with windows of 3 (3 072 cells
+// of 6 slots) and 2.8 with an exchange every step (50 400 tetrahedra, 197 a block).  Against the launch per colour and its
+// separate preparation the stage went from 400-450 to 76 us (48 tetrahedra), from 530-640 to 135 us (1 296), from 560-680
+// to 145 us (4 608) and from 945 to 450 us (50 400).  With the increments exchanged after every step (one wavefront a
 // workgroup, each cell waiting for its neighbours' versions) it took 250 us on 1 296 and 274 us on 4 608 tetrahedra;
-// half as many blocks cost up to a third more where the cells are many (4 608: 208 us), since the wavefronts of a
+// half as many blocks cost up to a third more where the cells are many (4 608), since the wavefronts of a
 // colour then share a SIMD, and nothing where they are few.
 //
 // Exchange: the six doubles of an increment travel as twelve 64-bit words, each holding 32 bits of payload and
@@ -53,24 +53,18 @@ template <int NF, int Q> __device__ inline double slot_value(double x) {
   if constexpr (Q < 4) return dpp_move<Q * 0x55>(x);
   else return dpp_move<0x141>(dpp_move<(Q - 4) * 0x55>(x));
 }
-// acc + x_0 + x_1 .., acc - x_0 - x_1 .. and acc + x_0 y_0 + x_1 y_1 .. (fused) over the slots, in slot order
-template <int NF, int Q = 0> __device__ inline void slot_sum(double& acc, double x) {
-  if constexpr (Q < NF) {
-    acc += slot_value<NF, Q>(x);
-    slot_sum<NF, Q + 1>(acc, x);
-  }
-}
+// acc + x_0 y_0 + x_1 y_1 .. (fused) over the slots, in slot order
 template <int NF, int Q = 0> __device__ inline void slot_fma(double& acc, double x, double y) {
   if constexpr (Q < NF) {
     acc = __builtin_fma(slot_value<NF, Q>(x), slot_value<NF, Q>(y), acc);
     slot_fma<NF, Q + 1>(acc, x, y);
   }
 }
-template <int NF, int Q = 0> __device__ inline void slot_subtract(double& acc, double x) {
-  if constexpr (Q < NF) {
-    acc -= slot_value<NF, Q>(x);
-    slot_subtract<NF, Q + 1>(acc, x);
-  }
+// x of a cell's first quad in all of its lanes
+template <int NF> __device__ inline double of_first_quad(double x, int a) {
+  if constexpr (SlotLanes<NF>::n == 4) return x;
+  const double y = dpp_move<0x141>(x);
+  return a < 4 ? x : y;
 }
 
 // The macro system's arithmetic with its roundings spelled out (no implicit fusing): the same bits as the
@@ -184,24 +178,52 @@ template <int NF> struct SlotLane {
   }
 };
 
-// Lane a of a cell's first quad stores doubles a and a + 4 of the cell's six
-template <class Put> __device__ inline void spread(int a, const double* x, Put&& put) {
-  double y[6];
-#pragma unroll
-  for (int q = 0; q < 6; ++q) {
-    y[q] = x[q];
-    asm("" : "+v"(y[q]));  // in registers: the selects below would otherwise become an indexed load from scratch
+// A cell's six components over its lanes: lane a of four keeps components a and a + 4, lane a of eight component a
+// (a < 6).  The lanes compute all six terms of one face each and swap them through LDS: 14 LDS accesses and one or two
+// sums a lane, where every lane adding all six out of the others' registers took 72 to 120 instructions (the stage on 1 296
+// tetrahedra 152 -> 135 us, on 3 072 cells of 6 slots 282 -> 240 us).
+template <int NF> struct Comps {
+  static constexpr int n = NF <= 4 ? 2 : 1;
+  double v[n];
+  // put(component, value) for the lane's components
+  template <class Put> __device__ void each(int a, Put&& put) const {
+    if (n == 1 && a >= 6) return;
+    put(a, v[0]);
+    if (n == 2 && a < 2) put(a + 4, v[n - 1]);
   }
-  if (a >= 4) return;
-  put(a, a == 0 ? y[0] : a == 1 ? y[1] : a == 2 ? y[2] : y[3]);
-  if (a < 2) put(a + 4, a == 0 ? y[4] : y[5]);
+  __device__ void select(int a, const double* x) {
+    double y[6];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      y[q] = x[q];
+      asm("" : "+v"(y[q]));  // in registers: the selects below would otherwise become an indexed load from scratch
+    }
+    v[0] = a == 0 ? y[0] : a == 1 ? y[1] : a == 2 ? y[2] : a == 3 ? y[3] : a == 4 ? y[4] : y[5];
+    if (n == 2) v[n - 1] = a == 0 ? y[4] : y[5];
+  }
+};
+constexpr int kSwapRow = 65;  // doubles per component of a wavefront's swap space (64 lanes; 65: no bank conflicts)
+// v -= the terms of the cell's slots, in slot order
+template <int NF> __device__ inline void subtract_terms(Comps<NF>& v, const double* term, int a, double* swap) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int q = 0; q < 6; ++q) swap[q * kSwapRow + lane] = term[q];
+  asm volatile("" ::: "memory");  // a wavefront's LDS accesses keep their order
+  const double* from = swap + (NF > 4 && a >= 6 ? 0 : a) * kSwapRow + (lane - a);
+#pragma unroll
+  for (int q = 0; q < NF; ++q) v.v[0] -= from[q];
+  if constexpr (Comps<NF>::n == 2) {
+    const double* high = swap + (a < 2 ? a + 4 : 4) * kSwapRow + (lane - a);
+#pragma unroll
+    for (int q = 0; q < NF; ++q) v.v[1] -= high[q];
+  }
+  asm volatile("" ::: "memory");
 }
 
-// The sweeps in one workgroup.  inc: the cells' increments in LDS, [nc][6].  relax(xj, x): one relaxation from the
-// neighbour's increment xj to the cell's x.
+// The sweeps in one workgroup.  inc: the cells' increments in LDS, [nc][6], at the end those of the last sweep.
+// relax(xj, x): one relaxation from the neighbour's increment xj to the lane's components x of the cell's.
 template <int NF, class Relax>
-__device__ inline void sweeps_in_lds(const SlotLane<NF>& L, int64_t nc, int m, int steps, double* inc, double* x,
-                                     Relax&& relax) {
+__device__ inline void sweeps_in_lds(const SlotLane<NF>& L, int64_t nc, int m, int steps, double* inc, Relax&& relax) {
   for (int64_t k = threadIdx.x; k < 6 * nc; k += blockDim.x) inc[k] = 0.0;
   __syncthreads();
   int c = 0, up = 1;
@@ -210,8 +232,9 @@ __device__ inline void sweeps_in_lds(const SlotLane<NF>& L, int64_t nc, int m, i
       double xj[6];
 #pragma unroll
       for (int q = 0; q < 6; ++q) xj[q] = L.vn >= 0 ? inc[6 * L.vn + q] : 0.0;
+      Comps<NF> x;
       relax(xj, x);
-      if (L.valid) spread(L.a, x, [&](int q, double v) { inc[6 * L.vi + q] = v; });
+      if (L.valid) x.each(L.a, [&](int q, double v) { inc[6 * L.vi + q] = v; });
     }
     __syncthreads();
     if (m > 1) {
@@ -233,7 +256,7 @@ __host__ __device__ inline void next_color(int& c, int& up, int m) {
 // LDS of a workgroup of the sweeps in blocks: more than half a compute unit's, so that no two share one (the waits of
 // one would keep the other's older wavefronts from issuing).
 constexpr int kBlockLds = 96 * 1024;
-static_assert(6 * sizeof(double) * kBlockVals <= kBlockLds, "increments of a block");
+
 
 // The sweeps in blocks (BlockPlan).  Within a window of h steps: LDS and a barrier a step, as in one workgroup.
 // After it a workgroup has published its increments of the window's colours, tagged with the window, and waits for
@@ -245,8 +268,7 @@ static_assert(6 * sizeof(double) * kBlockVals <= kBlockLds, "increments of a blo
 // false: a wait ran out.
 template <int NF, int Waves, class Relax>
 __device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord& r, int64_t nc, int m,
-                                        int steps, int h, uint64_t* words, uint32_t tag0, double* inc, double* x,
-                                        Relax&& relax) {
+                                        int steps, int h, uint64_t* words, uint32_t tag0, double* inc, Relax&& relax) {
   constexpr int NT = 64 * Waves, K = 12 * kBlockReads / NT;
   static_assert(12 * kBlockReads % NT == 0 && kBlockMax <= NT, "polls of a thread");
   __shared__ int stuck;
@@ -287,10 +309,11 @@ __device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord
         double xj[6];
 #pragma unroll
         for (int q = 0; q < 6; ++q) xj[q] = L.vn >= 0 ? inc[6 * L.vn + q] : 0.0;
+        Comps<NF> x;
         relax(xj, x);
-        if (L.valid) spread(L.a, x, [&](int q, double v) { inc[6 * L.vi + q] = v; });
+        if (L.valid) x.each(L.a, [&](int q, double v) { inc[6 * L.vi + q] = v; });
         if (more && s == last && L.own)
-          spread(L.a, x, [&](int q, double v) {
+          x.each(L.a, [&](int q, double v) {
             const uint64_t t = (uint64_t)tag << 32, u = __builtin_bit_cast(uint64_t, v);
             uint64_t* to = buf + kSweepWords * L.i + 2 * q;
             __hip_atomic_store(to, t | (uint32_t)u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -341,16 +364,23 @@ template <int NF, Form F> __device__ inline SlotLane<NF> lane_of(const Dev& d, c
   else L.find(d, bp.rec[blockIdx.x]);
   return L;
 }
+// LDS: the increments, then the swap space of every wavefront.
+__host__ __device__ constexpr int64_t increments_of(Form f, int64_t nc) { return 6 * (f == kLocal ? nc : kBlockVals); }
+template <Form F> __device__ inline double* swap_space(double* lds, int64_t nc) {
+  return lds + increments_of(F, nc) + 6 * kSwapRow * __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+// x: the cell's increments after the sweeps
 template <Form F, int NF, class Relax>
 __device__ inline bool sweeps(const SlotLane<NF>& L, const SweepPlan& pl, const BlockPlan& bp, int64_t nc, int steps,
-                              uint64_t* words, uint64_t* lds, uint32_t tag0, double* x, Relax&& relax) {
-  if constexpr (F == kLocal) {
-    sweeps_in_lds<NF>(L, nc, pl.m, steps, reinterpret_cast<double*>(lds), x, relax);
-    return true;
-  } else {
-    return sweeps_in_blocks<NF, threads_of(F) / 64>(L, bp.rec[blockIdx.x], nc, pl.m, steps, bp.h, words, tag0,
-                                                    reinterpret_cast<double*>(lds), x, relax);
-  }
+                              uint64_t* words, double* inc, uint32_t tag0, double* x, Relax&& relax) {
+  if constexpr (F == kLocal)
+    sweeps_in_lds<NF>(L, nc, pl.m, steps, inc, relax);
+  else if (!sweeps_in_blocks<NF, threads_of(F) / 64>(L, bp.rec[blockIdx.x], nc, pl.m, steps, bp.h, words, tag0, inc,
+                                                     relax))
+    return false;
+  if (L.valid)
+    for (int q = 0; q < 6; ++q) x[q] = inc[6 * L.vi + q];
+  return true;
 }
 
 // Step 4 (Eqs. 38-43): macro flux per cell (Eq. 37), spectral radii r_ij (Eq. 41), diagonal and right-hand side
@@ -359,7 +389,7 @@ __device__ inline bool sweeps(const SlotLane<NF>& L, const SweepPlan& pl, const 
 template <int NF, Form F>
 CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Work w, SweepPlan pl, BlockPlan bp,
                                   uint64_t* words, uint32_t tag0, int steps) {
-  extern __shared__ __align__(16) uint64_t lds_words[];
+  extern __shared__ __align__(16) double sweep_lds[];
   const SlotLane<NF> L = lane_of<NF, F>(d, pl, bp);
   const int64_t i = L.i;
   const GasC& g = d.gas;
@@ -393,6 +423,7 @@ CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Wo
   slot_fma<NF>(D, hav, r);
   const double inv_dt = inv_dt_cell(d, geo[2]);
   D += inv_dt;
+  D = of_first_quad<NF>(D, L.a);
   const double iD = 1.0 / D, D5 = D + 1.0 / (g.Z * tau);
 #pragma unroll
   for (int m = 0; m < 6; ++m) {
@@ -409,7 +440,12 @@ CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Wo
                       &gas.T_ref, &gas.C_s})
       asm("" : "+v"(*c));
   double dW[6] = {0, 0, 0, 0, 0, 0};
-  auto relax = [&](const double* dWj, double* x) {
+  Comps<NF> mine;
+#pragma unroll
+  for (int m = 0; m < 6; ++m) res[m] = of_first_quad<NF>(res[m], L.a);
+  mine.select(L.a, res);
+  double* const swap = swap_space<F>(sweep_lds, d.nc);
+  auto relax = [&](const double* dWj, Comps<NF>& x) {
     double term[6] = {0, 0, 0, 0, 0, 0};
     if (L.nb >= 0) {
       double Wp[6], dG[6];
@@ -419,14 +455,14 @@ CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Wo
 #pragma unroll
       for (int m = 0; m < 6; ++m) term[m] = hav * fma_(-r, dWj[m], dG[m]);
     }
-#pragma unroll
-    for (int m = 0; m < 6; ++m) {
-      double acc = res[m];
-      slot_subtract<NF>(acc, term[m]);
-      x[m] = m == 5 ? acc / D5 : acc * iD;
-    }
+    x = mine;
+    subtract_terms<NF>(x, term, L.a, swap);
+    constexpr int top = Comps<NF>::n - 1;
+    const double quotient = x.v[top] / D5;
+    if (top == 1) x.v[0] *= iD;
+    x.v[top] = L.a == (top == 1 ? 1 : 5) ? quotient : x.v[top] * iD;
   };
-  if (!sweeps<F>(L, pl, bp, d.nc, steps, words, lds_words, tag0, dW, relax)) {
+  if (!sweeps<F>(L, pl, bp, d.nc, steps, words, sweep_lds, tag0, dW, relax)) {
     atomicOr(&w.flag[0], kSweepStuck);
     return;
   }
@@ -454,7 +490,7 @@ CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Wo
 template <int NF, Form F>
 CIS_SWEEP_KERNEL void k_adj_macro_sweeps(Dev d, const double* W, const double* t, double* u, int32_t* flag, SweepPlan pl,
                                       BlockPlan bp, uint64_t* words, uint32_t tag0, int steps) {
-  extern __shared__ __align__(16) uint64_t lds_words[];
+  extern __shared__ __align__(16) double sweep_lds[];
   const SlotLane<NF> L = lane_of<NF, F>(d, pl, bp);
   const int64_t i = L.i;
   const GasC& g = d.gas;
@@ -481,26 +517,28 @@ CIS_SWEEP_KERNEL void k_adj_macro_sweeps(Dev d, const double* W, const double* t
   const double tau = macro_tau(pa, g);
   double D = 0.0;
   slot_fma<NF>(D, hav, r);
+  D = of_first_quad<NF>(D, L.a);
   const double iD = 1.0 / D, iD5 = 1.0 / (D + 1.0 / (g.Z * tau));
   double ti[6], x[6] = {0, 0, 0, 0, 0, 0};
 #pragma unroll
   for (int m = 0; m < 6; ++m) ti[m] = t[6 * i + m];
-  auto relax = [&](const double* uj, double* ui) {
+  Comps<NF> mine, scale;
+  mine.select(L.a, ti);
+  for (int k = 0; k < Comps<NF>::n; ++k) scale.v[k] = k == Comps<NF>::n - 1 && L.a == (k == 1 ? 1 : 5) ? iD5 : iD;
+  double* const swap = swap_space<F>(sweep_lds, d.nc);
+  auto relax = [&](const double* uj, Comps<NF>& ui) {
     double term[6] = {0, 0, 0, 0, 0, 0};
     if (L.nb >= 0) {
       double gj[6];
       euler_flux_vjp(Wi, nx, ny, nz, uj, gj);
 #pragma unroll
-      for (int m = 0; m < 6; ++m) term[m] = half_av * (gj[m] + r * uj[m]);
+      for (int m = 0; m < 6; ++m) term[m] = -(half_av * (gj[m] + r * uj[m]));
     }
-#pragma unroll
-    for (int m = 0; m < 6; ++m) {
-      double acc = ti[m];
-      slot_sum<NF>(acc, term[m]);
-      ui[m] = acc * (m == 5 ? iD5 : iD);
-    }
+    ui = mine;
+    subtract_terms<NF>(ui, term, L.a, swap);
+    for (int k = 0; k < Comps<NF>::n; ++k) ui.v[k] *= scale.v[k];
   };
-  if (!sweeps<F>(L, pl, bp, d.nc, steps, words, lds_words, tag0, x, relax)) {
+  if (!sweeps<F>(L, pl, bp, d.nc, steps, words, sweep_lds, tag0, x, relax)) {
     atomicOr(flag, kSweepStuck);
     return;
   }
@@ -659,10 +697,12 @@ template <Form F> const void* kernel_of(bool adjoint, const Dev& d) {
   return d.mf == 4 ? kernel_of<4, F>(adjoint) : kernel_of<kMaxFaces, F>(adjoint);
 }
 
+static_assert(sizeof(double) * (6 * kBlockVals + 6 * kSwapRow * kWideBlockWaves) <= kBlockLds, "LDS of a block");
+
 hipError_t run(const Dev& d, bool adjoint, const MacroSweeps& s, void** args, hipStream_t st) {
   if (s.plan.local)
     return hipLaunchKernel(kernel_of<kLocal>(adjoint, d), dim3(1), dim3(kLocalThreads), args,
-                           6 * sizeof(double) * (size_t)d.nc, st);
+                           sizeof(double) * (size_t)(increments_of(kLocal, d.nc) + 6 * kSwapRow * kLocalThreads / 64), st);
   const void* k = s.block.wide ? kernel_of<kWideBlocks>(adjoint, d) : kernel_of<kBlocks>(adjoint, d);
   return hipLaunchCooperativeKernel(k, dim3((unsigned)s.block.blocks),
                                     dim3(threads_of(s.block.wide ? kWideBlocks : kBlocks)), args, (unsigned)kBlockLds, st);
