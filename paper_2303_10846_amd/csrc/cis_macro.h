@@ -15,7 +15,7 @@ constexpr int kSweepColors = 16;  // most non-empty colours
 // wavefronts wave0[k] .. wave0[k + 1] - 1 (64 / lanes-per-cell cells each).
 struct SweepPlan {
   int m = 0;           // non-empty colours; 0: the mesh keeps a launch per colour
-  bool local = false;  // the whole mesh in one workgroup of kLocalThreads threads; else in blocks
+  bool local = false;  // the whole mesh in one workgroup of up to kLocalThreads threads; else in blocks
   int32_t off[kSweepColors], n[kSweepColors], wave0[kSweepColors + 1];
 };
 constexpr int kLocalThreads = 1024;

@@ -353,7 +353,7 @@ __device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord
   return true;
 }
 
-// The forms of both kernels: the whole mesh in one workgroup of kLocalThreads threads, or blocks of 8 or 16 wavefronts.
+// The forms of both kernels: the whole mesh in one workgroup of up to kLocalThreads threads, or blocks of 8 or 16 wavefronts.
 enum Form { kLocal, kBlocks, kWideBlocks };
 constexpr int threads_of(Form f) { return f == kLocal ? kLocalThreads : 64 * (f == kBlocks ? kBlockWaves : kWideBlockWaves); }
 #define CIS_SWEEP_KERNEL __global__ __launch_bounds__(threads_of(F)) \
@@ -700,9 +700,10 @@ template <Form F> const void* kernel_of(bool adjoint, const Dev& d) {
 static_assert(sizeof(double) * (6 * kBlockVals + 6 * kSwapRow * kWideBlockWaves) <= kBlockLds, "LDS of a block");
 
 hipError_t run(const Dev& d, bool adjoint, const MacroSweeps& s, void** args, hipStream_t st) {
+  // as many wavefronts as own cells: idle ones cost every barrier (a pass of 48 tetrahedra 166.6 -> 162.6 us)
   if (s.plan.local)
-    return hipLaunchKernel(kernel_of<kLocal>(adjoint, d), dim3(1), dim3(kLocalThreads), args,
-                           sizeof(double) * (size_t)(increments_of(kLocal, d.nc) + 6 * kSwapRow * kLocalThreads / 64), st);
+    return hipLaunchKernel(kernel_of<kLocal>(adjoint, d), dim3(1), dim3(64u * (unsigned)s.plan.wave0[s.plan.m]), args,
+                           sizeof(double) * (size_t)(increments_of(kLocal, d.nc) + 6 * kSwapRow * s.plan.wave0[s.plan.m]), st);
   const void* k = s.block.wide ? kernel_of<kWideBlocks>(adjoint, d) : kernel_of<kBlocks>(adjoint, d);
   return hipLaunchCooperativeKernel(k, dim3((unsigned)s.block.blocks),
                                     dim3(threads_of(s.block.wide ? kWideBlocks : kBlocks)), args, (unsigned)kBlockLds, st);
