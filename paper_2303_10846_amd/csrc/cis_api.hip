@@ -179,7 +179,10 @@ struct cis_state {
   Bufs buf{};
   Work work{};
   MacroSweeps sweeps{};
-  double* krylov = nullptr;  // Gram-Schmidt coefficients and norm of the adjoint's Krylov step
+  // Gram-Schmidt coefficients and norm of the adjoint's Krylov step; their pinned copy, and the event after it (made by
+  // the first adjoint solve)
+  double *krylov = nullptr, *krylov_host = nullptr;
+  hipEvent_t krylov_copied = nullptr;
   // library-owned device arrays
   // boundary faces grouped by bc slot, in face order, then their cells (each once): host offsets into d_bnd
   struct BndGroup {
@@ -202,6 +205,8 @@ struct cis_state {
   ~cis_state() {
     for (void* p : owned)
       if (p) (void)hipFree(p);
+    if (krylov_host) (void)hipHostFree(krylov_host);
+    if (krylov_copied) (void)hipEventDestroy(krylov_copied);
   }
 };
 
@@ -1524,6 +1529,10 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
     else
       launch_adj_sweeps(s->dev, s->buf, in, out, s->mesh->color_off.data(), s->mesh->n_colors, precond_pairs, q);
   };
+  if (!s->krylov_host && hipHostMalloc((void**)&s->krylov_host, (2 * kMaxRestart + 3) * sizeof(double)) != hipSuccess)
+    return fail(CIS_E_DEVICE, "pinned allocation failed");
+  if (!s->krylov_copied) HIP_TRY(hipEventCreateWithFlags(&s->krylov_copied, hipEventDisableTiming));
+  const double* const h2 = s->krylov_host;
   hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, q, s->work.flag, (int64_t)4);
   // right-hand side and the explicit parameter dependence of J
   double gpJ[3], gpL[3] = {0.0, 0.0, 0.0};
@@ -1537,17 +1546,18 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
   int32_t iters = 0;
   double beta = bnorm;
   launch_axpby(N, 1.0, b, 0.0, V, q);  // r = b - A*0
-  std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), gv(m + 1), y(m), h(m + 1), h2(2 * m + 3);
+  std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), gv(m + 1), y(m), h(m + 1);
   bool done = bnorm == 0.0;
   while (!done && iters < max_iter) {
     launch_axpby(N, 1.0 / beta, V, 0.0, V, q);
     std::fill(gv.begin(), gv.end(), 0.0);
     gv[0] = beta;
     int jend = 0;
+    bool ahead = false;  // z already holds the preconditioned vector of the step
     for (int j = 0; j < m && iters < max_iter; ++j) {
       double* vj = V + (int64_t)j * N;
       double* w = V + (int64_t)(j + 1) * N;
-      precond(vj, z);
+      if (!ahead) precond(vj, z);
       run_vjp(s, z, 0.0, sl, w);
       // classical Gram-Schmidt, twice, and the norm; the coefficients stay on the device until the step's end (a copy
       // and a wait for each of the three left the device idle for 40 us at a time)
@@ -1558,8 +1568,13 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
       launch_gemv_sub(V, N, j + 1, hd + (j + 1), w, q);
       launch_dots(w, N, 1, w, part, hd + 2 * (j + 1), q);
       launch_normalize(N, hd + 2 * (j + 1), w, q);
-      HIP_TRY(hipMemcpyAsync(h2.data(), hd, (2 * j + 3) * sizeof(double), hipMemcpyDeviceToHost, q));
-      HIP_TRY(hipStreamSynchronize(q));
+      HIP_TRY(hipMemcpyAsync(s->krylov_host, hd, (2 * j + 3) * sizeof(double), hipMemcpyDeviceToHost, q));
+      HIP_TRY(hipEventRecord(s->krylov_copied, q));
+      // the next step's preconditioner runs while the host looks at this one (384 cells x 1288: 34 us a step; at
+      // convergence one application is for nothing)
+      ahead = j + 1 < m && iters + 1 < max_iter;
+      if (ahead) precond(w, z);
+      HIP_TRY(hipEventSynchronize(s->krylov_copied));
       for (int i = 0; i <= j; ++i) h[i] = h2[i] + h2[j + 1 + i];
       const double hn = std::sqrt(h2[2 * (j + 1)]);
       // Givens rotations on column j
