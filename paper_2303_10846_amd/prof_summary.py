@@ -38,7 +38,7 @@ def _find(d: str, suffix: str) -> str:
 
 
 def short_name(k: str) -> str:
-    k = k.split("(")[0]
+    k = k.replace("(anonymous namespace)::", "").split("(")[0]
     return k.replace("void ", "").strip()
 
 
