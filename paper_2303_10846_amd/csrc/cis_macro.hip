@@ -10,13 +10,13 @@
 // instead of after each (a word's way from a store to a load on another XCD takes 0.5 us, a whole exchange 1.5).
 //
 // Measured: a step costs 0.47 us in one workgroup (48 tetrahedra), most of it the relaxation's chain of FP64
-// instructions; in blocks 0.85 us with windows of 4 steps (1 296 and 4 608 tetrahedra), 1.0 with windows of 3 (3 072 cells
-// of 6 slots) and 2.8 with an exchange every step (50 400 tetrahedra, 197 a block).  Against the launch per colour and its
-// separate preparation the stage went from 400-450 to 76 us (48 tetrahedra), from 530-640 to 135 us (1 296), from 560-680
-// to 145 us (4 608) and from 945 to 450 us (50 400).  With the increments exchanged after every step (one wavefront a
-// workgroup, each cell waiting for its neighbours' versions) it took 250 us on 1 296 and 274 us on 4 608 tetrahedra;
-// half as many blocks cost up to a third more where the cells are many (4 608), since the wavefronts of a
-// colour then share a SIMD, and nothing where they are few.
+// instructions; in blocks 0.85 us with windows of 4 steps (1 296 and 4 608 tetrahedra), 1.0 with windows of 3
+// (3 072 cells of 6 slots) and 2.8 with an exchange every step (50 400 tetrahedra, 197 a block).  Against the
+// launch per colour and its separate preparation the stage went from 400-450 to 76 us (48 tetrahedra), from
+// 530-640 to 135 us (1 296), from 560-680 to 145 us (4 608) and from 945 to 450 us (50 400).  With the increments
+// exchanged after every step (one wavefront a workgroup, each cell waiting for its neighbours' versions) it took
+// 250 us on 1 296 and 274 us on 4 608 tetrahedra; half as many blocks cost up to a third more where the cells are
+// many (4 608), since the wavefronts of a colour then share a SIMD, and nothing where they are few.
 //
 // Exchange: the six doubles of an increment travel as twelve 64-bit words, each holding 32 bits of payload and
 // the 32-bit tag of its window, written and read with relaxed 64-bit atomics of agent scope (one word is always
@@ -180,8 +180,8 @@ template <int NF> struct SlotLane {
 
 // A cell's six components over its lanes: lane a of four keeps components a and a + 4, lane a of eight component a
 // (a < 6).  The lanes compute all six terms of one face each and swap them through LDS: 14 LDS accesses and one or two
-// sums a lane, where every lane adding all six out of the others' registers took 72 to 120 instructions (the stage on 1 296
-// tetrahedra 152 -> 135 us, on 3 072 cells of 6 slots 282 -> 240 us).
+// sums a lane, where every lane adding all six out of the others' registers took 72 to 120 instructions (the stage
+// on 1 296 tetrahedra 152 -> 135 us, on 3 072 cells of 6 slots 282 -> 240 us).
 template <int NF> struct Comps {
   static constexpr int n = NF <= 4 ? 2 : 1;
   double v[n];
@@ -220,6 +220,14 @@ template <int NF> __device__ inline void subtract_terms(Comps<NF>& v, const doub
   asm volatile("" ::: "memory");
 }
 
+// The position after colour c of the sequence 0, 1, .., m-1, m-2, .., 0, 1, ..
+__host__ __device__ inline void next_color(int& c, int& up, int m) {
+  if (m < 2) return;
+  if (c == m - 1) up = -1;
+  if (c == 0) up = 1;
+  c += up;
+}
+
 // The sweeps in one workgroup.  inc: the cells' increments in LDS, [nc][6], at the end those of the last sweep.
 // relax(xj, x): one relaxation from the neighbour's increment xj to the lane's components x of the cell's.
 template <int NF, class Relax>
@@ -237,20 +245,8 @@ __device__ inline void sweeps_in_lds(const SlotLane<NF>& L, int64_t nc, int m, i
       if (L.valid) x.each(L.a, [&](int q, double v) { inc[6 * L.vi + q] = v; });
     }
     __syncthreads();
-    if (m > 1) {
-      if (c == m - 1) up = -1;
-      if (c == 0) up = 1;
-      c += up;
-    }
+    next_color(c, up, m);
   }
-}
-
-// The position after colour c of the sequence 0, 1, .., m-1, m-2, .., 0, 1, ..
-__host__ __device__ inline void next_color(int& c, int& up, int m) {
-  if (m < 2) return;
-  if (c == m - 1) up = -1;
-  if (c == 0) up = 1;
-  c += up;
 }
 
 // LDS of a workgroup of the sweeps in blocks: more than half a compute unit's, so that no two share one (the waits of
@@ -297,7 +293,8 @@ __device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord
     uint64_t* const buf = words + (window & 1u) * (uint64_t)(kSweepWords * nc);
     uint64_t* const in = entered + (window & 1u) * (uint64_t)(8 * kBlockMax);
     const uint32_t tag = tag0 + 1u + window;
-    if (tid == NT - 1) __hip_atomic_store(in + 8 * blockIdx.x, (uint64_t)tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == NT - 1)
+      __hip_atomic_store(in + 8 * blockIdx.x, (uint64_t)tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int last = -1;  // last step of the window that relaxes this wavefront's colour
     uint32_t relaxed = 0;
     for (int s = 0, cc = c, uu = up; s < n; ++s, next_color(cc, uu, m)) {
@@ -353,9 +350,12 @@ __device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord
   return true;
 }
 
-// The forms of both kernels: the whole mesh in one workgroup of up to kLocalThreads threads, or blocks of 8 or 16 wavefronts.
+// The forms of both kernels: the whole mesh in one workgroup of up to kLocalThreads threads, or blocks of 8 or 16
+// wavefronts.
 enum Form { kLocal, kBlocks, kWideBlocks };
-constexpr int threads_of(Form f) { return f == kLocal ? kLocalThreads : 64 * (f == kBlocks ? kBlockWaves : kWideBlockWaves); }
+constexpr int threads_of(Form f) {
+  return f == kLocal ? kLocalThreads : 64 * (f == kBlocks ? kBlockWaves : kWideBlockWaves);
+}
 #define CIS_SWEEP_KERNEL __global__ __launch_bounds__(threads_of(F)) \
     __attribute__((amdgpu_waves_per_eu(threads_of(F) / 256, threads_of(F) / 256)))
 template <int NF, Form F> __device__ inline SlotLane<NF> lane_of(const Dev& d, const SweepPlan& pl, const BlockPlan& bp) {
@@ -701,9 +701,11 @@ static_assert(sizeof(double) * (6 * kBlockVals + 6 * kSwapRow * kWideBlockWaves)
 
 hipError_t run(const Dev& d, bool adjoint, const MacroSweeps& s, void** args, hipStream_t st) {
   // as many wavefronts as own cells: idle ones cost every barrier (a pass of 48 tetrahedra 166.6 -> 162.6 us)
-  if (s.plan.local)
-    return hipLaunchKernel(kernel_of<kLocal>(adjoint, d), dim3(1), dim3(64u * (unsigned)s.plan.wave0[s.plan.m]), args,
-                           sizeof(double) * (size_t)(increments_of(kLocal, d.nc) + 6 * kSwapRow * s.plan.wave0[s.plan.m]), st);
+  if (s.plan.local) {
+    const int waves = s.plan.wave0[s.plan.m];
+    return hipLaunchKernel(kernel_of<kLocal>(adjoint, d), dim3(1), dim3(64u * (unsigned)waves), args,
+                           sizeof(double) * (size_t)(increments_of(kLocal, d.nc) + 6 * kSwapRow * waves), st);
+  }
   const void* k = s.block.wide ? kernel_of<kWideBlocks>(adjoint, d) : kernel_of<kBlocks>(adjoint, d);
   return hipLaunchCooperativeKernel(k, dim3((unsigned)s.block.blocks),
                                     dim3(threads_of(s.block.wide ? kWideBlocks : kBlocks)), args, (unsigned)kBlockLds, st);
@@ -748,7 +750,7 @@ int block_count(const SweepPlan& pl, const Dev& d, int64_t nc) {
   return (int)std::min<int64_t>(std::min(cus, kBlockMax), nc);
 }
 
-// Windows tried, the longest first (the fewest exchanges; measured on 1 296 tetrahedra: 144 us with 4 steps, 192 with 2):
+// Windows tried, the longest first (the fewest exchanges; on 1 296 tetrahedra 144 us with 4 steps, 192 with 2):
 // a period and its divisors (and two periods of two colours, whose cells all
 // depend on each other only through the other colour).
 static BlockCands block_windows(int m) {
@@ -770,8 +772,8 @@ void block_probe(const Dev& d, int blocks, const MacroSweeps& f, int32_t* most, 
 
 bool block_plan(const Dev& d, int blocks, MacroSweeps& f, const int32_t* most, hipStream_t st) {
   BlockCands c = block_windows(f.plan.m);
-  // 8 wavefronts where a window fits them, two a SIMD; 16 only where none does (a longer window with 16 gains nothing: the
-  // wavefronts of a colour share a SIMD)
+  // 8 wavefronts where a window fits them, two a SIMD; 16 only where none does (a longer window with 16 gains
+  // nothing: the wavefronts of a colour share a SIMD)
   int k = 0;
   while (k < c.n && most[k] > kBlockWaves) ++k;
   f.block.wide = k == c.n;
