@@ -29,7 +29,7 @@ EXPORTS = [
     "cis_wall_heat_flux", "cis_debug_stage", "cis_profile_enable", "cis_profile_read", "cis_state_set_bc",
     "cis_steady_residual", "cis_residual_vjp", "cis_adjoint_required_bytes", "cis_adjoint_solve", "cis_wall_loads",
     "cis_wall_coefficients_of_loads", "cis_wall_coefficients", "cis_iterate_noalloc", "cis_limiter_freeze",
-    "cis_mesh_create_cells",
+    "cis_mesh_create_cells", "cis_debug_sweeps",
 ]
 STAGE_NAMES = ["recon", "face", "macro", "residual", "micro", "update"]
 
@@ -161,6 +161,8 @@ def load(allow_build: bool = True):
     lib.cis_wall_heat_flux.argtypes = [P, C.c_int32, d]
     lib.cis_debug_stage.restype = st
     lib.cis_debug_stage.argtypes = [P, C.c_int32, d]
+    lib.cis_debug_sweeps.restype = st
+    lib.cis_debug_sweeps.argtypes = [P, C.c_int64, C.c_int64, i32]
     lib.cis_profile_enable.restype = st
     lib.cis_profile_enable.argtypes = [P, C.c_int32]
     lib.cis_profile_read.restype = st
@@ -475,6 +477,14 @@ class Solver:
         out = np.empty(self.nc if name == "tau_t" else (self.nc, 6))
         _check(self.lib.cis_debug_stage(self.h, which, _dp(out)))
         return out
+
+    def debug_sweeps(self, polls: int = -1, first: int = 0) -> dict:
+        """The form of the macro sweeps (cis_debug_sweeps); polls >= 0 sets the limit of their waits from the
+        first-th launch on."""
+        info = (C.c_int32 * 4)()
+        _check(self.lib.cis_debug_sweeps(self.h, int(polls), int(first), info))
+        return dict(form=("colours", "workgroup", "blocks", "wide blocks")[info[0]], window=info[1], blocks=info[2],
+                    redone=info[3])
 
     # -- steady residual, VJP and adjoint (FP64) ------------------------------
     def set_bc(self, bcs):

@@ -882,8 +882,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_ysub(int64_t nc, int64_t off, co
 }  // namespace
 
 void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, double* out, double* tmp, double* cell,
-                              const int64_t* color_off, int64_t n_colors, int micro_pairs, int macro_pairs, MacroSweeps& sweeps,
-                              int32_t* flag, hipStream_t st) {
+                              const int64_t* color_off, int64_t n_colors, int micro_pairs, int macro_pairs,
+                              MacroSweeps* sweeps, int32_t* flag, hipStream_t st) {
   const int64_t nc = d.nc, P = d.nc * d.nv;
   double* gW = cell;
   double* gq = gW + 6 * nc;
@@ -902,7 +902,8 @@ void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, dou
   if (macro_pairs > 0) {
     // t = B^T z (W part), then Mac^T u = t and x_phi = z + M_c^T u
     hipLaunchKernelGGL((k_cell_vjp<true, true>), dim3((unsigned)nc), dim3(kBlock), 0, st, d, b, a);
-    if (sweeps.plan.m == 0 || launch_adj_macro_sweeps(d, b, sweeps, gW, u, macro_pairs, flag, st) != hipSuccess) {
+    if (!sweeps || sweeps->plan.m == 0 ||
+        launch_adj_macro_sweeps(d, b, *sweeps, gW, u, macro_pairs, flag, st) != hipSuccess) {
       (void)hipGetLastError();
       if (d.mf == 4)
         hipLaunchKernelGGL(k_adj_macro_prep<4>, dim3(ncb), dim3(kBlock), 0, st, d, b, rc, mD);
@@ -969,9 +970,10 @@ __global__ __launch_bounds__(kBlock) void k_axpby(int64_t n, double a, const dou
     y[i] = (c == 0.0 ? 0.0 : c * y[i]) + (a == 0.0 ? 0.0 : a * x[i]);
 }
 
-// w /= sqrt(*n2), left as it is where that is not positive
-__global__ __launch_bounds__(kBlock) void k_normalize(int64_t n, const double* n2, double* w) {
-  const double norm = sqrt(*n2);
+// w /= sqrt(n2[0]), left as it is where that is not positive; n2[1] = the macro sweeps' wait ran out
+__global__ __launch_bounds__(kBlock) void k_normalize(int64_t n, double* n2, const int32_t* flag, double* w) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) n2[1] = flag[0] & kSweepStuck ? 1.0 : 0.0;
+  const double norm = sqrt(n2[0]);
   if (!(norm > 0.0)) return;
   const double a = 1.0 / norm;
   for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) w[i] = a * w[i];
@@ -993,8 +995,8 @@ void launch_axpby(int64_t n, double a, const double* x, double c, double* y, hip
   hipLaunchKernelGGL(k_axpby, dim3(grid_for(n)), dim3(kBlock), 0, st, n, a, x, c, y);
 }
 
-void launch_normalize(int64_t n, const double* n2, double* w, hipStream_t st) {
-  hipLaunchKernelGGL(k_normalize, dim3(grid_for(n)), dim3(kBlock), 0, st, n, n2, w);
+void launch_normalize(int64_t n, double* n2, const int32_t* flag, double* w, hipStream_t st) {
+  hipLaunchKernelGGL(k_normalize, dim3(grid_for(n)), dim3(kBlock), 0, st, n, n2, flag, w);
 }
 
 int dot_partials() { return kDotBlocks; }

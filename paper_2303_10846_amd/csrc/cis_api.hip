@@ -179,7 +179,7 @@ struct cis_state {
   Bufs buf{};
   Work work{};
   MacroSweeps sweeps{};
-  // Gram-Schmidt coefficients and norm of the adjoint's Krylov step; their pinned copy, and the event after it (made by
+  // Gram-Schmidt coefficients, norm and lost-wait mark of the adjoint's Krylov step; their pinned copy, and the event after it (made by
   // the first adjoint solve)
   double *krylov = nullptr, *krylov_host = nullptr;
   hipEvent_t krylov_copied = nullptr;
@@ -434,20 +434,22 @@ cis_status wall_faces(cis_state* s, int32_t tag, std::vector<cis_wall_face>& out
   return CIS_OK;
 }
 
-// Steps 2-6, n_iter times, on the state's stream, with the work arrays `w`; mark(it, k) runs between the stages.
-template <class Mark> cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t n_iter, Mark&& mark) {
+// Steps 2-6, iterations first .. n_iter - 1, on the state's stream, with the work arrays `w`; mark(it, k) runs between
+// the stages.  one_launch: the macro sweeps in one launch where the mesh fits one (cis_macro.h), else one per colour.
+template <class Mark>
+cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t first, int32_t n_iter, bool one_launch, Mark&& mark) {
   const cis_mesh* m = s->mesh;
   hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s->stream, w.flag, (int64_t)4);
   return dispatch(s, [&](auto* tp) {
     using T = std::remove_pointer_t<decltype(tp)>;
-    for (int32_t it = 0; it < n_iter; ++it) {
+    for (int32_t it = first; it < n_iter; ++it) {
       mark(it, 0);
       launch_recon<T>(s->dev, s->buf, s->stream);
       mark(it, 1);
       launch_face<T>(s->dev, s->buf, w, s->stream);
       mark(it, 2);
-      // one launch where the mesh fits one (cis_macro.h), else a launch per colour
-      if (s->sweeps.plan.m == 0 || launch_macro_sweeps(s->dev, s->buf, w, s->sweeps, s->num.n_macro, s->stream) != hipSuccess) {
+      if (!one_launch || s->sweeps.plan.m == 0 ||
+          launch_macro_sweeps(s->dev, s->buf, w, s->sweeps, s->num.n_macro, s->stream) != hipSuccess) {
         (void)hipGetLastError();
         launch_macro(s->dev, s->buf, w, m->color_off.data(), m->n_colors, s->num.n_macro, s->stream);
       }
@@ -463,15 +465,27 @@ template <class Mark> cis_status enqueue_iterations(cis_state* s, const Work& w,
   });
 }
 
-// Copy the residual history (Step 7) of the last n_iter iterations and the positivity flags back; synchronises.
-cis_status finish_iterations(cis_state* s, const Work& w, int32_t n_iter, double* res_hist) {
-  int32_t flag[4] = {0, 0, 0, 0};
-  HIP_TRY(hipMemcpyAsync(flag, w.flag, sizeof(flag), hipMemcpyDeviceToHost, s->stream));
-  if (res_hist)
-    HIP_TRY(hipMemcpyAsync(res_hist, w.res, 6 * (size_t)n_iter * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-  HIP_TRY(hipStreamSynchronize(s->stream));
-  if (flag[0] & kSweepStuck) return fail(CIS_E_DEVICE, "a macro sweep waited for a workgroup that never ran");
-  if (flag[0]) return fail(CIS_E_NONFINITE, "non-finite or non-positive state (flag " + std::to_string(flag[0]) + ")");
+// The iterations and their residual history (Step 7) and positivity flags on the host; synchronises.  Where a wait of
+// the macro sweeps ran out, the state is still that of the last complete iteration, and the rest of them follow with a
+// launch per colour.  one (or NULL): the iterations whose macro stage was one launch.
+template <class Mark>
+cis_status run_iterations(cis_state* s, const Work& w, int32_t n_iter, double* res_hist, int32_t* one, Mark&& mark) {
+  int32_t done = 0, wrong = 0;
+  for (bool one_launch = true;; one_launch = false) {
+    const cis_status st = enqueue_iterations(s, w, done, n_iter, one_launch, mark);
+    if (st != CIS_OK) return st;
+    int32_t flag[4] = {0, 0, 0, 0};
+    HIP_TRY(hipMemcpyAsync(flag, w.flag, sizeof(flag), hipMemcpyDeviceToHost, s->stream));
+    if (res_hist)
+      HIP_TRY(hipMemcpyAsync(res_hist, w.res, 6 * (size_t)n_iter * sizeof(double), hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    wrong |= flag[0] & ~kSweepStuck;
+    if (one && one_launch) *one = s->sweeps.plan.m ? flag[1] : 0;
+    if (!(flag[0] & kSweepStuck)) break;
+    done = std::max(done, flag[1]);
+    ++s->sweeps.redone;
+  }
+  if (wrong) return fail(CIS_E_NONFINITE, "non-finite or non-positive state (flag " + std::to_string(wrong) + ")");
   return CIS_OK;
 }
 
@@ -1215,24 +1229,25 @@ cis_status cis_iterate(cis_state* s, int32_t n_iter, double* res_hist) {
   auto mark = [&](int32_t it, int k) {
     if (s->profile) (void)hipEventRecord(ev[7 * (size_t)it + k], s->stream);
   };
-  cis_status st = enqueue_iterations(s, s->work, n_iter, mark);
+  int32_t one = 0;
+  const cis_status st = run_iterations(s, s->work, n_iter, res_hist, &one, mark);
   if (s->profile) {
     const cis_mesh* m = s->mesh;
     (void)hipStreamSynchronize(s->stream);
     const int64_t nmac = (int64_t)sweep_sequence(m->color_off.data(), m->n_colors, s->num.n_macro).size();
     const int64_t nmic = micro_launches(s->dev, m->color_off.data(), m->n_colors, s->num.n_micro);
-    const int64_t per_it[6] = {1, 1, s->sweeps.plan.m ? 1 : 3 + nmac, 1, nmic, 3};
-    for (int32_t it = 0; it < n_iter; ++it)
+    for (int32_t it = 0; it < n_iter; ++it) {
+      const int64_t per_it[6] = {1, 1, it < one ? 1 : 3 + nmac, 1, nmic, 3};
       for (int k = 0; k < 6; ++k) {
         float ms = 0.0f;
         (void)hipEventElapsedTime(&ms, ev[7 * (size_t)it + k], ev[7 * (size_t)it + k + 1]);
         s->prof_ms[k] += ms;
         s->prof_launch[k] += per_it[k];
       }
+    }
     for (auto& e : ev) (void)hipEventDestroy(e);
   }
-  if (st != CIS_OK) return st;
-  return finish_iterations(s, s->work, n_iter, res_hist);
+  return st;
 }
 
 cis_status cis_iterate_noalloc(cis_state* s, int32_t n_iter, double* res_hist) {
@@ -1249,9 +1264,7 @@ cis_status cis_iterate_noalloc(cis_state* s, int32_t n_iter, double* res_hist) {
   w.flag = reinterpret_cast<int32_t*>(sp);
   w.respart = sp + kScratchFlagDoubles;
   w.res = sp + kScratchFlagDoubles + kScratchPartDoubles;
-  st = enqueue_iterations(s, w, n_iter, [](int32_t, int) {});
-  if (st != CIS_OK) return st;
-  return finish_iterations(s, w, n_iter, res_hist);
+  return run_iterations(s, w, n_iter, res_hist, nullptr, [](int32_t, int) {});
 }
 
 cis_status cis_residual(cis_state* s, void* FG, void* FR, double* Fmac) {
@@ -1426,6 +1439,23 @@ cis_status cis_debug_stage(cis_state* s, int32_t which, double* out) {
   return fail(CIS_E_INVALID_ARG, "unknown stage");
 }
 
+cis_status cis_debug_sweeps(cis_state* s, int64_t polls, int64_t from, int32_t* info) {
+  if (!s || polls < -1 || polls > UINT32_MAX || from < 0) return fail(CIS_E_INVALID_ARG, "bad argument");
+  MacroSweeps& f = s->sweeps;
+  if (polls >= 0) {
+    f.polls = (uint32_t)polls;
+    f.polls_from = from;
+  }
+  if (info) {
+    const bool blocks = f.plan.m > 0 && !f.plan.local;
+    info[0] = f.plan.m == 0 ? 0 : f.plan.local ? 1 : f.block.wide ? 3 : 2;
+    info[1] = blocks ? f.block.h : 0;
+    info[2] = blocks ? f.block.blocks : 0;
+    info[3] = f.redone;
+  }
+  return CIS_OK;
+}
+
 cis_status cis_state_set_bc(cis_state* s, const cis_bc* bc, int32_t n_bc) {
   if (!s || (n_bc > 0 && !bc)) return fail(CIS_E_INVALID_ARG, "NULL argument");
   if ((size_t)n_bc != s->bcs.size()) return fail(CIS_E_INVALID_ARG, "n_bc differs from the state's");
@@ -1520,10 +1550,11 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
   auto dots = [&](const double* Vb, int nvec, const double* w, double* host) {
     return dev_dots(s, Vb, N, nvec, w, part, hdev, host);
   };
+  bool one_launch = true;  // of the macro sweeps, until a wait of theirs runs out
   auto precond = [&](const double* in, double* out) {
     if (macro_pairs > 0)
       launch_adj_block_precond(s->dev, s->buf, in, out, ptmp, pcell, s->mesh->color_off.data(), s->mesh->n_colors,
-                               precond_pairs, macro_pairs, s->sweeps, s->work.flag, q);
+                               precond_pairs, macro_pairs, one_launch ? &s->sweeps : nullptr, s->work.flag, q);
     else if (precond_pairs == 0)
       launch_precond(s->dev, s->buf, in, out, q);
     else
@@ -1533,7 +1564,13 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
     return fail(CIS_E_DEVICE, "pinned allocation failed");
   if (!s->krylov_copied) HIP_TRY(hipEventCreateWithFlags(&s->krylov_copied, hipEventDisableTiming));
   const double* const h2 = s->krylov_host;
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, q, s->work.flag, (int64_t)4);
+  auto clear_flag = [&] { hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, q, s->work.flag, (int64_t)4); };
+  auto give_up_one_launch = [&] {
+    one_launch = false;
+    ++s->sweeps.redone;
+    clear_flag();
+  };
+  clear_flag();
   // right-hand side and the explicit parameter dependence of J
   double gpJ[3], gpL[3] = {0.0, 0.0, 0.0};
   run_vjp(s, nullptr, 1.0, sl, b);
@@ -1567,14 +1604,20 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
       launch_dots(V, N, j + 1, w, part, hd + (j + 1), q);
       launch_gemv_sub(V, N, j + 1, hd + (j + 1), w, q);
       launch_dots(w, N, 1, w, part, hd + 2 * (j + 1), q);
-      launch_normalize(N, hd + 2 * (j + 1), w, q);
-      HIP_TRY(hipMemcpyAsync(s->krylov_host, hd, (2 * j + 3) * sizeof(double), hipMemcpyDeviceToHost, q));
+      launch_normalize(N, hd + 2 * (j + 1), s->work.flag, w, q);
+      HIP_TRY(hipMemcpyAsync(s->krylov_host, hd, (2 * j + 4) * sizeof(double), hipMemcpyDeviceToHost, q));
       HIP_TRY(hipEventRecord(s->krylov_copied, q));
       // the next step's preconditioner runs while the host looks at this one (384 cells x 1288: 34 us a step; at
       // convergence one application is for nothing)
       ahead = j + 1 < m && iters + 1 < max_iter;
       if (ahead) precond(w, z);
       HIP_TRY(hipEventSynchronize(s->krylov_copied));
+      if (h2[2 * (j + 1) + 1] != 0.0) {  // this step's preconditioned vector is not valid: the step again
+        give_up_one_launch();
+        ahead = false;
+        --j;
+        continue;
+      }
       for (int i = 0; i <= j; ++i) h[i] = h2[i] + h2[j + 1 + i];
       const double hn = std::sqrt(h2[2 * (j + 1)]);
       // Givens rotations on column j
@@ -1605,6 +1648,15 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
     launch_axpby(N, 0.0, z, 0.0, z, q);
     launch_gemv_sub(V, N, jend, hdev, z, q);
     precond(z, V + (int64_t)m * N);
+    if (macro_pairs > 0 && one_launch && s->sweeps.block.blocks) {
+      int32_t flag = 0;
+      HIP_TRY(hipMemcpyAsync(&flag, s->work.flag, sizeof(flag), hipMemcpyDeviceToHost, q));
+      HIP_TRY(hipStreamSynchronize(q));
+      if (flag & kSweepStuck) {
+        give_up_one_launch();
+        precond(z, V + (int64_t)m * N);
+      }
+    }
     launch_axpby(N, 1.0, V + (int64_t)m * N, 1.0, lam, q);
     // true residual r = b - A lam, and lam^T dR/dp
     run_vjp(s, lam, 0.0, sl, V);
@@ -1616,10 +1668,6 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
     beta = std::sqrt(r2);
     done = beta <= rtol * bnorm || beta == 0.0;
   }
-  int32_t flag = 0;
-  HIP_TRY(hipMemcpyAsync(&flag, s->work.flag, sizeof(flag), hipMemcpyDeviceToHost, q));
-  HIP_TRY(hipStreamSynchronize(q));
-  if (flag & kSweepStuck) return fail(CIS_E_DEVICE, "a macro sweep waited for a workgroup that never ran");
   for (int k = 0; k < 3; ++k) dJdp[k] = gpJ[k] - gpL[k];
   if (info) {
     info->iterations = iters;

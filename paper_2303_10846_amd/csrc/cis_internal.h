@@ -97,7 +97,8 @@ struct Work {
   double* cellres;   // [nc][6]
   double* res;       // [hist][6]
   double* respart;   // [kResidualParts][6] partial sums of the residual
-  int32_t* flag;     // [4]
+  int32_t* flag;     // [4]: bits of what went wrong (1, 2, 4: not positive or not finite; kSweepStuck), the iterations
+                     // completed, two unused
   double* gpf;       // [nf][3] per-face parameter adjoints of the VJP (boundary faces)
   double* bnd;       // [n_b][6] gathered rows of boundary faces
 };
@@ -156,7 +157,8 @@ void launch_adj_sweeps(const Dev& d, const Bufs& b, const double* in, double* ou
 void launch_dots(const double* V, int64_t n, int nvec, const double* w, double* part, double* out, hipStream_t st);
 void launch_gemv_sub(const double* V, int64_t n, int nvec, const double* h, double* w, hipStream_t st);
 void launch_axpby(int64_t n, double a, const double* x, double c, double* y, hipStream_t st);
-void launch_normalize(int64_t n, const double* n2, double* w, hipStream_t st);  // w /= sqrt(*n2) where positive
+// w /= sqrt(n2[0]) where that is positive; n2[1] = 1 if the macro sweeps' wait ran out (Work::flag), else 0
+void launch_normalize(int64_t n, double* n2, const int32_t* flag, double* w, hipStream_t st);
 int dot_partials();
 
 }  // namespace cis

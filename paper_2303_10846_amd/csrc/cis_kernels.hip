@@ -1790,6 +1790,7 @@ __device__ inline void update_cell(const Dev& d, const Bufs& b, const Work& w, i
 
 template <class T, bool Comp> __global__ __launch_bounds__(kBlock) void k_update(Dev d, Bufs b, Work w) {
   __shared__ double red[(kBlock / 64) * 2 * 12];
+  if (w.flag[0] & kSweepStuck) return;  // no valid prediction: the iteration is done again
   const int64_t i = blockIdx.x;
   const int64_t nv = d.nv;
   const double* ec = w.eq + ER * i;
@@ -1827,6 +1828,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_res_part(int64_t nc, const do
   Acc<6, false, kBlock> acc;
   acc.zero();
   int bad = 0;
+  if (flag[0] & kSweepStuck) return;
   for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < nc; i += (int64_t)kResParts * kBlock) {
     for (int m = 0; m < 6; ++m) acc.add(m, cellres[6 * i + m]);
     const double* Wi = W + 6 * i;
@@ -1839,8 +1841,11 @@ __global__ __launch_bounds__(kBlock) void k_reduce_res_part(int64_t nc, const do
   if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = tot[threadIdx.x];
 }
 
-// stage 2: one workgroup adds the kResParts partials in a fixed order
-__global__ __launch_bounds__(kBlock) void k_reduce_res(int64_t nc, const double* part, double* res, int32_t* flag) {
+// stage 2: one workgroup adds the kResParts partials in a fixed order; done = the iterations completed so far, into
+// flag[1]
+__global__ __launch_bounds__(kBlock) void k_reduce_res(int64_t nc, const double* part, double* res, int32_t* flag,
+                                                       int32_t done) {
+  if (flag[0] & kSweepStuck) return;
   __shared__ double red[(kBlock / 64) * 2 * 6];
   Acc<6, false, kBlock> acc;
   acc.zero();
@@ -1853,6 +1858,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_res(int64_t nc, const double*
     res[threadIdx.x] = v;
     if (!isfinite(v)) atomicOr(&flag[0], 4);
   }
+  if (threadIdx.x == 0) flag[1] = done;
 }
 
 template <class T> void launch_update(const Dev& d, const Bufs& b, const Work& w, int64_t it, hipStream_t st) {
@@ -1861,7 +1867,7 @@ template <class T> void launch_update(const Dev& d, const Bufs& b, const Work& w
   hipLaunchKernelGGL(k_reduce_res_part, dim3(kResParts), dim3(kBlock), 0, st, d.nc, (const double*)w.cellres,
                      w.respart, w.flag, (const double*)b.W);
   hipLaunchKernelGGL(k_reduce_res, dim3(1), dim3(kBlock), 0, st, d.nc, (const double*)w.respart, w.res + 6 * it,
-                     w.flag);
+                     w.flag, (int32_t)(it + 1));
 }
 
 int max_velocities() { return 16384; }

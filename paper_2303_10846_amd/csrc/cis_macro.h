@@ -52,6 +52,11 @@ constexpr int kBlockLink = kBlockMax * kBlockMax / 32;
 // 64-bit words of the exchange buffer: [2][nc][kSweepWords], then one word per block a 64-byte line, [2][kBlockMax][8]
 inline __host__ __device__ int64_t sweep_words(int64_t nc) { return 2 * (kSweepWords * nc + 8 * kBlockMax); }
 
+// Polls of one wait before a block gives up (each at least a memory round trip, 0.5 us: 0.1 to 0.3 s).  A wait that
+// long means that a workgroup is kept off the device, by a kernel of another stream or process, so the flag turns the
+// rest of the call to a launch per colour, which waits for nothing.
+constexpr uint32_t kSweepPolls = 1u << 18;
+
 // State of the sweeps of one cis_state: the plans, the exchange buffer (device) and the tag of
 // the last window published in it.
 struct MacroSweeps {
@@ -59,6 +64,9 @@ struct MacroSweeps {
   BlockPlan block;
   uint64_t* words = nullptr;
   uint32_t tag = 0;
+  uint32_t polls = kSweepPolls;  // limit of a wait, but for the first polls_from launches (tests set both)
+  int64_t polls_from = 0;
+  int32_t redone = 0;  // calls that went on with a launch per colour after a wait ran out
 };
 
 // The colours of a mesh: m = 0 where there are more than kSweepColors.
@@ -73,7 +81,9 @@ int block_count(const SweepPlan& pl, const Dev& d, int64_t nc);
 void block_probe(const Dev& d, int blocks, const MacroSweeps& f, int32_t* most, hipStream_t st);
 bool block_plan(const Dev& d, int blocks, MacroSweeps& f, const int32_t* most, hipStream_t st);
 
-// Bit of Work::flag[0] set when a wait of the sweeps in blocks ran out (its results are then not valid).
+// Bit of Work::flag[0] set when a wait of the sweeps in blocks ran out.  Its results are then not valid, and from there
+// on nothing in the call may write the state: a launch that finds the bit set returns at once, the update leaves G, R,
+// W and q alone, and the host redoes the iteration (or the Krylov step) and the rest with a launch per colour.
 constexpr int32_t kSweepStuck = 8;
 
 // Step 4 in one launch (spectral radii, right-hand side, n_macro forward + backward sweep pairs and the

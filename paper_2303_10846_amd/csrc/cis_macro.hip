@@ -28,7 +28,7 @@
 // once).  Issue: a SIMD serves its oldest wavefront first, and polling ones of other workgroups kept a younger one
 // of the same SIMD from ever publishing (seen with three workgroups a SIMD), so a block has its compute unit to
 // itself (kBlockLds), and its wavefronts poll only once all of them have published.  Every wait is bounded
-// besides (kSpinMax).
+// besides (kSweepPolls): a kernel of another stream or process may keep a block off the device for as long as it runs.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -134,9 +134,6 @@ __host__ __device__ inline int sequence_length(int m, int pairs) {
   return pairs == 0 ? 0 : m == 1 ? 1 : pairs * 2 * (m - 1) + 1;
 }
 
-// Polls of one wait before the kernel gives up (each at least a memory round trip); a wait that long means a
-// wavefront is missing, and the flag turns the call into an error.
-constexpr uint32_t kSpinMax = 1u << 18;
 // A lane's cell and neighbour
 template <int NF> struct SlotLane {
   static constexpr int NL = SlotLanes<NF>::n, CW = 64 / NL;
@@ -264,7 +261,8 @@ constexpr int kBlockLds = 96 * 1024;
 // false: a wait ran out.
 template <int NF, int Waves, class Relax>
 __device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord& r, int64_t nc, int m,
-                                        int steps, int h, uint64_t* words, uint32_t tag0, double* inc, Relax&& relax) {
+                                        int steps, int h, uint64_t* words, uint32_t tag0, uint32_t polls, double* inc,
+                                        Relax&& relax) {
   constexpr int NT = 64 * Waves, K = 12 * kBlockReads / NT;
   static_assert(12 * kBlockReads % NT == 0 && kBlockMax <= NT, "polls of a thread");
   __shared__ int stuck;
@@ -326,7 +324,7 @@ __device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord
     for (int k = 0; k < K; ++k)
       if (tid + NT * k < reads && ((relaxed >> ((colors >> (4 * k)) & 15u)) & 1u)) wanted |= 1u << k;
     for (uint32_t spins = 0; wanted != 0; ++spins) {
-      if (spins > kSpinMax) {
+      if (spins >= polls) {
         stuck = 1;
         break;
       }
@@ -372,11 +370,11 @@ template <Form F> __device__ inline double* swap_space(double* lds, int64_t nc) 
 // x: the cell's increments after the sweeps
 template <Form F, int NF, class Relax>
 __device__ inline bool sweeps(const SlotLane<NF>& L, const SweepPlan& pl, const BlockPlan& bp, int64_t nc, int steps,
-                              uint64_t* words, double* inc, uint32_t tag0, double* x, Relax&& relax) {
+                              uint64_t* words, double* inc, uint32_t tag0, uint32_t polls, double* x, Relax&& relax) {
   if constexpr (F == kLocal)
     sweeps_in_lds<NF>(L, nc, pl.m, steps, inc, relax);
-  else if (!sweeps_in_blocks<NF, threads_of(F) / 64>(L, bp.rec[blockIdx.x], nc, pl.m, steps, bp.h, words, tag0, inc,
-                                                     relax))
+  else if (!sweeps_in_blocks<NF, threads_of(F) / 64>(L, bp.rec[blockIdx.x], nc, pl.m, steps, bp.h, words, tag0, polls,
+                                                     inc, relax))
     return false;
   if (L.valid)
     for (int q = 0; q < 6; ++q) x[q] = inc[6 * L.vi + q];
@@ -388,8 +386,9 @@ __device__ inline bool sweeps(const SlotLane<NF>& L, const SweepPlan& pl, const 
 // equilibrium coefficients (q~ = q^n).
 template <int NF, Form F>
 CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Work w, SweepPlan pl, BlockPlan bp,
-                                  uint64_t* words, uint32_t tag0, int steps) {
+                                  uint64_t* words, uint32_t tag0, uint32_t polls, int steps) {
   extern __shared__ __align__(16) double sweep_lds[];
+  const bool lost = F != kLocal && (w.flag[0] & kSweepStuck);  // an earlier launch of the call gave up
   const SlotLane<NF> L = lane_of<NF, F>(d, pl, bp);
   const int64_t i = L.i;
   const GasC& g = d.gas;
@@ -462,7 +461,7 @@ CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Wo
     if (top == 1) x.v[0] *= iD;
     x.v[top] = L.a == (top == 1 ? 1 : 5) ? quotient : x.v[top] * iD;
   };
-  if (!sweeps<F>(L, pl, bp, d.nc, steps, words, sweep_lds, tag0, dW, relax)) {
+  if (lost || !sweeps<F>(L, pl, bp, d.nc, steps, words, sweep_lds, tag0, polls, dW, relax)) {
     atomicOr(&w.flag[0], kSweepStuck);
     return;
   }
@@ -489,8 +488,9 @@ CIS_SWEEP_KERNEL void k_macro_sweeps(Dev d, const double* W, const double* q, Wo
 // D_i = sum_f (A_f/V_i) r_f / 2 (+ 1/(Z tau_i) for rho E_rot).
 template <int NF, Form F>
 CIS_SWEEP_KERNEL void k_adj_macro_sweeps(Dev d, const double* W, const double* t, double* u, int32_t* flag, SweepPlan pl,
-                                      BlockPlan bp, uint64_t* words, uint32_t tag0, int steps) {
+                                      BlockPlan bp, uint64_t* words, uint32_t tag0, uint32_t polls, int steps) {
   extern __shared__ __align__(16) double sweep_lds[];
+  const bool lost = F != kLocal && (flag[0] & kSweepStuck);
   const SlotLane<NF> L = lane_of<NF, F>(d, pl, bp);
   const int64_t i = L.i;
   const GasC& g = d.gas;
@@ -538,7 +538,7 @@ CIS_SWEEP_KERNEL void k_adj_macro_sweeps(Dev d, const double* W, const double* t
     subtract_terms<NF>(ui, term, L.a, swap);
     for (int k = 0; k < Comps<NF>::n; ++k) ui.v[k] *= scale.v[k];
   };
-  if (!sweeps<F>(L, pl, bp, d.nc, steps, words, sweep_lds, tag0, x, relax)) {
+  if (lost || !sweeps<F>(L, pl, bp, d.nc, steps, words, sweep_lds, tag0, polls, x, relax)) {
     atomicOr(flag, kSweepStuck);
     return;
   }
@@ -718,6 +718,7 @@ uint32_t take_tags(MacroSweeps& f, int steps) {
   f.tag += (uint32_t)steps + 1u;
   return t0;
 }
+uint32_t take_polls(MacroSweeps& f) { return f.polls_from > 0 ? (--f.polls_from, kSweepPolls) : f.polls; }
 
 }  // namespace
 
@@ -792,21 +793,21 @@ bool block_plan(const Dev& d, int blocks, MacroSweeps& f, const int32_t* most, h
 
 hipError_t launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, MacroSweeps& f, int n_macro, hipStream_t st) {
   int steps = sequence_length(f.plan.m, n_macro);
-  uint32_t tag0 = take_tags(f, steps);
+  uint32_t tag0 = take_tags(f, steps), polls = take_polls(f);
   Dev dd = d;
   const double *W = b.W, *q = b.q;
   Work ww = w;
-  void* args[] = {&dd, &W, &q, &ww, &f.plan, &f.block, &f.words, &tag0, &steps};
+  void* args[] = {&dd, &W, &q, &ww, &f.plan, &f.block, &f.words, &tag0, &polls, &steps};
   return run(d, false, f, args, st);
 }
 
 hipError_t launch_adj_macro_sweeps(const Dev& d, const Bufs& b, MacroSweeps& f, const double* t, double* u, int n_pairs,
                                  int32_t* flag, hipStream_t st) {
   int steps = sequence_length(f.plan.m, n_pairs);
-  uint32_t tag0 = take_tags(f, steps);
+  uint32_t tag0 = take_tags(f, steps), polls = take_polls(f);
   Dev dd = d;
   const double* W = b.W;
-  void* args[] = {&dd, &W, &t, &u, &flag, &f.plan, &f.block, &f.words, &tag0, &steps};
+  void* args[] = {&dd, &W, &t, &u, &flag, &f.plan, &f.block, &f.words, &tag0, &polls, &steps};
   return run(d, true, f, args, st);
 }
 
