@@ -292,12 +292,13 @@ cis_status cis_wall_coefficients(cis_state* s, int32_t tag, const cis_wall_ref* 
    3: tau~ [n_cells]. */
 cis_status cis_debug_stage(cis_state* s, int32_t which, double* out_host);
 
-/* The macro sweeps of a state (for checks).  info (host [4], or NULL): the form of the stage (0 a launch per colour,
+/* The macro sweeps of a state (for checks).  info (host [5], or NULL): the form of the stage (0 a launch per colour,
    1 one workgroup, 2 blocks of 8 wavefronts, 3 blocks of 16), the steps of a window and the number of blocks (0 unless
-   in blocks), and how many calls went on with a launch per colour because a wait of the sweeps in blocks ran out (the
-   results are the same).  polls >= 0 sets the polls after which a wait gives up, from the from-th launch after this
-   call on (0: the first); -1 leaves it alone. */
-cis_status cis_debug_sweeps(cis_state* s, int64_t polls, int64_t from, int32_t* info);
+   in blocks), how many calls went on with a launch per colour because a wait of the sweeps in blocks ran out (the
+   results are the same), and the tag of their last window.  polls >= 0 sets the polls after which a wait gives up, from
+   the from-th launch after this call on (0: the first); tag >= 0 (not below the last) moves the tags up to it; -1 leaves
+   either alone. */
+cis_status cis_debug_sweeps(cis_state* s, int64_t polls, int64_t from, int64_t tag, int32_t* info);
 
 /* Per-stage device time of cis_iterate, measured with hipEvents recorded on the state's stream between the
    stages of every iteration, accumulated while enabled (enable = 1 also resets the accumulators).

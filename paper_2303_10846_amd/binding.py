@@ -162,7 +162,7 @@ def load(allow_build: bool = True):
     lib.cis_debug_stage.restype = st
     lib.cis_debug_stage.argtypes = [P, C.c_int32, d]
     lib.cis_debug_sweeps.restype = st
-    lib.cis_debug_sweeps.argtypes = [P, C.c_int64, C.c_int64, i32]
+    lib.cis_debug_sweeps.argtypes = [P, C.c_int64, C.c_int64, C.c_int64, i32]
     lib.cis_profile_enable.restype = st
     lib.cis_profile_enable.argtypes = [P, C.c_int32]
     lib.cis_profile_read.restype = st
@@ -478,13 +478,13 @@ class Solver:
         _check(self.lib.cis_debug_stage(self.h, which, _dp(out)))
         return out
 
-    def debug_sweeps(self, polls: int = -1, first: int = 0) -> dict:
+    def debug_sweeps(self, polls: int = -1, first: int = 0, tag: int = -1) -> dict:
         """The form of the macro sweeps (cis_debug_sweeps); polls >= 0 sets the limit of their waits from the
-        first-th launch on."""
-        info = (C.c_int32 * 4)()
-        _check(self.lib.cis_debug_sweeps(self.h, int(polls), int(first), info))
+        first-th launch on, tag >= 0 moves the tags of their windows up."""
+        info = (C.c_int32 * 5)()
+        _check(self.lib.cis_debug_sweeps(self.h, int(polls), int(first), int(tag), info))
         return dict(form=("colours", "workgroup", "blocks", "wide blocks")[info[0]], window=info[1], blocks=info[2],
-                    redone=info[3])
+                    redone=info[3], tag=info[4])
 
     # -- steady residual, VJP and adjoint (FP64) ------------------------------
     def set_bc(self, bcs):

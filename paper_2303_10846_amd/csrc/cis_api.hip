@@ -1088,10 +1088,7 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
   s->buf = Bufs{buf->G, buf->R, buf->dG, buf->dR, buf->resG, buf->resR, buf->faceG, buf->faceR, buf->W, buf->q};
   int32_t waves[kBlockCands] = {};
   if (blocks) {
-    // tag 0 in every word: no window of the first launch
-    const int64_t n = 2 * sweep_words(nc);
-    hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s->stream,
-                       reinterpret_cast<int32_t*>(s->sweeps.words), n);
+    clear_sweep_words(s->sweeps, nc, s->stream);
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s->stream, block_waves, (int64_t)kBlockCands);
     hipLaunchKernelGGL(k_zero_i32, dim3((kBlockLink + 255) / 256), dim3(256), 0, s->stream,
                        reinterpret_cast<int32_t*>(s->sweeps.block.link), (int64_t)kBlockLink);
@@ -1439,9 +1436,12 @@ cis_status cis_debug_stage(cis_state* s, int32_t which, double* out) {
   return fail(CIS_E_INVALID_ARG, "unknown stage");
 }
 
-cis_status cis_debug_sweeps(cis_state* s, int64_t polls, int64_t from, int32_t* info) {
-  if (!s || polls < -1 || polls > UINT32_MAX || from < 0) return fail(CIS_E_INVALID_ARG, "bad argument");
+cis_status cis_debug_sweeps(cis_state* s, int64_t polls, int64_t from, int64_t tag, int32_t* info) {
+  if (!s || polls < -1 || polls > UINT32_MAX || from < 0 || tag < -1 || tag > kSweepTagMax)
+    return fail(CIS_E_INVALID_ARG, "bad argument");
   MacroSweeps& f = s->sweeps;
+  if (tag >= 0 && tag < f.tag) return fail(CIS_E_INVALID_ARG, "tags only increase");
+  if (tag >= 0) f.tag = (uint32_t)tag;
   if (polls >= 0) {
     f.polls = (uint32_t)polls;
     f.polls_from = from;
@@ -1452,6 +1452,7 @@ cis_status cis_debug_sweeps(cis_state* s, int64_t polls, int64_t from, int32_t* 
     info[1] = blocks ? f.block.h : 0;
     info[2] = blocks ? f.block.blocks : 0;
     info[3] = f.redone;
+    info[4] = (int32_t)f.tag;
   }
   return CIS_OK;
 }

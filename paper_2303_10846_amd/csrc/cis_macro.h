@@ -57,6 +57,9 @@ inline __host__ __device__ int64_t sweep_words(int64_t nc) { return 2 * (kSweepW
 // rest of the call to a launch per colour, which waits for nothing.
 constexpr uint32_t kSweepPolls = 1u << 18;
 
+// Largest tag of a window: tags are compared as increasing numbers, and a launch (up to 3 million steps) takes one a step.
+constexpr uint32_t kSweepTagMax = 0x7fffffffu;
+
 // State of the sweeps of one cis_state: the plans, the exchange buffer (device) and the tag of
 // the last window published in it.
 struct MacroSweeps {
@@ -68,6 +71,9 @@ struct MacroSweeps {
   int64_t polls_from = 0;
   int32_t redone = 0;  // calls that went on with a launch per colour after a wait ran out
 };
+
+// Tag 0, that of no window, in every word of the exchange buffer
+void clear_sweep_words(const MacroSweeps& f, int64_t nc, hipStream_t st);
 
 // The colours of a mesh: m = 0 where there are more than kSweepColors.
 SweepPlan sweep_plan(const Dev& d, const int64_t* color_off, int64_t n_colors);

@@ -340,7 +340,7 @@ __device__ inline bool sweeps_in_blocks(const SlotLane<NF>& L, const BlockRecord
           wanted &= ~(1u << k);
         }
       // the reader entered this window (or by now the next but one, whose tag replaces this one's)
-      if (((wanted >> K) & 1u) && (uint32_t)hers - tag < 0x80000000u && hers != 0) wanted &= ~(1u << K);
+      if (((wanted >> K) & 1u) && (uint32_t)hers >= tag) wanted &= ~(1u << K);
     }
     __syncthreads();
     if (stuck) return false;
@@ -711,16 +711,32 @@ hipError_t run(const Dev& d, bool adjoint, const MacroSweeps& s, void** args, hi
                                     dim3(threads_of(s.block.wide ? kWideBlocks : kBlocks)), args, (unsigned)kBlockLds, st);
 }
 
-// The tags of one launch: versions 1 .. of this call follow the last call's, so no word left behind by an earlier
-// call carries an awaited tag.
-uint32_t take_tags(MacroSweeps& f, int steps) {
+__global__ __launch_bounds__(256) void k_clear_words(uint64_t* words, int64_t n) {
+  const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (k < n) words[k] = 0;
+}
+
+// The tags of one launch follow the last launch's, so no word left behind by an earlier one carries an awaited tag and
+// a later window has the larger one.  Before they would pass kSweepTagMax (13 million launches of 161 steps) the words
+// are cleared and the tags start again; 0 is the tag of no window.
+uint32_t take_tags(const Dev& d, MacroSweeps& f, int steps, hipStream_t st) {
+  const uint32_t n = (uint32_t)steps + 1u;
+  if (f.block.blocks && f.tag > kSweepTagMax - n) {
+    clear_sweep_words(f, d.nc, st);
+    f.tag = 0;
+  }
   const uint32_t t0 = f.tag;
-  f.tag += (uint32_t)steps + 1u;
+  f.tag += n;
   return t0;
 }
 uint32_t take_polls(MacroSweeps& f) { return f.polls_from > 0 ? (--f.polls_from, kSweepPolls) : f.polls; }
 
 }  // namespace
+
+void clear_sweep_words(const MacroSweeps& f, int64_t nc, hipStream_t st) {
+  const int64_t n = sweep_words(nc);
+  hipLaunchKernelGGL(k_clear_words, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, f.words, n);
+}
 
 SweepPlan sweep_plan(const Dev& d, const int64_t* color_off, int64_t n_colors) {
   SweepPlan pl;
@@ -793,7 +809,7 @@ bool block_plan(const Dev& d, int blocks, MacroSweeps& f, const int32_t* most, h
 
 hipError_t launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, MacroSweeps& f, int n_macro, hipStream_t st) {
   int steps = sequence_length(f.plan.m, n_macro);
-  uint32_t tag0 = take_tags(f, steps), polls = take_polls(f);
+  uint32_t tag0 = take_tags(d, f, steps, st), polls = take_polls(f);
   Dev dd = d;
   const double *W = b.W, *q = b.q;
   Work ww = w;
@@ -804,7 +820,7 @@ hipError_t launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, Macro
 hipError_t launch_adj_macro_sweeps(const Dev& d, const Bufs& b, MacroSweeps& f, const double* t, double* u, int n_pairs,
                                  int32_t* flag, hipStream_t st) {
   int steps = sequence_length(f.plan.m, n_pairs);
-  uint32_t tag0 = take_tags(f, steps), polls = take_polls(f);
+  uint32_t tag0 = take_tags(d, f, steps, st), polls = take_polls(f);
   Dev dd = d;
   const double* W = b.W;
   void* args[] = {&dd, &W, &t, &u, &flag, &f.plan, &f.block, &f.words, &tag0, &polls, &steps};

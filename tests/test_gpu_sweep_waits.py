@@ -117,3 +117,20 @@ def test_sweeps_beside_products_on_another_stream():
     torch.cuda.synchronize()
     assert torch.isfinite(y).all()
     assert rel(got, want) <= TOL["fp64"]
+
+
+@pytest.mark.parametrize("kind,n", [("tet", 6), ("hex", 6)])
+def test_tags_start_again_before_they_run_out(kind, n):
+    """The tags of the windows end at 2^31 - 1; the launch that would pass it clears the exchange buffer."""
+    a, b = _solver(kind, n), _solver(kind, n)
+    a.iterate(2)
+    per_launch = a.debug_sweeps()["tag"] // 2
+    b.iterate(2)
+    # the third launch from here passes the end; then one that ends on it exactly, and the next
+    for left in (2 * per_launch + 1, per_launch, per_launch - 1):
+        b.debug_sweeps(tag=2**31 - 1 - left)
+        assert rel(b.iterate(5), a.iterate(5)) <= TOL["fp64"]
+        assert b.debug_sweeps()["redone"] == 0
+        assert b.debug_sweeps()["tag"] == (5 - left // per_launch) * per_launch
+    for x, y in zip(b.get_state(), a.get_state()):
+        assert rel(x, y) <= TOL["fp64"]
