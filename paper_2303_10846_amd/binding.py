@@ -483,8 +483,8 @@ class Solver:
         first-th launch on, tag >= 0 moves the tags of their windows up."""
         info = (C.c_int32 * 5)()
         _check(self.lib.cis_debug_sweeps(self.h, int(polls), int(first), int(tag), info))
-        return dict(form=("colours", "workgroup", "blocks", "wide blocks")[info[0]], window=info[1], blocks=info[2],
-                    redone=info[3], tag=info[4])
+        return dict(form=("colours", "workgroup", "blocks", "wide blocks", "not laid out")[info[0]], window=info[1],
+                    blocks=info[2], redone=info[3], tag=info[4])
 
     # -- steady residual, VJP and adjoint (FP64) ------------------------------
     def set_bc(self, bcs):

@@ -902,9 +902,7 @@ void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, dou
   if (macro_pairs > 0) {
     // t = B^T z (W part), then Mac^T u = t and x_phi = z + M_c^T u
     hipLaunchKernelGGL((k_cell_vjp<true, true>), dim3((unsigned)nc), dim3(kBlock), 0, st, d, b, a);
-    if (!sweeps || sweeps->plan.m == 0 ||
-        launch_adj_macro_sweeps(d, b, *sweeps, gW, u, macro_pairs, flag, st) != hipSuccess) {
-      (void)hipGetLastError();
+    if (!sweeps || !launch_adj_macro_sweeps(d, b, *sweeps, gW, u, macro_pairs, flag, st)) {
       if (d.mf == 4)
         hipLaunchKernelGGL(k_adj_macro_prep<4>, dim3(ncb), dim3(kBlock), 0, st, d, b, rc, mD);
       else

@@ -448,11 +448,8 @@ cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t first, int32_
       mark(it, 1);
       launch_face<T>(s->dev, s->buf, w, s->stream);
       mark(it, 2);
-      if (!one_launch || s->sweeps.plan.m == 0 ||
-          launch_macro_sweeps(s->dev, s->buf, w, s->sweeps, s->num.n_macro, s->stream) != hipSuccess) {
-        (void)hipGetLastError();
+      if (!one_launch || !launch_macro_sweeps(s->dev, s->buf, w, s->sweeps, s->num.n_macro, s->stream))
         launch_macro(s->dev, s->buf, w, m->color_off.data(), m->n_colors, s->num.n_macro, s->stream);
-      }
       mark(it, 3);
       launch_residual<T>(s->dev, s->buf, w, s->buf.resG, s->buf.resR, 0, s->stream);
       mark(it, 4);
@@ -471,6 +468,7 @@ cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t first, int32_
 template <class Mark>
 cis_status run_iterations(cis_state* s, const Work& w, int32_t n_iter, double* res_hist, int32_t* one, Mark&& mark) {
   int32_t done = 0, wrong = 0;
+  lay_out_blocks(s->dev, s->sweeps, s->stream);
   for (bool one_launch = true;; one_launch = false) {
     const cis_status st = enqueue_iterations(s, w, done, n_iter, one_launch, mark);
     if (st != CIS_OK) return st;
@@ -480,7 +478,7 @@ cis_status run_iterations(cis_state* s, const Work& w, int32_t n_iter, double* r
       HIP_TRY(hipMemcpyAsync(res_hist, w.res, 6 * (size_t)n_iter * sizeof(double), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
     wrong |= flag[0] & ~kSweepStuck;
-    if (one && one_launch) *one = s->sweeps.plan.m ? flag[1] : 0;
+    if (one && one_launch) *one = s->sweeps.ready() ? flag[1] : 0;
     if (!(flag[0] & kSweepStuck)) break;
     done = std::max(done, flag[1]);
     ++s->sweeps.redone;
@@ -1044,14 +1042,15 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
   s->dev.mf = mf;
   s->sweeps.plan = sweep_plan(s->dev, m->color_off.data(), m->n_colors);
   const int blocks = block_count(s->sweeps.plan, s->dev, nc);
-  int32_t* block_waves = nullptr;
+  s->sweeps.block.blocks = blocks;
   if (blocks) {
     arena.want(&s->sweeps.words, (size_t)sweep_words(nc));
     arena.want(&s->sweeps.block.rec, (size_t)blocks);
     arena.want(&s->sweeps.block.owner, nc);
     arena.want(&s->sweeps.block.link, kBlockLink);
-    arena.want(&block_waves, kBlockCands);
+    arena.want(&s->sweeps.block.most, kBlockCands);
   }
+  if (!blocks && !s->sweeps.plan.local) s->sweeps.plan.m = 0;
   s->res_cap = 64;
   cis_status e = arena.commit(s);
   if (e == CIS_OK) e = own_alloc(s, &w.res, 6 * s->res_cap);
@@ -1086,21 +1085,11 @@ cis_status cis_state_create(const cis_mesh* m, const cis_dvs* dv, const cis_gas*
   d.lim_frozen = nullptr;
   fill_dev_numerics(s);
   s->buf = Bufs{buf->G, buf->R, buf->dG, buf->dR, buf->resG, buf->resR, buf->faceG, buf->faceR, buf->W, buf->q};
-  int32_t waves[kBlockCands] = {};
-  if (blocks) {
-    clear_sweep_words(s->sweeps, nc, s->stream);
-    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s->stream, block_waves, (int64_t)kBlockCands);
-    hipLaunchKernelGGL(k_zero_i32, dim3((kBlockLink + 255) / 256), dim3(256), 0, s->stream,
-                       reinterpret_cast<int32_t*>(s->sweeps.block.link), (int64_t)kBlockLink);
-    block_probe(d, blocks, s->sweeps, block_waves, s->stream);
-  }
   launch_upwind_codes(d, s->stream);
-  if (blocks) (void)hipMemcpyAsync(waves, block_waves, sizeof waves, hipMemcpyDeviceToHost, s->stream);
   if (hipStreamSynchronize(s->stream) != hipSuccess || hipGetLastError() != hipSuccess) {
     delete s;
     return fail(CIS_E_DEVICE, "upwind codes failed");
   }
-  if (!s->sweeps.plan.local && !(blocks && block_plan(d, blocks, s->sweeps, waves, s->stream))) s->sweeps.plan.m = 0;
   *out = s;
   return CIS_OK;
 }
@@ -1447,8 +1436,8 @@ cis_status cis_debug_sweeps(cis_state* s, int64_t polls, int64_t from, int64_t t
     f.polls_from = from;
   }
   if (info) {
-    const bool blocks = f.plan.m > 0 && !f.plan.local;
-    info[0] = f.plan.m == 0 ? 0 : f.plan.local ? 1 : f.block.wide ? 3 : 2;
+    const bool blocks = f.plan.m > 0 && !f.plan.local && f.laid_out;
+    info[0] = f.plan.m == 0 ? 0 : f.plan.local ? 1 : !f.laid_out ? 4 : f.block.wide ? 3 : 2;
     info[1] = blocks ? f.block.h : 0;
     info[2] = blocks ? f.block.blocks : 0;
     info[3] = f.redone;
@@ -1561,6 +1550,7 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
     else
       launch_adj_sweeps(s->dev, s->buf, in, out, s->mesh->color_off.data(), s->mesh->n_colors, precond_pairs, q);
   };
+  if (macro_pairs > 0) lay_out_blocks(s->dev, s->sweeps, q);
   if (!s->krylov_host && hipHostMalloc((void**)&s->krylov_host, (2 * kMaxRestart + 3) * sizeof(double)) != hipSuccess)
     return fail(CIS_E_DEVICE, "pinned allocation failed");
   if (!s->krylov_copied) HIP_TRY(hipEventCreateWithFlags(&s->krylov_copied, hipEventDisableTiming));
@@ -1649,7 +1639,7 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
     launch_axpby(N, 0.0, z, 0.0, z, q);
     launch_gemv_sub(V, N, jend, hdev, z, q);
     precond(z, V + (int64_t)m * N);
-    if (macro_pairs > 0 && one_launch && s->sweeps.block.blocks) {
+    if (macro_pairs > 0 && one_launch && s->sweeps.ready() && !s->sweeps.plan.local) {
       int32_t flag = 0;
       HIP_TRY(hipMemcpyAsync(&flag, s->work.flag, sizeof(flag), hipMemcpyDeviceToHost, q));
       HIP_TRY(hipStreamSynchronize(q));

@@ -40,12 +40,14 @@ struct BlockRecord {
   uint8_t read_color[kBlockReads];
   int16_t ack[kBlockMax];              // the workgroups that read this one's
 };
+constexpr int kBlockCands = 6;  // windows tried
 struct BlockPlan {
-  int blocks = 0;    // 0: the mesh does not fit
+  int blocks = 0;    // 0: the mesh is too large or runs in one workgroup
   int h = 0;
   bool wide = false;
   BlockRecord* rec = nullptr;  // [blocks], device
   int32_t* owner = nullptr;    // [nc] block of a cell
+  int32_t* most = nullptr;     // [kBlockCands] wavefronts that each window asks of the largest block
   uint32_t* link = nullptr;    // [kBlockMax][kBlockMax / 32] bit b of row a: block b reads increments of block a
 };
 constexpr int kBlockLink = kBlockMax * kBlockMax / 32;
@@ -65,11 +67,13 @@ constexpr uint32_t kSweepTagMax = 0x7fffffffu;
 struct MacroSweeps {
   SweepPlan plan;
   BlockPlan block;
+  bool laid_out = false;
   uint64_t* words = nullptr;
   uint32_t tag = 0;
   uint32_t polls = kSweepPolls;  // limit of a wait, but for the first polls_from launches (tests set both)
   int64_t polls_from = 0;
   int32_t redone = 0;  // calls that went on with a launch per colour after a wait ran out
+  bool ready() const { return plan.m > 0 && (plan.local || laid_out); }  // the sweeps can be one launch
 };
 
 // Tag 0, that of no window, in every word of the exchange buffer
@@ -79,13 +83,12 @@ void clear_sweep_words(const MacroSweeps& f, int64_t nc, hipStream_t st);
 SweepPlan sweep_plan(const Dev& d, const int64_t* color_off, int64_t n_colors);
 
 // Blocks for a mesh of nc cells on the current device (0: none, the mesh is too large or runs in one workgroup).
-// block_probe finds the wavefronts that windows of several lengths ask of the largest block (most[kBlockCands],
-// device, zeroed); block_plan takes the longest that fits, from a host copy of them, and lays out f.block.rec
-// ([blocks]) on the stream.  false: none fits.
-constexpr int kBlockCands = 6;
 int block_count(const SweepPlan& pl, const Dev& d, int64_t nc);
-void block_probe(const Dev& d, int blocks, const MacroSweeps& f, int32_t* most, hipStream_t st);
-bool block_plan(const Dev& d, int blocks, MacroSweeps& f, const int32_t* most, hipStream_t st);
+
+// Before the first sweeps of a state (its other calls don't pay for it: 0.15 ms): finds the longest window that fits and
+// lays out f.block.rec on the stream, which it waits for.  Where none fits, or the device refuses a launch, the state keeps a
+// launch per colour (plan.m = 0).
+void lay_out_blocks(const Dev& d, MacroSweeps& f, hipStream_t st);
 
 // Bit of Work::flag[0] set when a wait of the sweeps in blocks ran out.  Its results are then not valid, and from there
 // on nothing in the call may write the state: a launch that finds the bit set returns at once, the update leaves G, R,
@@ -93,12 +96,11 @@ bool block_plan(const Dev& d, int blocks, MacroSweeps& f, const int32_t* most, h
 constexpr int32_t kSweepStuck = 8;
 
 // Step 4 in one launch (spectral radii, right-hand side, n_macro forward + backward sweep pairs and the
-// predicted equilibrium); f.plan.m > 0.
-hipError_t launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, MacroSweeps& f, int n_macro, hipStream_t st);
+// predicted equilibrium), after lay_out_blocks.  false: not launched, the mesh takes a launch per colour.
+bool launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, MacroSweeps& f, int n_macro, hipStream_t st);
 
-// Mac^T u = t of the adjoint's block preconditioner, n_pairs sweep pairs from u = 0; f.plan.m > 0.  flag: as
-// Work::flag.
-hipError_t launch_adj_macro_sweeps(const Dev& d, const Bufs& b, MacroSweeps& f, const double* t, double* u, int n_pairs,
-                                 int32_t* flag, hipStream_t st);
+// Mac^T u = t of the adjoint's block preconditioner, n_pairs sweep pairs from u = 0, likewise.  flag: as Work::flag.
+bool launch_adj_macro_sweeps(const Dev& d, const Bufs& b, MacroSweeps& f, const double* t, double* u, int n_pairs,
+                             int32_t* flag, hipStream_t st);
 
 }  // namespace cis

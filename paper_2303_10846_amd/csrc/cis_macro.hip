@@ -564,7 +564,7 @@ __global__ __launch_bounds__(kBlockMax) void k_block_acks(BlockPlan bp, int bloc
 }
 
 // The plan of block blockIdx.x for windows of cand.h[blockIdx.y] steps (write: into its record and the
-// links; else the owners and the most wavefronts of a block, into most[blockIdx.y], kTooMany where something else does
+// links; else the owners and the most wavefronts of a block, into bp.most[blockIdx.y], kTooMany where something else does
 // not fit).
 // What a window's own values depend on, by walking its steps backwards: `need` holds the cells whose value is needed
 // after the step; those of the step's colour are relaxed in it and pass the need on to their neighbours.
@@ -573,7 +573,7 @@ struct BlockCands {
   int n = 0, h[kBlockCands];
 };
 __global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl, BlockPlan bp, BlockCands cand, int cw,
-                                                             int write, int32_t* most) {
+                                                             int write) {
   enum : uint8_t { kNeed = 1, kValue = 2, kSlot = 4, kOwn = 8, kRelax = 16, kRead = 32 };
   extern __shared__ int16_t plan_lds[];
   int16_t* const loc = plan_lds;  // [nc] place of a cell's increment
@@ -670,7 +670,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl
   }
   if (!write) {
     const bool fits = slots + others <= kBlockVals && reads <= kBlockReads;
-    if (tid == 0) atomicMax(&most[blockIdx.y], fits ? waves : kTooMany);
+    if (tid == 0) atomicMax(&bp.most[blockIdx.y], fits ? waves : kTooMany);
     return;
   }
   for (int v = tid; v < kBlockVals; v += kPlanThreads) r->cell[v] = -1;
@@ -699,7 +699,7 @@ template <Form F> const void* kernel_of(bool adjoint, const Dev& d) {
 
 static_assert(sizeof(double) * (6 * kBlockVals + 6 * kSwapRow * kWideBlockWaves) <= kBlockLds, "LDS of a block");
 
-hipError_t run(const Dev& d, bool adjoint, const MacroSweeps& s, void** args, hipStream_t st) {
+hipError_t enqueue(const Dev& d, bool adjoint, const MacroSweeps& s, void** args, hipStream_t st) {
   // as many wavefronts as own cells: idle ones cost every barrier (a pass of 48 tetrahedra 166.6 -> 162.6 us)
   if (s.plan.local) {
     const int waves = s.plan.wave0[s.plan.m];
@@ -710,10 +710,25 @@ hipError_t run(const Dev& d, bool adjoint, const MacroSweeps& s, void** args, hi
   return hipLaunchCooperativeKernel(k, dim3((unsigned)s.block.blocks),
                                     dim3(threads_of(s.block.wide ? kWideBlocks : kBlocks)), args, (unsigned)kBlockLds, st);
 }
+// false: not launched.  An error that was there before stays for the caller's check; a refusal of this launch (a grid
+// that the device cannot hold at once) keeps the state at a launch per colour from here on.
+bool run(const Dev& d, bool adjoint, MacroSweeps& s, void** args, hipStream_t st) {
+  if (hipPeekAtLastError() != hipSuccess) return false;
+  if (enqueue(d, adjoint, s, args, st) == hipSuccess) return true;
+  (void)hipGetLastError();
+  s.plan.m = 0;
+  return false;
+}
 
 __global__ __launch_bounds__(256) void k_clear_words(uint64_t* words, int64_t n) {
   const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (k < n) words[k] = 0;
+}
+
+__global__ __launch_bounds__(256) void k_clear_plan(BlockPlan bp) {
+  const int k = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (k < kBlockLink) bp.link[k] = 0;
+  if (k < kBlockCands) bp.most[k] = 0;
 }
 
 // The tags of one launch follow the last launch's, so no word left behind by an earlier one carries an awaited tag and
@@ -781,14 +796,20 @@ static BlockCands block_windows(int m) {
 
 static int cells_per_wave(const Dev& d) { return 64 / (d.mf == 4 ? SlotLanes<4>::n : SlotLanes<kMaxFaces>::n); }
 
-void block_probe(const Dev& d, int blocks, const MacroSweeps& f, int32_t* most, hipStream_t st) {
-  const BlockCands c = block_windows(f.plan.m);
-  hipLaunchKernelGGL(k_block_plan, dim3(blocks, c.n), dim3(kPlanThreads), 3 * (size_t)d.nc, st, d, f.plan, f.block, c,
-                     cells_per_wave(d), 0, most);
-}
-
-bool block_plan(const Dev& d, int blocks, MacroSweeps& f, const int32_t* most, hipStream_t st) {
+void lay_out_blocks(const Dev& d, MacroSweeps& f, hipStream_t st) {
+  // an error that is there already is the caller's to report: the layout waits for the next call
+  if (f.laid_out || f.plan.m == 0 || f.plan.local || hipPeekAtLastError() != hipSuccess) return;
+  f.laid_out = true;
+  const int blocks = f.block.blocks;
   BlockCands c = block_windows(f.plan.m);
+  int32_t most[kBlockCands] = {};
+  clear_sweep_words(f, d.nc, st);
+  hipLaunchKernelGGL(k_clear_plan, dim3((kBlockLink + 255) / 256), dim3(256), 0, st, f.block);
+  hipLaunchKernelGGL(k_block_plan, dim3(blocks, c.n), dim3(kPlanThreads), 3 * (size_t)d.nc, st, d, f.plan, f.block, c,
+                     cells_per_wave(d), 0);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipMemcpyAsync(most, f.block.most, sizeof most, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
   // 8 wavefronts where a window fits them, two a SIMD; 16 only where none does (a longer window with 16 gains
   // nothing: the wavefronts of a colour share a SIMD)
   int k = 0;
@@ -796,18 +817,21 @@ bool block_plan(const Dev& d, int blocks, MacroSweeps& f, const int32_t* most, h
   f.block.wide = k == c.n;
   if (f.block.wide)
     for (k = 0; k < c.n && most[k] > kWideBlockWaves; ++k) {}
-  if (k == c.n) return false;
-  c.h[0] = c.h[k];
-  hipLaunchKernelGGL(k_block_plan, dim3(blocks), dim3(kPlanThreads), 3 * (size_t)d.nc, st, d, f.plan, f.block, c,
-                     cells_per_wave(d), 1, (int32_t*)nullptr);
-  hipLaunchKernelGGL(k_block_acks, dim3(1), dim3(kBlockMax), 0, st, f.block, blocks,
-                     c.h[0] >= f.plan.m ? 1 : 0);
-  f.block.h = c.h[0];
-  f.block.blocks = blocks;
-  return true;
+  if (e == hipSuccess && k < c.n) {
+    f.block.h = c.h[0] = c.h[k];
+    hipLaunchKernelGGL(k_block_plan, dim3(blocks), dim3(kPlanThreads), 3 * (size_t)d.nc, st, d, f.plan, f.block, c,
+                       cells_per_wave(d), 1);
+    hipLaunchKernelGGL(k_block_acks, dim3(1), dim3(kBlockMax), 0, st, f.block, blocks, f.block.h >= f.plan.m ? 1 : 0);
+    e = hipGetLastError();
+  }
+  if (e != hipSuccess || k == c.n) {
+    (void)hipGetLastError();
+    f.plan.m = 0;
+  }
 }
 
-hipError_t launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, MacroSweeps& f, int n_macro, hipStream_t st) {
+bool launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, MacroSweeps& f, int n_macro, hipStream_t st) {
+  if (!f.ready()) return false;
   int steps = sequence_length(f.plan.m, n_macro);
   uint32_t tag0 = take_tags(d, f, steps, st), polls = take_polls(f);
   Dev dd = d;
@@ -817,8 +841,9 @@ hipError_t launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, Macro
   return run(d, false, f, args, st);
 }
 
-hipError_t launch_adj_macro_sweeps(const Dev& d, const Bufs& b, MacroSweeps& f, const double* t, double* u, int n_pairs,
-                                 int32_t* flag, hipStream_t st) {
+bool launch_adj_macro_sweeps(const Dev& d, const Bufs& b, MacroSweeps& f, const double* t, double* u, int n_pairs,
+                             int32_t* flag, hipStream_t st) {
+  if (!f.ready()) return false;
   int steps = sequence_length(f.plan.m, n_pairs);
   uint32_t tag0 = take_tags(d, f, steps, st), polls = take_polls(f);
   Dev dd = d;

@@ -134,3 +134,16 @@ def test_tags_start_again_before_they_run_out(kind, n):
         assert b.debug_sweeps()["tag"] == (5 - left // per_launch) * per_launch
     for x, y in zip(b.get_state(), a.get_state()):
         assert rel(x, y) <= TOL["fp64"]
+
+
+def test_blocks_are_laid_out_by_the_first_call_that_sweeps():
+    s = _solver("hex", 6, nv_side=5)
+    s.residual()
+    s.wall_loads(1)
+    s.adjoint(1, 2, restart=2, max_iter=2)  # no macro sweeps in its preconditioner
+    assert s.debug_sweeps()["form"] == "not laid out"
+    s.adjoint(1, 2, restart=2, max_iter=2, macro_pairs=2)
+    assert s.debug_sweeps()["form"] == "blocks"
+    s = _solver("hex", 6)
+    s.iterate_noalloc(1)
+    assert s.debug_sweeps()["form"] == "blocks"
