@@ -376,6 +376,11 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
                              double rtol, int32_t precond_pairs, int32_t macro_pairs, void* work,
                              int64_t work_bytes, double* lam, double* dJdp, double* J, cis_adjoint_info* info);
 
+/* The sweeps of that preconditioner alone (for checks), at the current W, `pairs` (1..200) pairs from zero, device
+   arrays: macro = 0: (D + N^T) x = -in for the G and R rows, the W and q rows copied ([2 n_cells n_vel + 12 n_cells]
+   doubles); macro = 1: the transposed steady macroscopic system with right-hand side in ([n_cells][6]). */
+cis_status cis_debug_adjoint_sweeps(cis_state* s, int32_t macro, int32_t pairs, const double* in_dev, double* out_dev);
+
 #ifdef __cplusplus
 }
 #endif

@@ -29,7 +29,7 @@ EXPORTS = [
     "cis_wall_heat_flux", "cis_debug_stage", "cis_profile_enable", "cis_profile_read", "cis_state_set_bc",
     "cis_steady_residual", "cis_residual_vjp", "cis_adjoint_required_bytes", "cis_adjoint_solve", "cis_wall_loads",
     "cis_wall_coefficients_of_loads", "cis_wall_coefficients", "cis_iterate_noalloc", "cis_limiter_freeze",
-    "cis_mesh_create_cells", "cis_debug_sweeps",
+    "cis_mesh_create_cells", "cis_debug_sweeps", "cis_debug_adjoint_sweeps",
 ]
 STAGE_NAMES = ["recon", "face", "macro", "residual", "micro", "update"]
 
@@ -163,6 +163,8 @@ def load(allow_build: bool = True):
     lib.cis_debug_stage.argtypes = [P, C.c_int32, d]
     lib.cis_debug_sweeps.restype = st
     lib.cis_debug_sweeps.argtypes = [P, C.c_int64, C.c_int64, C.c_int64, i32]
+    lib.cis_debug_adjoint_sweeps.restype = st
+    lib.cis_debug_adjoint_sweeps.argtypes = [P, C.c_int32, C.c_int32, P, P]
     lib.cis_profile_enable.restype = st
     lib.cis_profile_enable.argtypes = [P, C.c_int32]
     lib.cis_profile_read.restype = st
@@ -485,6 +487,12 @@ class Solver:
         _check(self.lib.cis_debug_sweeps(self.h, int(polls), int(first), int(tag), info))
         return dict(form=("colours", "workgroup", "blocks", "wide blocks", "not laid out")[info[0]], window=info[1],
                     blocks=info[2], redone=info[3], tag=info[4])
+
+    def debug_adjoint_sweeps(self, x, macro: bool, pairs: int):
+        """The sweeps of the adjoint's preconditioner on x (a device tensor; cis_debug_adjoint_sweeps)."""
+        out = self.torch.empty_like(x)
+        _check(self.lib.cis_debug_adjoint_sweeps(self.h, int(macro), int(pairs), _ptr(x), _ptr(out)))
+        return out
 
     # -- steady residual, VJP and adjoint (FP64) ------------------------------
     def set_bc(self, bcs):

@@ -23,4 +23,10 @@ void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, dou
                               const int64_t* color_off, int64_t n_colors, int micro_pairs, int macro_pairs,
                               MacroSweeps* sweeps, int32_t* flag, hipStream_t st);
 
+// Its macro part: Mac^T u = t ([n_cells][6]) with `pairs` PR-SGS pairs from u = 0.  rc [n_cells][max_faces] and mD
+// [n_cells][2]: scratch.
+void launch_adj_macro(const Dev& d, const Bufs& b, const double* t, double* u, double* rc, double* mD,
+                      const int64_t* color_off, int64_t n_colors, int pairs, MacroSweeps* sweeps, int32_t* flag,
+                      hipStream_t st);
+
 }  // namespace cis

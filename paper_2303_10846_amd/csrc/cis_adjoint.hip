@@ -881,6 +881,27 @@ __global__ __launch_bounds__(kBlock) void k_adj_ysub(int64_t nc, int64_t off, co
 
 }  // namespace
 
+void launch_adj_macro(const Dev& d, const Bufs& b, const double* t, double* u, double* rc, double* mD,
+                      const int64_t* color_off, int64_t n_colors, int pairs, MacroSweeps* sweeps, int32_t* flag,
+                      hipStream_t st) {
+  if (sweeps && launch_adj_macro_sweeps(d, b, *sweeps, t, u, pairs, flag, st)) return;
+  const unsigned ncb = (unsigned)((d.nc + kBlock - 1) / kBlock);
+  if (d.mf == 4)
+    hipLaunchKernelGGL(k_adj_macro_prep<4>, dim3(ncb), dim3(kBlock), 0, st, d, b, rc, mD);
+  else
+    hipLaunchKernelGGL(k_adj_macro_prep<kMaxFaces>, dim3(ncb), dim3(kBlock), 0, st, d, b, rc, mD);
+  launch_axpby(6 * d.nc, 0.0, t, 0.0, u, st);
+  for (const int64_t c : sweep_sequence(color_off, n_colors, pairs)) {
+    const int64_t n = color_off[c + 1] - color_off[c];
+    if (d.mf == 4)
+      hipLaunchKernelGGL(k_adj_macro_sweep<4>, dim3((unsigned)((4 * n + 63) / 64)), dim3(64), 0, st, d, b,
+                         (const double*)rc, (const double*)mD, t, u, color_off[c], color_off[c + 1]);
+    else
+      hipLaunchKernelGGL(k_adj_macro_sweep<kMaxFaces>, dim3((unsigned)((8 * n + 63) / 64)), dim3(64), 0, st, d, b,
+                         (const double*)rc, (const double*)mD, t, u, color_off[c], color_off[c + 1]);
+  }
+}
+
 void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, double* out, double* tmp, double* cell,
                               const int64_t* color_off, int64_t n_colors, int micro_pairs, int macro_pairs,
                               MacroSweeps* sweeps, int32_t* flag, hipStream_t st) {
@@ -891,7 +912,6 @@ void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, dou
   double* rc = u + 6 * nc;
   double* mD = rc + (int64_t)d.mf * nc;
   const unsigned nch = (unsigned)std::min<int64_t>((d.nv + kBlock - 1) / kBlock, 64);
-  const unsigned ncb = (unsigned)((nc + kBlock - 1) / kBlock);
   // z = -(D + N)^-T (s_phi + M^T s_Y)
   hipLaunchKernelGGL(k_adj_expand, dim3((unsigned)nc, nch), dim3(kBlock), 0, st, d, b, in, tmp);
   if (micro_pairs > 0)
@@ -902,22 +922,7 @@ void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, dou
   if (macro_pairs > 0) {
     // t = B^T z (W part), then Mac^T u = t and x_phi = z + M_c^T u
     hipLaunchKernelGGL((k_cell_vjp<true, true>), dim3((unsigned)nc), dim3(kBlock), 0, st, d, b, a);
-    if (!sweeps || !launch_adj_macro_sweeps(d, b, *sweeps, gW, u, macro_pairs, flag, st)) {
-      if (d.mf == 4)
-        hipLaunchKernelGGL(k_adj_macro_prep<4>, dim3(ncb), dim3(kBlock), 0, st, d, b, rc, mD);
-      else
-        hipLaunchKernelGGL(k_adj_macro_prep<kMaxFaces>, dim3(ncb), dim3(kBlock), 0, st, d, b, rc, mD);
-      launch_axpby(6 * nc, 0.0, gW, 0.0, u, st);
-      for (const int64_t c : sweep_sequence(color_off, n_colors, macro_pairs)) {
-        const int64_t n = color_off[c + 1] - color_off[c];
-        if (d.mf == 4)
-          hipLaunchKernelGGL(k_adj_macro_sweep<4>, dim3((unsigned)((4 * n + 63) / 64)), dim3(64), 0, st, d, b,
-                             (const double*)rc, (const double*)mD, (const double*)gW, u, color_off[c], color_off[c + 1]);
-        else
-          hipLaunchKernelGGL(k_adj_macro_sweep<kMaxFaces>, dim3((unsigned)((8 * n + 63) / 64)), dim3(64), 0, st, d, b,
-                             (const double*)rc, (const double*)mD, (const double*)gW, u, color_off[c], color_off[c + 1]);
-      }
-    }
+    launch_adj_macro(d, b, gW, u, rc, mD, color_off, n_colors, macro_pairs, sweeps, flag, st);
     hipLaunchKernelGGL(k_adj_lift, dim3((unsigned)nc, nch), dim3(kBlock), 0, st, d, (const double*)u, out);
   }
   // x_Y = s_Y - B^T x_phi

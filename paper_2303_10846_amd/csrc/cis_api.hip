@@ -1446,6 +1446,29 @@ cis_status cis_debug_sweeps(cis_state* s, int64_t polls, int64_t from, int64_t t
   return CIS_OK;
 }
 
+cis_status cis_debug_adjoint_sweeps(cis_state* s, int32_t macro, int32_t pairs, const double* in, double* out) {
+  if (!s || !in || !out || in == out || pairs < 1 || pairs > 200) return fail(CIS_E_INVALID_ARG, "bad argument");
+  if (s->precision != CIS_FP64) return fail(CIS_E_UNSUPPORTED, "the adjoint is FP64 only");
+  const int64_t* off = s->mesh->color_off.data();
+  const Work& w = s->work;
+  int32_t flag = 0;
+  if (!macro) {
+    launch_adj_sweeps(s->dev, s->buf, in, out, off, s->mesh->n_colors, pairs, s->stream);
+  } else {
+    lay_out_blocks(s->dev, s->sweeps, s->stream);
+    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s->stream, w.flag, (int64_t)4);
+    launch_adj_macro(s->dev, s->buf, in, out, w.rcf, w.mD, off, s->mesh->n_colors, pairs, &s->sweeps, w.flag, s->stream);
+    HIP_TRY(hipMemcpyAsync(&flag, w.flag, sizeof(flag), hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    if (flag & kSweepStuck)
+      launch_adj_macro(s->dev, s->buf, in, out, w.rcf, w.mD, off, s->mesh->n_colors, pairs, nullptr, w.flag, s->stream);
+  }
+  const cis_status st = device_check("adjoint sweeps");
+  if (st != CIS_OK) return st;
+  HIP_TRY(hipStreamSynchronize(s->stream));
+  return CIS_OK;
+}
+
 cis_status cis_state_set_bc(cis_state* s, const cis_bc* bc, int32_t n_bc) {
   if (!s || (n_bc > 0 && !bc)) return fail(CIS_E_INVALID_ARG, "NULL argument");
   if ((size_t)n_bc != s->bcs.size()) return fail(CIS_E_INVALID_ARG, "n_bc differs from the state's");
