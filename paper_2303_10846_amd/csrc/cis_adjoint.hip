@@ -915,7 +915,7 @@ void launch_adj_block_precond(const Dev& d, const Bufs& b, const double* in, dou
   // z = -(D + N)^-T (s_phi + M^T s_Y)
   hipLaunchKernelGGL(k_adj_expand, dim3((unsigned)nc, nch), dim3(kBlock), 0, st, d, b, in, tmp);
   if (micro_pairs > 0)
-    launch_adj_sweeps(d, b, tmp, out, color_off, n_colors, micro_pairs, st);
+    launch_adj_sweeps(d, b, tmp, out, color_off, n_colors, micro_pairs, sweeps && sweeps->in_blocks(), st);
   else
     launch_precond(d, b, tmp, out, st);
   AdjArgs a{out, out + P, nullptr, nullptr, 0.0, -1, -1, -1, nullptr, nullptr, gW, gq, nullptr};

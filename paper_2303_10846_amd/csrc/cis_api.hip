@@ -453,7 +453,8 @@ cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t first, int32_
       mark(it, 3);
       launch_residual<T>(s->dev, s->buf, w, s->buf.resG, s->buf.resR, 0, s->stream);
       mark(it, 4);
-      launch_micro<T>(s->dev, s->buf, w, m->color_off.data(), m->n_colors, s->num.n_micro, s->stream);
+      launch_micro<T>(s->dev, s->buf, w, m->color_off.data(), m->n_colors, s->num.n_micro,
+                      s->sweeps.in_blocks(), s->stream);
       mark(it, 5);
       launch_update<T>(s->dev, s->buf, w, it, s->stream);
       mark(it, 6);
@@ -1221,7 +1222,9 @@ cis_status cis_iterate(cis_state* s, int32_t n_iter, double* res_hist) {
     const cis_mesh* m = s->mesh;
     (void)hipStreamSynchronize(s->stream);
     const int64_t nmac = (int64_t)sweep_sequence(m->color_off.data(), m->n_colors, s->num.n_macro).size();
-    const int64_t nmic = micro_launches(s->dev, m->color_off.data(), m->n_colors, s->num.n_micro);
+    const int64_t nmic = micro_launches(s->dev, m->color_off.data(), m->n_colors, s->num.n_micro,
+                                        s->precision == CIS_FP64 ? sizeof(double) : sizeof(float),
+                                        s->sweeps.in_blocks());
     for (int32_t it = 0; it < n_iter; ++it) {
       const int64_t per_it[6] = {1, 1, it < one ? 1 : 3 + nmac, 1, nmic, 3};
       for (int k = 0; k < 6; ++k) {
@@ -1453,7 +1456,7 @@ cis_status cis_debug_adjoint_sweeps(cis_state* s, int32_t macro, int32_t pairs, 
   const Work& w = s->work;
   int32_t flag = 0;
   if (!macro) {
-    launch_adj_sweeps(s->dev, s->buf, in, out, off, s->mesh->n_colors, pairs, s->stream);
+    launch_adj_sweeps(s->dev, s->buf, in, out, off, s->mesh->n_colors, pairs, false, s->stream);
   } else {
     lay_out_blocks(s->dev, s->sweeps, s->stream);
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s->stream, w.flag, (int64_t)4);
@@ -1571,7 +1574,7 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
     else if (precond_pairs == 0)
       launch_precond(s->dev, s->buf, in, out, q);
     else
-      launch_adj_sweeps(s->dev, s->buf, in, out, s->mesh->color_off.data(), s->mesh->n_colors, precond_pairs, q);
+      launch_adj_sweeps(s->dev, s->buf, in, out, s->mesh->color_off.data(), s->mesh->n_colors, precond_pairs, false, q);
   };
   if (macro_pairs > 0) lay_out_blocks(s->dev, s->sweeps, q);
   if (!s->krylov_host && hipHostMalloc((void**)&s->krylov_host, (2 * kMaxRestart + 3) * sizeof(double)) != hipSuccess)
@@ -1662,7 +1665,7 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
     launch_axpby(N, 0.0, z, 0.0, z, q);
     launch_gemv_sub(V, N, jend, hdev, z, q);
     precond(z, V + (int64_t)m * N);
-    if (macro_pairs > 0 && one_launch && s->sweeps.ready() && !s->sweeps.plan.local) {
+    if (macro_pairs > 0 && one_launch && s->sweeps.in_blocks()) {
       int32_t flag = 0;
       HIP_TRY(hipMemcpyAsync(&flag, s->work.flag, sizeof(flag), hipMemcpyDeviceToHost, q));
       HIP_TRY(hipStreamSynchronize(q));

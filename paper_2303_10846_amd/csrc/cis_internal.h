@@ -131,10 +131,12 @@ void launch_macro(const Dev& d, const Bufs& b, const Work& w, const int64_t* col
                   int n_macro, hipStream_t st);
 template <class T> void launch_residual(const Dev& d, const Bufs& b, const Work& w, void* outG, void* outR,
                                         int flux_only, hipStream_t st);
-// Launches of launch_micro's sweeps
-int64_t micro_launches(const Dev& d, const int64_t* color_off, int64_t n_colors, int n_micro);
+// Launches of launch_micro's sweeps, distributions of value_bytes a value.  beside_blocks: the stream's macro sweeps
+// run in blocks (as a cooperative launch).
+int64_t micro_launches(const Dev& d, const int64_t* color_off, int64_t n_colors, int n_micro, size_t value_bytes,
+                       bool beside_blocks);
 template <class T> void launch_micro(const Dev& d, const Bufs& b, const Work& w, const int64_t* color_off,
-                                     int64_t n_colors, int n_micro, hipStream_t st);
+                                     int64_t n_colors, int n_micro, bool beside_blocks, hipStream_t st);
 template <class T> void launch_update(const Dev& d, const Bufs& b, const Work& w, int64_t it, hipStream_t st);
 void launch_macro_flux_cells(const Dev& d, const Work& w, hipStream_t st);
 void launch_upwind_codes(const Dev& d, hipStream_t st);
@@ -153,7 +155,7 @@ void launch_cell_steady(const Dev& d, const Bufs& b, double* rG, double* rR, dou
 void launch_vjp(const Dev& d, const Bufs& b, const AdjArgs& a, hipStream_t st);
 void launch_precond(const Dev& d, const Bufs& b, const double* in, double* out, hipStream_t st);
 void launch_adj_sweeps(const Dev& d, const Bufs& b, const double* in, double* out, const int64_t* color_off,
-                       int64_t n_colors, int n_pairs, hipStream_t st);
+                       int64_t n_colors, int n_pairs, bool beside_blocks, hipStream_t st);
 void launch_dots(const double* V, int64_t n, int nvec, const double* w, double* part, double* out, hipStream_t st);
 void launch_gemv_sub(const double* V, int64_t n, int nvec, const double* h, double* w, hipStream_t st);
 void launch_axpby(int64_t n, double a, const double* x, double c, double* y, hipStream_t st);

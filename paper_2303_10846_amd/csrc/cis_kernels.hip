@@ -1479,13 +1479,27 @@ __global__ __launch_bounds__(kChunkThreads) void k_micro_chunk(Dev d, Bufs b, Wo
   }
 }
 
-// Which meshes take the sweeps in one launch.  Measured, one launch against one per colour: 11.5 against 36 us (48
-// tets x 216, FP64, 9 relaxations), the preconditioner's 56 against 85 us (384 six-slot cells x 1288, 13), but 52
-// against 50 us (1296 tets x 512, FP32) and 58 against 56 us (925 x 729, FP64), where a colour's cells
-// outgrow a round and its loads bind.  1024 cells are a few rounds of 256 cells a colour; 2^19 values lie
-// between the last two pairs.
-static bool chunk_sweeps(const Dev& d, const ColorPlan& pl) {
-  return pl.m > 0 && d.nc <= 1024 && d.nc * d.nv <= (int64_t)1 << 19;
+// Which sweeps run in one launch: those estimated at less than 0.9 of the launches per colour.  A launch takes 3.6 us
+// (4.6 beside macro sweeps in blocks: launches of a stream start later after a cooperative one) and a stream of its values.  In one launch a relaxation costs its latency, which grows with the cells of a colour
+// that a lane's workgroup goes through, or the reading of their geometry by every workgroup, at 8.4 TB/s out of the L2
+// (1.6 times as long where a colour takes two rounds of 256 cells), besides a start that grows with the mesh.  Beyond
+// kChunkResident velocities the workgroups no longer run all at once.  Coefficients from 664 shapes (1 to 1 000 cells of
+// 4 and 6 slots, 8 to 15 625 velocities, 1, 2 and 10 pairs, both precisions, forward and transposed), of which the rule
+// takes none that measured slower in one launch.  E.g. forward, FP64, one launch against one per colour: 14.3 against
+// 34 us (48 tets x 512, 9 relaxations), 36 against 48 (750 x 512, 9); 71 against 44 (48 x 10 648), 45 against 24 (1 000
+// six-slot cells x 216, 5) and 25 against 19 (512 x 1 000, 3) keep the launches per colour.
+constexpr int64_t kChunkResident = 2048;  // two workgroups a compute unit
+static bool chunk_sweeps(const Dev& d, const ColorPlan& pl, const int64_t* color_off, const std::vector<int64_t>& seq,
+                         size_t value_bytes, bool beside_blocks) {
+  if (pl.m < 2 || d.nc > 1024 || d.nv > kChunkResident) return false;
+  double chunk = 5.0 + 0.01 * (double)d.nc, colours = 3.0;  // us
+  for (const int64_t c : seq) {
+    const double n = (double)(color_off[c + 1] - color_off[c]), values = n * (double)d.nv;
+    const double geometry = values * (16 + 24 * d.mf) / 8.4e6 * (n > 256 ? 1.6 : 1.0);
+    chunk += std::max(0.75 + 0.0012 * d.mf * n, geometry);
+    colours += (beside_blocks ? 4.6 : 3.6) + 0.8e-6 * (double)value_bytes * values;
+  }
+  return chunk < 0.9 * colours;
 }
 static ColorPlan color_plan(const int64_t* color_off, int64_t n_colors) {
   ColorPlan pl{};
@@ -1498,18 +1512,17 @@ static ColorPlan color_plan(const int64_t* color_off, int64_t n_colors) {
   }
   return pl;
 }
-int64_t micro_launches(const Dev& d, const int64_t* color_off, int64_t n_colors, int n_micro) {
-  const int64_t n = (int64_t)sweep_sequence(color_off, n_colors, n_micro).size();
-  return n > 0 && chunk_sweeps(d, color_plan(color_off, n_colors)) ? 1 : n;
+int64_t micro_launches(const Dev& d, const int64_t* color_off, int64_t n_colors, int n_micro, size_t value_bytes,
+                       bool beside_blocks) {
+  const std::vector<int64_t> seq = sweep_sequence(color_off, n_colors, n_micro);
+  return chunk_sweeps(d, color_plan(color_off, n_colors), color_off, seq, value_bytes, beside_blocks) ? 1 : (int64_t)seq.size();
 }
 
 template <class T, int NF>
-static bool launch_micro_chunk(const Dev& d, const Bufs& b, const Work& w, const ColorPlan& pl, int steps, hipStream_t st) {
-  if (!chunk_sweeps(d, pl)) return false;
+static void launch_micro_chunk(const Dev& d, const Bufs& b, const Work& w, const ColorPlan& pl, int steps, hipStream_t st) {
   const dim3 grid((unsigned)((d.nv + kChunkVel - 1) / kChunkVel));
   const size_t lds = (size_t)d.nc * kChunkVel * 2 * sizeof(T);
   hipLaunchKernelGGL((k_micro_chunk<T, NF>), grid, dim3(kChunkThreads), lds, st, d, b, w, pl, steps);
-  return true;
 }
 
 // Preconditioner of the discrete adjoint (FP64): point relaxation over one colour of
@@ -1627,10 +1640,10 @@ __global__ __launch_bounds__(kChunkThreads) void k_adj_chunk(Dev d, Bufs b, cons
 }
 
 void launch_adj_sweeps(const Dev& d, const Bufs& b, const double* in, double* out, const int64_t* color_off,
-                       int64_t n_colors, int n_pairs, hipStream_t st) {
+                       int64_t n_colors, int n_pairs, bool beside_blocks, hipStream_t st) {
   const std::vector<int64_t> seq = sweep_sequence(color_off, n_colors, n_pairs);
   const ColorPlan pl = color_plan(color_off, n_colors);
-  const bool chunk = chunk_sweeps(d, pl);
+  const bool chunk = chunk_sweeps(d, pl, color_off, seq, sizeof(double), beside_blocks);
   if (chunk) {
     const dim3 grid((unsigned)((d.nv + kChunkVel - 1) / kChunkVel));
     const size_t lds = (size_t)d.nc * (2 * kChunkVel + 1) * sizeof(double);
@@ -1692,7 +1705,7 @@ template <class T> __global__ __launch_bounds__(kBlock) void k_zero(T* a, T* b, 
 
 template <class T, int NF>
 void launch_micro_nf(const Dev& d, const Bufs& b, const Work& w, const int64_t* color_off, int64_t n_colors,
-                     int n_micro, hipStream_t st) {
+                     int n_micro, bool beside_blocks, hipStream_t st) {
   const std::vector<int64_t> seq = sweep_sequence(color_off, n_colors, n_micro);
   if (seq.empty()) {
     // no sweep: the increments of Eq. 33 stay zero
@@ -1701,7 +1714,11 @@ void launch_micro_nf(const Dev& d, const Bufs& b, const Work& w, const int64_t* 
     hipLaunchKernelGGL(k_zero<T>, dim3(nb), dim3(kBlock), 0, st, (T*)b.dG, (T*)b.dR, n);
     return;
   }
-  if (launch_micro_chunk<T, NF>(d, b, w, color_plan(color_off, n_colors), (int)seq.size(), st)) return;
+  const ColorPlan pl = color_plan(color_off, n_colors);
+  if (chunk_sweeps(d, pl, color_off, seq, sizeof(T), beside_blocks)) {
+    launch_micro_chunk<T, NF>(d, b, w, pl, (int)seq.size(), st);
+    return;
+  }
   int64_t nonempty = 0;
   for (int64_t c = 0; c < n_colors; ++c) nonempty += color_off[c + 1] > color_off[c];
   constexpr int V = 16 / sizeof(T);  // 16-byte vectors: four FP32 or two FP64 velocities
@@ -1724,11 +1741,11 @@ void launch_micro_nf(const Dev& d, const Bufs& b, const Work& w, const int64_t* 
 
 template <class T>
 void launch_micro(const Dev& d, const Bufs& b, const Work& w, const int64_t* color_off, int64_t n_colors, int n_micro,
-                  hipStream_t st) {
+                  bool beside_blocks, hipStream_t st) {
   if (d.mf == 4)
-    launch_micro_nf<T, 4>(d, b, w, color_off, n_colors, n_micro, st);
+    launch_micro_nf<T, 4>(d, b, w, color_off, n_colors, n_micro, beside_blocks, st);
   else
-    launch_micro_nf<T, kMaxFaces>(d, b, w, color_off, n_colors, n_micro, st);
+    launch_micro_nf<T, kMaxFaces>(d, b, w, color_off, n_colors, n_micro, beside_blocks, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -1885,8 +1902,8 @@ template void launch_boundary_faces<float>(const Dev&, const Bufs&, const Work&,
                                            const int32_t*, int64_t, hipStream_t);
 template void launch_residual<double>(const Dev&, const Bufs&, const Work&, void*, void*, int, hipStream_t);
 template void launch_residual<float>(const Dev&, const Bufs&, const Work&, void*, void*, int, hipStream_t);
-template void launch_micro<double>(const Dev&, const Bufs&, const Work&, const int64_t*, int64_t, int, hipStream_t);
-template void launch_micro<float>(const Dev&, const Bufs&, const Work&, const int64_t*, int64_t, int, hipStream_t);
+template void launch_micro<double>(const Dev&, const Bufs&, const Work&, const int64_t*, int64_t, int, bool, hipStream_t);
+template void launch_micro<float>(const Dev&, const Bufs&, const Work&, const int64_t*, int64_t, int, bool, hipStream_t);
 template void launch_update<double>(const Dev&, const Bufs&, const Work&, int64_t, hipStream_t);
 template void launch_update<float>(const Dev&, const Bufs&, const Work&, int64_t, hipStream_t);
 

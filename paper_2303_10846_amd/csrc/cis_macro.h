@@ -74,6 +74,7 @@ struct MacroSweeps {
   int64_t polls_from = 0;
   int32_t redone = 0;  // calls that went on with a launch per colour after a wait ran out
   bool ready() const { return plan.m > 0 && (plan.local || laid_out); }  // the sweeps can be one launch
+  bool in_blocks() const { return ready() && !plan.local; }
 };
 
 // Tag 0, that of no window, in every word of the exchange buffer
