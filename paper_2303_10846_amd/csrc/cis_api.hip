@@ -434,10 +434,18 @@ cis_status wall_faces(cis_state* s, int32_t tag, std::vector<cis_wall_face>& out
   return CIS_OK;
 }
 
+int64_t micro_stage_launches(const cis_state* s, bool beside_blocks) {
+  return micro_launches(s->dev, s->mesh->color_off.data(), s->mesh->n_colors, s->num.n_micro,
+                        s->precision == CIS_FP64 ? sizeof(double) : sizeof(float), beside_blocks);
+}
+constexpr int64_t kOtherLaunches = 6;  // of an iteration besides the macro and micro stages
+
 // Steps 2-6, iterations first .. n_iter - 1, on the state's stream, with the work arrays `w`; mark(it, k) runs between
-// the stages.  one_launch: the macro sweeps in one launch where the mesh fits one (cis_macro.h), else one per colour.
+// the stages.  one_launch: the macro sweeps in one launch where the mesh fits one (cis_macro.h), else one per colour;
+// beside_blocks: the form of the micro sweeps (launch_micro).
 template <class Mark>
-cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t first, int32_t n_iter, bool one_launch, Mark&& mark) {
+cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t first, int32_t n_iter, bool one_launch,
+                              bool beside_blocks, Mark&& mark) {
   const cis_mesh* m = s->mesh;
   hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s->stream, w.flag, (int64_t)4);
   return dispatch(s, [&](auto* tp) {
@@ -454,7 +462,7 @@ cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t first, int32_
       launch_residual<T>(s->dev, s->buf, w, s->buf.resG, s->buf.resR, 0, s->stream);
       mark(it, 4);
       launch_micro<T>(s->dev, s->buf, w, m->color_off.data(), m->n_colors, s->num.n_micro,
-                      s->sweeps.in_blocks(), s->stream);
+                      beside_blocks, s->stream);
       mark(it, 5);
       launch_update<T>(s->dev, s->buf, w, it, s->stream);
       mark(it, 6);
@@ -465,13 +473,17 @@ cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t first, int32_
 
 // The iterations and their residual history (Step 7) and positivity flags on the host; synchronises.  Where a wait of
 // the macro sweeps ran out, the state is still that of the last complete iteration, and the rest of them follow with a
-// launch per colour.  one (or NULL): the iterations whose macro stage was one launch.
+// launch per colour.  launches (or NULL): those of the macro and the micro stage.
 template <class Mark>
-cis_status run_iterations(cis_state* s, const Work& w, int32_t n_iter, double* res_hist, int32_t* one, Mark&& mark) {
-  int32_t done = 0, wrong = 0;
-  lay_out_blocks(s->dev, s->sweeps, s->stream);
-  for (bool one_launch = true;; one_launch = false) {
-    const cis_status st = enqueue_iterations(s, w, done, n_iter, one_launch, mark);
+cis_status run_iterations(cis_state* s, const Work& w, int32_t n_iter, double* res_hist, int64_t* launches, Mark&& mark) {
+  int32_t done = 0, wrong = 0, one = 0;
+  bool one_launch = s->sweeps.plan.local;
+  if (!one_launch && s->sweeps.plan.m > 0)
+    one_launch = blocks_pay(s->sweeps, s->num.n_macro, kOtherLaunches + micro_stage_launches(s, true));
+  if (one_launch) lay_out_blocks(s->dev, s->sweeps, s->stream);
+  const bool beside_blocks = one_launch && s->sweeps.in_blocks();
+  for (;; one_launch = false) {
+    const cis_status st = enqueue_iterations(s, w, done, n_iter, one_launch, beside_blocks, mark);
     if (st != CIS_OK) return st;
     int32_t flag[4] = {0, 0, 0, 0};
     HIP_TRY(hipMemcpyAsync(flag, w.flag, sizeof(flag), hipMemcpyDeviceToHost, s->stream));
@@ -479,10 +491,16 @@ cis_status run_iterations(cis_state* s, const Work& w, int32_t n_iter, double* r
       HIP_TRY(hipMemcpyAsync(res_hist, w.res, 6 * (size_t)n_iter * sizeof(double), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
     wrong |= flag[0] & ~kSweepStuck;
-    if (one && one_launch) *one = s->sweeps.ready() ? flag[1] : 0;
+    if (one_launch && s->sweeps.ready()) one = flag[1];
     if (!(flag[0] & kSweepStuck)) break;
     done = std::max(done, flag[1]);
     ++s->sweeps.redone;
+  }
+  if (launches) {
+    const int64_t per_colour =
+        3 + (int64_t)sweep_sequence(s->mesh->color_off.data(), s->mesh->n_colors, s->num.n_macro).size();
+    launches[0] = one + (n_iter - one) * per_colour;
+    launches[1] = n_iter * micro_stage_launches(s, beside_blocks);
   }
   if (wrong) return fail(CIS_E_NONFINITE, "non-finite or non-positive state (flag " + std::to_string(wrong) + ")");
   return CIS_OK;
@@ -1216,24 +1234,18 @@ cis_status cis_iterate(cis_state* s, int32_t n_iter, double* res_hist) {
   auto mark = [&](int32_t it, int k) {
     if (s->profile) (void)hipEventRecord(ev[7 * (size_t)it + k], s->stream);
   };
-  int32_t one = 0;
-  const cis_status st = run_iterations(s, s->work, n_iter, res_hist, &one, mark);
+  int64_t stage[2] = {0, 0};
+  const cis_status st = run_iterations(s, s->work, n_iter, res_hist, s->profile ? stage : nullptr, mark);
   if (s->profile) {
-    const cis_mesh* m = s->mesh;
     (void)hipStreamSynchronize(s->stream);
-    const int64_t nmac = (int64_t)sweep_sequence(m->color_off.data(), m->n_colors, s->num.n_macro).size();
-    const int64_t nmic = micro_launches(s->dev, m->color_off.data(), m->n_colors, s->num.n_micro,
-                                        s->precision == CIS_FP64 ? sizeof(double) : sizeof(float),
-                                        s->sweeps.in_blocks());
-    for (int32_t it = 0; it < n_iter; ++it) {
-      const int64_t per_it[6] = {1, 1, it < one ? 1 : 3 + nmac, 1, nmic, 3};
+    const int64_t per_call[6] = {n_iter, n_iter, stage[0], n_iter, stage[1], 3 * (int64_t)n_iter};
+    for (int k = 0; k < 6; ++k) s->prof_launch[k] += per_call[k];
+    for (int32_t it = 0; it < n_iter; ++it)
       for (int k = 0; k < 6; ++k) {
         float ms = 0.0f;
         (void)hipEventElapsedTime(&ms, ev[7 * (size_t)it + k], ev[7 * (size_t)it + k + 1]);
         s->prof_ms[k] += ms;
-        s->prof_launch[k] += per_it[k];
       }
-    }
     for (auto& e : ev) (void)hipEventDestroy(e);
   }
   return st;

@@ -96,6 +96,13 @@ void lay_out_blocks(const Dev& d, MacroSweeps& f, hipStream_t st);
 // W and q alone, and the host redoes the iteration (or the Krylov step) and the rest with a launch per colour.
 constexpr int32_t kSweepStuck = 8;
 
+// Whether the sweeps in blocks pay for n_pairs pairs in an iteration of `others` further launches.  Their launch is
+// cooperative, on a hardware queue of its own: besides the 20 us around it every later launch of the stream starts
+// 1.2 us later, until the host next waits (1 000 cells, 21 micro relaxations: 82 -> 109 us).  They save about 10 us and
+// 2 us a relaxation (stage on 1 000 hexahedra 49 -> 31 us with 3 relaxations, 104 -> 52 with 21; on 1 296 tetrahedra
+// 47 -> 32 with 5, 143 -> 60 with 41).
+bool blocks_pay(const MacroSweeps& f, int n_pairs, int64_t others);
+
 // Step 4 in one launch (spectral radii, right-hand side, n_macro forward + backward sweep pairs and the
 // predicted equilibrium), after lay_out_blocks.  false: not launched, the mesh takes a launch per colour.
 bool launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, MacroSweeps& f, int n_macro, hipStream_t st);

@@ -830,6 +830,10 @@ void lay_out_blocks(const Dev& d, MacroSweeps& f, hipStream_t st) {
   }
 }
 
+bool blocks_pay(const MacroSweeps& f, int n_pairs, int64_t others) {
+  return 10.0 + 2.0 * sequence_length(f.plan.m, n_pairs) > 1.2 * (double)others;
+}
+
 bool launch_macro_sweeps(const Dev& d, const Bufs& b, const Work& w, MacroSweeps& f, int n_macro, hipStream_t st) {
   if (!f.ready()) return false;
   int steps = sequence_length(f.plan.m, n_macro);

@@ -147,3 +147,25 @@ def test_blocks_are_laid_out_by_the_first_call_that_sweeps():
     s = _solver("hex", 6)
     s.iterate_noalloc(1)
     assert s.debug_sweeps()["form"] == "blocks"
+
+
+@pytest.mark.parametrize("n_macro,n_micro,one", [(40, 2, True), (2, 2, True), (2, 50, False), (40, 50, True),
+                                                 (0, 2, False)])
+def test_blocks_only_where_they_pay(n_macro, n_micro, one):
+    """Launches of a stream start later after the cooperative one: with few macro and many micro sweeps the launches
+    per colour are the faster form."""
+    import oracle
+    from paper_2303_10846_amd.binding import Solver
+    c = configs.open_box_case(n=10, nv_side=4, kind="hex")
+    num = dict(c["num"], n_macro=n_macro, n_micro=n_micro)
+    o = oracle.Oracle(c, num=num)
+    o.init_equilibrium(c["W0"])
+    s = Solver(c, num=num)
+    s.init_equilibrium(c["W0"])
+    s.profile(True)
+    s.iterate(2)
+    o.iterate(2)
+    assert s.profile_read()["macro"][1] == (2 if one else 2 * (3 + (2 * n_macro + 1 if n_macro else 0)))
+    assert s.debug_sweeps()["form"] == ("blocks" if one else "not laid out")
+    for x, y in zip(s.get_state(), o.get_state()):
+        assert rel(x, y) <= TOL["fp64"]
