@@ -40,7 +40,7 @@ struct BlockRecord {
   uint8_t read_color[kBlockReads];
   int16_t ack[kBlockMax];              // the workgroups that read this one's
 };
-constexpr int kBlockCands = 6;  // windows tried
+constexpr int kBlockCands = 8;  // most windows tried: the divisors of a period of up to 30
 struct BlockPlan {
   int blocks = 0;    // 0: the mesh is too large or runs in one workgroup
   int h = 0;
