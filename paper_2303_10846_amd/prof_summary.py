@@ -38,8 +38,14 @@ def _find(d: str, suffix: str) -> str:
 
 
 def short_name(k: str) -> str:
-    k = k.replace("(anonymous namespace)::", "").split("(")[0]
-    return k.replace("void ", "").strip()
+    """The kernel with its template arguments, without its parameter list."""
+    k = k.replace("(anonymous namespace)::", "").replace("void ", "")
+    depth = 0
+    for at, ch in enumerate(k):
+        depth += (ch == "<") - (ch == ">")
+        if ch == "(" and depth == 0:
+            return k[:at].strip()
+    return k.strip()
 
 
 def stats(trace_dir: str, out: str, command: str, top: int = 16, bench_log: str = None):

@@ -45,3 +45,12 @@ def test_sq_valu_issue_time(tmp_path):
     text = open(out).read()
     assert "valu_issue_us: 1000.0" in text
     assert f"valu_per_wave: {n / 1000.0:.1f}" in text
+
+
+def test_short_name_keeps_the_template_arguments():
+    f = prof_summary.short_name
+    assert f("void cis::k_face<float, 3, 4, 256, false>(cis::Dev, cis::Bufs, cis::Work, int const*)") == \
+        "cis::k_face<float, 3, 4, 256, false>"
+    assert f("void cis::(anonymous namespace)::k_macro_sweeps<4, (cis::(anonymous namespace)::Form)1>(cis::Dev, "
+             "double const*)") == "cis::k_macro_sweeps<4, (cis::Form)1>"
+    assert f("cis::k_reduce_res(long, double const*, double*, int*, int)") == "cis::k_reduce_res"
