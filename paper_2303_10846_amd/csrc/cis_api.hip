@@ -485,28 +485,37 @@ cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t first, int32_
 
 // The iterations and their residual history (Step 7) and positivity flags on the host; synchronises.  Where a wait of
 // the macro sweeps ran out, the state is still that of the last complete iteration, and the rest of them follow with a
-// launch per colour.  launches (or NULL): those of the macro and the micro stage.
+// launch per colour; kSweepPiece bounds the iterations that such a wait makes idle (a wait of the host in 256
+// iterations, 20 us in at least 40 ms).  launches (or NULL): those of the macro and the micro stage.
+constexpr int32_t kSweepPiece = 256;
 template <class Mark>
-cis_status run_iterations(cis_state* s, const Work& w, int32_t n_iter, double* res_hist, int64_t* launches, Mark&& mark) {
+cis_status run_iterations(cis_state* s, const Work& w, int32_t n_iter, double* res_hist, int64_t* launches,
+                          Mark&& mark) {
   int32_t done = 0, wrong = 0, one = 0;
   bool one_launch = s->sweeps.plan.local;
   if (!one_launch && s->sweeps.plan.m > 0)
     one_launch = blocks_pay(s->sweeps, s->num.n_macro, kOtherLaunches + micro_stage_launches(s, true));
   if (one_launch) lay_out_blocks(s->dev, s->sweeps, s->stream);
   const bool beside_blocks = one_launch && s->sweeps.in_blocks();
-  for (;; one_launch = false) {
-    const cis_status st = enqueue_iterations(s, w, done, n_iter, one_launch, beside_blocks, mark);
+  while (done < n_iter) {
+    const int32_t end = one_launch && beside_blocks ? std::min(n_iter, done + kSweepPiece) : n_iter;
+    const cis_status st = enqueue_iterations(s, w, done, end, one_launch, beside_blocks, mark);
     if (st != CIS_OK) return st;
     int32_t flag[4] = {0, 0, 0, 0};
     HIP_TRY(hipMemcpyAsync(flag, w.flag, sizeof(flag), hipMemcpyDeviceToHost, s->stream));
     if (res_hist)
-      HIP_TRY(hipMemcpyAsync(res_hist, w.res, 6 * (size_t)n_iter * sizeof(double), hipMemcpyDeviceToHost, s->stream));
+      HIP_TRY(hipMemcpyAsync(res_hist + 6 * (size_t)done, w.res + 6 * (size_t)done,
+                             6 * (size_t)(end - done) * sizeof(double), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
     wrong |= flag[0] & ~kSweepStuck;
-    if (one_launch && s->sweeps.ready()) one = flag[1];
-    if (!(flag[0] & kSweepStuck)) break;
-    done = std::max(done, flag[1]);
-    ++s->sweeps.redone;
+    const bool stuck = flag[0] & kSweepStuck;
+    const int32_t reached = stuck ? std::max(done, flag[1]) : end;
+    if (one_launch && s->sweeps.ready()) one += reached - done;
+    done = reached;
+    if (stuck) {
+      one_launch = false;
+      ++s->sweeps.redone;
+    }
   }
   if (launches) {
     const int64_t per_colour =

@@ -169,3 +169,20 @@ def test_blocks_only_where_they_pay(n_macro, n_micro, one):
     assert s.debug_sweeps()["form"] == ("blocks" if one else "not laid out")
     for x, y in zip(s.get_state(), o.get_state()):
         assert rel(x, y) <= TOL["fp64"]
+
+
+@pytest.mark.parametrize("first", [None, 0, 255, 256, 300])
+def test_long_calls_run_in_pieces(first):
+    """A call of more iterations than one piece (256), undisturbed and with a wait that runs out in either piece."""
+    a, b = _solver("hex", 6, nv_side=3), _solver("hex", 6, nv_side=3)
+    want = np.concatenate([a.iterate(100), a.iterate(100), a.iterate(100), a.iterate(40)])
+    if first is not None:
+        b.debug_sweeps(polls=0, first=first)
+    b.profile(True)
+    got = b.iterate(340)
+    assert b.debug_sweeps()["redone"] == (first is not None)
+    one = 340 if first is None else first
+    assert b.profile_read()["macro"][1] == one + (340 - one) * (3 + 81)
+    assert rel(got, want) <= TOL["fp64"]
+    for x, y in zip(b.get_state(), a.get_state()):
+        assert rel(x, y) <= TOL["fp64"]
