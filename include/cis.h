@@ -351,7 +351,7 @@ typedef struct {
 } cis_adjoint_info;
 
 /* Device workspace of cis_adjoint_solve for GMRES(restart), in bytes: (restart + 4) vectors of
-   2 n_cells n_vel + 12 n_cells doubles, plus reduction scratch and 24 doubles per cell. */
+   2 n_cells n_vel + 12 n_cells doubles, plus reduction scratch and 26 doubles per cell. */
 cis_status cis_adjoint_required_bytes(const cis_state* s, int32_t restart, int64_t* bytes);
 
 /* Discrete adjoint at the current (steady) state: solves (dR/dx)^T lam = (dJ/dx)^T by restarted GMRES

@@ -678,7 +678,8 @@ template <int NF> __global__ __launch_bounds__(kBlock) void k_recon_vjp(Dev d, B
 }
 
 // Row staging of the face terms: 256 threads where the two rows take at most 38 KB of LDS (four workgroups a
-// compute unit), 512 up to 77 KB (two), none beyond.
+// compute unit up to 2 405 velocities, as 2.4 KB of sums and the face state come on top; three up to 2 432), 512 up
+// to 77 KB (two), none beyond.
 template <bool HasV, int NF> void launch_face_vjp(const Dev& d, const Bufs& b, const AdjArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)d.nf);
   const size_t row = 2 * sizeof(double) * (size_t)d.nv;

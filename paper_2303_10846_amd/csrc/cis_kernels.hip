@@ -1480,7 +1480,8 @@ __global__ __launch_bounds__(kChunkThreads) void k_micro_chunk(Dev d, Bufs b, Wo
 }
 
 // Which sweeps run in one launch: those estimated at less than 0.9 of the launches per colour.  A launch takes 3.6 us
-// (4.6 beside macro sweeps in blocks: launches of a stream start later after a cooperative one) and a stream of its values.  In one launch a relaxation costs its latency, which grows with the cells of a colour
+// (4.6 beside macro sweeps in blocks: launches of a stream start later after a cooperative one) and the time of its
+// values.  In one launch a relaxation costs its latency, which grows with the cells of a colour
 // that a lane's workgroup goes through, or the reading of their geometry by every workgroup, at 8.4 TB/s out of the L2
 // (1.6 times as long where a colour takes two rounds of 256 cells), besides a start that grows with the mesh.  Beyond
 // kChunkResident velocities the workgroups no longer run all at once.  Coefficients from 664 shapes (1 to 1 000 cells of

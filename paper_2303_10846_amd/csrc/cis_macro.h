@@ -27,7 +27,9 @@ constexpr int kBlockWaves = 8;            // wavefronts of a workgroup, each wit
 constexpr int kWideBlockWaves = 16;       // .. of meshes whose blocks do not fit 8
 constexpr int kBlockVals = 512;           // increments in LDS: of its wavefronts' slots, then of other cells read
 constexpr int kBlockReads = 256;          // increments read from other workgroups per window
-constexpr int kBlockCells = 54000;        // largest mesh (3 bytes of LDS a cell while the plan is made)
+// Largest mesh: 3 bytes of LDS a cell while the plan is made; with 6 face slots the wavefronts end it earlier: 16 of 8
+// cells, so 256 blocks of 128 own cells, 32 768, could hold no neighbours (24 389 fit)
+constexpr int kBlockCells = 54000;
 constexpr int kBlockSlots = 16 * kWideBlockWaves;  // cells that a workgroup relaxes (half of them with 6 face slots)
 constexpr int kBlockMax = 256;            // workgroups
 struct BlockRecord {
@@ -59,7 +61,7 @@ inline __host__ __device__ int64_t sweep_words(int64_t nc) { return 2 * (kSweepW
 // rest of the call to a launch per colour, which waits for nothing.
 constexpr uint32_t kSweepPolls = 1u << 18;
 
-// Largest tag of a window: tags are compared as increasing numbers, and a launch (up to 3 million steps) takes one a step.
+// Largest tag of a window: tags are compared as increasing numbers; a launch (up to 3 million steps) takes one a step.
 constexpr uint32_t kSweepTagMax = 0x7fffffffu;
 
 // State of the sweeps of one cis_state: the plans, the exchange buffer (device) and the tag of
@@ -86,9 +88,9 @@ SweepPlan sweep_plan(const Dev& d, const int64_t* color_off, int64_t n_colors);
 // Blocks for a mesh of nc cells on the current device (0: none, the mesh is too large or runs in one workgroup).
 int block_count(const SweepPlan& pl, const Dev& d, int64_t nc);
 
-// Before the first sweeps of a state (its other calls don't pay for it: 0.15 ms): finds the longest window that fits and
-// lays out f.block.rec on the stream, which it waits for.  Where none fits, or the device refuses a launch, the state keeps a
-// launch per colour (plan.m = 0).
+// Before the first sweeps of a state (its other calls don't pay for it: 0.12 ms on 1 296 cells, 0.5 on 50 400): finds
+// the longest window that fits and lays out f.block.rec on the stream, which it waits for.  Where none fits, or the
+// device refuses a launch, the state keeps a launch per colour (plan.m = 0).
 void lay_out_blocks(const Dev& d, MacroSweeps& f, hipStream_t st);
 
 // Bit of Work::flag[0] set when a wait of the sweeps in blocks ran out.  Its results are then not valid, and from there
