@@ -134,7 +134,7 @@ def _setup(kind, n, nv_side):
     ("hex", 1, 2, "workgroup"), ("tet", 3, 3, "workgroup"), ("hex", 5, 10, "workgroup"),
     ("hex", 6, 10, "blocks"), ("tet", 4, 1, "blocks"), ("tet", 6, 10, "blocks"), ("mixed", 5, 3, "blocks"),
     ("hex", 10, 2, "blocks"), ("tet", 14, 3, "blocks"), ("tet", 20, 4, "wide blocks"), ("hex", 29, 3, "wide blocks"),
-    ("tet", 21, 3, "colours"), ("hex", 33, 2, "colours"),
+    ("tet", 21, 3, "colours"),
 ])
 def test_transposed_macro_sweeps(kind, n, pairs, form):
     import torch

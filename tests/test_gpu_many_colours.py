@@ -51,8 +51,9 @@ def test_macro_sweeps_of_many_colours(kind, n, colours, n_macro, form):
     assert s.debug_sweeps()["form"] == form
 
 
-@pytest.mark.parametrize("kind,n,colours", [("hex", 6, 5), ("tet", 6, 13)])
-def test_adjoint_sweeps_of_many_colours(kind, n, colours):
+@pytest.mark.parametrize("kind,n,colours,form", [("hex", 6, 5, "blocks"), ("tet", 6, 13, "blocks"),
+                                                 ("hex", 6, 17, "colours"), ("mixed", 5, 18, "colours")])
+def test_adjoint_sweeps_of_many_colours(kind, n, colours, form):
     """Transposed macro sweeps: the split colouring against the mesh's own, the same relaxations."""
     import torch
     from paper_2303_10846_amd.binding import Solver
@@ -66,5 +67,5 @@ def test_adjoint_sweeps_of_many_colours(kind, n, colours):
     b.set_state(*state)
     t = torch.randn(s.nc, 6, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
     x, y = (k.debug_adjoint_sweeps(t, True, 5).cpu().numpy() for k in (s, b))
-    assert b.debug_sweeps()["form"] == "blocks"
+    assert b.debug_sweeps()["form"] == form
     assert rel(y, x) < TOL
