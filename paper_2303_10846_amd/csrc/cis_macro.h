@@ -79,7 +79,7 @@ struct MacroSweeps {
   bool in_blocks() const { return ready() && !plan.local; }
 };
 
-// Tag 0, that of no window, in every word of the exchange buffer
+// Tag 0, that of no window, in every word of the exchange buffer (and the links of the layout, used before any tag)
 void clear_sweep_words(const MacroSweeps& f, int64_t nc, hipStream_t st);
 
 // The colours of a mesh: m = 0 where there are more than kSweepColors.
@@ -88,7 +88,7 @@ SweepPlan sweep_plan(const Dev& d, const int64_t* color_off, int64_t n_colors);
 // Blocks for a mesh of nc cells on the current device (0: none, the mesh is too large or runs in one workgroup).
 int block_count(const SweepPlan& pl, const Dev& d, int64_t nc);
 
-// Before the first sweeps of a state (its other calls don't pay for it: 0.12 ms on 1 296 cells, 0.5 on 50 400): finds
+// Before the first sweeps of a state (its other calls don't pay for it: 0.1 ms on 1 296 cells, 0.35 on 50 400): finds
 // the longest window that fits and lays out f.block.rec on the stream, which it waits for.  Where none fits, or the
 // device refuses a launch, the state keeps a launch per colour (plan.m = 0).
 void lay_out_blocks(const Dev& d, MacroSweeps& f, hipStream_t st);

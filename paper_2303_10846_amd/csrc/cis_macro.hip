@@ -578,7 +578,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl
   extern __shared__ int16_t plan_lds[];
   int16_t* const loc = plan_lds;  // [nc] place of a cell's increment
   uint8_t* const st = reinterpret_cast<uint8_t*>(plan_lds + d.nc);  // [nc]
-  __shared__ int wave_sum[kPlanThreads / 64];
+  __shared__ int part[kSweepColors + 2][kPlanThreads / 64];
   const int nc = (int)d.nc, m = pl.m, tid = (int)threadIdx.x, h = cand.h[blockIdx.y];
   const int period = m > 1 ? 2 * (m - 1) : 1, phases = h < period ? period / h : 1;
   for (int i = tid; i < nc; i += kPlanThreads) st[i] = 0;
@@ -615,64 +615,66 @@ __global__ __launch_bounds__(kPlanThreads) void k_block_plan(Dev d, SweepPlan pl
       if ((st[i] & kNeed) && !(st[i] & kOwn)) st[i] |= kRead;
     __syncthreads();
   }
-  // places, in cell order: rank of a set flag among those of lower threads, and their sum
-  auto rank = [&](bool flag, int& total) {
-    const uint64_t mask = __ballot(flag);
-    const int lane = tid & 63, wv = tid >> 6;
-    if (lane == 0) wave_sum[wv] = __popcll(mask);
-    __syncthreads();
-    int before = 0;
-    total = 0;
-    for (int k = 0; k < kPlanThreads / 64; ++k) {
-      before += k < wv ? wave_sum[k] : 0;
-      total += wave_sum[k];
+  // Counts, then places in cell order: wavefront wv takes the wv-th part of a colour's cells, or of all cells, so that
+  // its places follow those of lower wavefronts.  Rows of `part`: the slots of each colour, other values, values read.
+  constexpr int kWaves = kPlanThreads / 64;
+  const int lane = tid & 63, wv = tid >> 6;
+  const auto cells = [&](int row, uint8_t with, uint8_t without, auto&& put) {
+    const int first = row < m ? pl.off[row] : 0, n = row < m ? pl.n[row] : nc;
+    const int j1 = first + (int)((int64_t)n * (wv + 1) / kWaves);
+    int found = 0;
+    for (int j0 = first + (int)((int64_t)n * wv / kWaves); j0 < j1; j0 += 64) {
+      const int i = j0 + lane;
+      const bool set = i < j1 && (st[i] & with) && !(st[i] & without);
+      const uint64_t mask = __ballot(set);
+      if (set) put(i, found + __popcll(mask & ((1ull << lane) - 1ull)));
+      found += __popcll(mask);
     }
-    __syncthreads();
-    return before + __popcll(mask & ((1ull << lane) - 1ull));
+    return found;
+  };
+  for (int c = 0; c < m + 2; ++c) {
+    const int found = cells(c, c < m ? kSlot : c == m ? kValue : kRead, c == m ? kSlot : 0, [](int, int) {});
+    if (lane == 0) part[c][wv] = found;
+  }
+  __syncthreads();
+  const auto sum = [&](int row, int waves) {
+    int n = 0;
+    for (int k = 0; k < waves; ++k) n += part[row][k];
+    return n;
   };
   int waves = 0;
-  BlockRecord* const r = bp.rec + blockIdx.x;
-  if (write && tid < kWideBlockWaves) r->color[tid] = -1;
-  __syncthreads();
-  for (int c = 0; c < m; ++c) {
-    int found = 0;
-    for (int i0 = 0; i0 < pl.n[c]; i0 += kPlanThreads) {
-      const int i = pl.off[c] + i0 + tid;
-      const bool slot = i0 + tid < pl.n[c] && (st[i] & kSlot);
-      int total;
-      const int at = rank(slot, total);
-      if (slot) loc[i] = (int16_t)min(waves * cw + found + at, 32767);
-      found += total;
-    }
-    const int w = (found + cw - 1) / cw;
-    if (write && tid < w && waves + tid < kWideBlockWaves) r->color[waves + tid] = c;
-    waves += w;
-  }
-  const int slots = waves * cw;
-  int others = 0, reads = 0;
-  for (int i0 = 0; i0 < nc; i0 += kPlanThreads) {
-    const int i = i0 + tid;
-    const uint8_t f = i < nc ? st[i] : (uint8_t)0;
-    int total;
-    const int at = rank((f & kValue) && !(f & kSlot), total);
-    if ((f & kValue) && !(f & kSlot)) loc[i] = (int16_t)min(slots + others + at, 32767);
-    others += total;
-    const int ar = rank((f & kRead) != 0, total);
-    if (write && (f & kRead)) {
-      const int at = min(reads + ar, kBlockReads - 1);
-      int c = 0;
-      while (c + 1 < m && i >= pl.off[c + 1]) ++c;
-      r->read[at] = loc[i];
-      r->read_color[at] = (uint8_t)c;
-      atomicOr(&bp.link[bp.owner[i] * (kBlockMax / 32) + blockIdx.x / 32], 1u << (blockIdx.x % 32));
-    }
-    reads += total;
-  }
+  for (int c = 0; c < m; ++c) waves += (sum(c, kWaves) + cw - 1) / cw;
+  const int slots = waves * cw, others = sum(m, kWaves), reads = sum(m + 1, kWaves);
   if (!write) {
     const bool fits = slots + others <= kBlockVals && reads <= kBlockReads;
     if (tid == 0) atomicMax(&bp.most[blockIdx.y], fits ? waves : kTooMany);
     return;
   }
+  BlockRecord* const r = bp.rec + blockIdx.x;
+  if (tid < kWideBlockWaves) {  // the colour of each wavefront of slots
+    int c = 0, end = 0;
+    for (; c < m; ++c) {
+      end += (sum(c, kWaves) + cw - 1) / cw;
+      if (tid < end) break;
+    }
+    r->color[tid] = c < m ? c : -1;
+  }
+  for (int c = 0, base = 0; c < m + 1; ++c) {
+    const int before = base + sum(c, wv);
+    (void)cells(c, c < m ? kSlot : kValue, c < m ? 0 : kSlot,
+                [&](int i, int at) { loc[i] = (int16_t)min(before + at, 32767); });
+    base += c < m ? (sum(c, kWaves) + cw - 1) / cw * cw : 0;
+  }
+  __syncthreads();
+  const int read0 = sum(m + 1, wv);
+  (void)cells(m + 1, kRead, 0, [&](int i, int at) {
+    at = min(read0 + at, kBlockReads - 1);
+    int c = 0;
+    while (c + 1 < m && i >= pl.off[c + 1]) ++c;
+    r->read[at] = loc[i];
+    r->read_color[at] = (uint8_t)c;
+    atomicOr(&bp.link[bp.owner[i] * (kBlockMax / 32) + blockIdx.x / 32], 1u << (blockIdx.x % 32));
+  });
   for (int v = tid; v < kBlockVals; v += kPlanThreads) r->cell[v] = -1;
   __syncthreads();
   if (tid == 0) r->reads = reads;
@@ -720,13 +722,10 @@ bool run(const Dev& d, bool adjoint, MacroSweeps& s, void** args, hipStream_t st
   return false;
 }
 
-__global__ __launch_bounds__(256) void k_clear_words(uint64_t* words, int64_t n) {
+// Zeros in the exchange words, and in what the layout of the blocks accumulates
+__global__ __launch_bounds__(256) void k_clear_words(uint64_t* words, int64_t n, BlockPlan bp) {
   const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (k < n) words[k] = 0;
-}
-
-__global__ __launch_bounds__(256) void k_clear_plan(BlockPlan bp) {
-  const int k = (int)(blockIdx.x * 256 + threadIdx.x);
   if (k < kBlockLink) bp.link[k] = 0;
   if (k < kBlockCands) bp.most[k] = 0;
 }
@@ -750,7 +749,8 @@ uint32_t take_polls(MacroSweeps& f) { return f.polls_from > 0 ? (--f.polls_from,
 
 void clear_sweep_words(const MacroSweeps& f, int64_t nc, hipStream_t st) {
   const int64_t n = sweep_words(nc);
-  hipLaunchKernelGGL(k_clear_words, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, f.words, n);
+  static_assert(2 * 8 * kBlockMax >= kBlockLink && kBlockLink >= kBlockCands, "words cover the links");
+  hipLaunchKernelGGL(k_clear_words, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, f.words, n, f.block);
 }
 
 SweepPlan sweep_plan(const Dev& d, const int64_t* color_off, int64_t n_colors) {
@@ -804,7 +804,6 @@ void lay_out_blocks(const Dev& d, MacroSweeps& f, hipStream_t st) {
   BlockCands c = block_windows(f.plan.m);
   int32_t most[kBlockCands] = {};
   clear_sweep_words(f, d.nc, st);
-  hipLaunchKernelGGL(k_clear_plan, dim3((kBlockLink + 255) / 256), dim3(256), 0, st, f.block);
   hipLaunchKernelGGL(k_block_plan, dim3(blocks, c.n), dim3(kPlanThreads), 3 * (size_t)d.nc, st, d, f.plan, f.block, c,
                      cells_per_wave(d), 0);
   hipError_t e = hipGetLastError();
