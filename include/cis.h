@@ -293,12 +293,11 @@ cis_status cis_wall_coefficients(cis_state* s, int32_t tag, const cis_wall_ref* 
 cis_status cis_debug_stage(cis_state* s, int32_t which, double* out_host);
 
 /* The macro sweeps of a state (for checks).  info (host [5], or NULL): the form of the stage (0 a launch per colour,
-   1 one workgroup, 2 blocks of 8 wavefronts, 3 blocks of 16, 4 blocks not laid out yet: the first call that sweeps
-   does), the steps of a window and the number of blocks (0 unless
-   in blocks), how many calls went on with a launch per colour because a wait of the sweeps in blocks ran out (the
-   results are the same), and the tag of their last window.  polls >= 0 sets the polls after which a wait gives up, from
-   the from-th launch after this call on (0: the first); tag >= 0 (not below the last) moves the tags up to it; -1 leaves
-   either alone. */
+   1 one workgroup, 2 blocks of 8 wavefronts, 3 blocks of 16, 4 blocks that the first call that sweeps will lay out),
+   the steps of a window and the number of blocks (0 unless in blocks), how many calls went on with a launch per colour
+   because a wait of the sweeps in blocks ran out (the results are the same), and the tag of their last window.
+   polls >= 0 sets the polls after which a wait gives up, from the from-th launch after this call on (0: the first);
+   tag >= 0 (not below the last) moves the tags up to it; -1 leaves either alone. */
 cis_status cis_debug_sweeps(cis_state* s, int64_t polls, int64_t from, int64_t tag, int32_t* info);
 
 /* Per-stage device time of cis_iterate, measured with hipEvents recorded on the state's stream between the

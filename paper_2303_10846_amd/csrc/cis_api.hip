@@ -179,8 +179,8 @@ struct cis_state {
   Bufs buf{};
   Work work{};
   MacroSweeps sweeps{};
-  // Gram-Schmidt coefficients, norm and lost-wait mark of the adjoint's Krylov step; their pinned copy, and the event after it (made by
-  // the first adjoint solve)
+  // Gram-Schmidt coefficients, norm and lost-wait mark of the adjoint's Krylov step; their pinned copy, and the event
+  // after it (made by the first adjoint solve)
   double *krylov = nullptr, *krylov_host = nullptr;
   hipEvent_t krylov_copied = nullptr;
   // library-owned device arrays
@@ -316,7 +316,8 @@ void run_vjp(cis_state* s, const double* v, double cJ, const AdjSlots& sl, doubl
 // Rows of boundary faces (width values each, at most 6) from a per-face array, gathered on the device; small arrays are
 // copied whole and the rows taken here (the gathering launch: steady residual of 48 tetrahedra 43 -> 46 us)
 constexpr size_t kCopyWhole = 32 * 1024;
-cis_status gather_boundary(cis_state* s, const double* src, int width, int64_t first, int64_t n, std::vector<double>& h) {
+cis_status gather_boundary(cis_state* s, const double* src, int width, int64_t first, int64_t n,
+                           std::vector<double>& h) {
   h.resize((size_t)width * n);
   if (n == 0) return CIS_OK;
   const bool whole = (size_t)s->mesh->nf * width * sizeof(double) <= kCopyWhole;
@@ -473,8 +474,7 @@ cis_status enqueue_iterations(cis_state* s, const Work& w, int32_t first, int32_
       mark(it, 3);
       launch_residual<T>(s->dev, s->buf, w, s->buf.resG, s->buf.resR, 0, s->stream);
       mark(it, 4);
-      launch_micro<T>(s->dev, s->buf, w, m->color_off.data(), m->n_colors, s->num.n_micro,
-                      beside_blocks, s->stream);
+      launch_micro<T>(s->dev, s->buf, w, m->color_off.data(), m->n_colors, s->num.n_micro, beside_blocks, s->stream);
       mark(it, 5);
       launch_update<T>(s->dev, s->buf, w, it, s->stream);
       mark(it, 6);
@@ -1493,11 +1493,13 @@ cis_status cis_debug_adjoint_sweeps(cis_state* s, int32_t macro, int32_t pairs, 
   } else {
     lay_out_blocks(s->dev, s->sweeps, s->stream);
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s->stream, w.flag, (int64_t)4);
-    launch_adj_macro(s->dev, s->buf, in, out, w.rcf, w.mD, off, s->mesh->n_colors, pairs, &s->sweeps, w.flag, s->stream);
+    const auto macro_sweeps = [&](MacroSweeps* sweeps) {
+      launch_adj_macro(s->dev, s->buf, in, out, w.rcf, w.mD, off, s->mesh->n_colors, pairs, sweeps, w.flag, s->stream);
+    };
+    macro_sweeps(&s->sweeps);
     HIP_TRY(hipMemcpyAsync(&flag, w.flag, sizeof(flag), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
-    if (flag & kSweepStuck)
-      launch_adj_macro(s->dev, s->buf, in, out, w.rcf, w.mD, off, s->mesh->n_colors, pairs, nullptr, w.flag, s->stream);
+    if (flag & kSweepStuck) macro_sweeps(nullptr);
   }
   const cis_status st = device_check("adjoint sweeps");
   if (st != CIS_OK) return st;
@@ -1607,7 +1609,8 @@ cis_status cis_adjoint_solve(cis_state* s, int32_t wall_tag, int32_t ff_tag, int
     else if (precond_pairs == 0)
       launch_precond(s->dev, s->buf, in, out, q);
     else
-      launch_adj_sweeps(s->dev, s->buf, in, out, s->mesh->color_off.data(), s->mesh->n_colors, precond_pairs, false, q);
+      launch_adj_sweeps(s->dev, s->buf, in, out, s->mesh->color_off.data(), s->mesh->n_colors, precond_pairs, false,
+                        q);
   };
   if (macro_pairs > 0) lay_out_blocks(s->dev, s->sweeps, q);
   if (!s->krylov_host && hipHostMalloc((void**)&s->krylov_host, (2 * kMaxRestart + 3) * sizeof(double)) != hipSuccess)
