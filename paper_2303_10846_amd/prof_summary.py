@@ -19,7 +19,8 @@ import hashlib
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = [os.path.join(HERE, "csrc", n) for n in ("cis_kernels.hip", "cis_device.h", "cis_internal.h")]
+KERNEL_SOURCES = [os.path.join(HERE, "csrc", n) for n in ("cis_kernels.hip", "cis_macro.hip", "cis_device.h",
+                                                              "cis_internal.h", "cis_macro.h")]
 
 
 def source_hash() -> str:
